@@ -10,7 +10,8 @@
 
 namespace fd {
 hipError_t run_attn_generic(const AttnParams& p, int dtype, hipStream_t st);
-hipError_t run_attn_combine(const AttnParams& p, int dtype, int log2_units, int skip_single, hipStream_t st);
+hipError_t run_attn_combine(const AttnParams& p, int dtype, hipStream_t st);
+int attn_generic_rows_per_wg();
 bool attn_mfma_supports(int dtype, int head_dim, int page_size);
 size_t draft_select_workspace_bytes(int total_rows, int vocab);
 hipError_t run_draft_select(const void* logits, int dt, long long row_stride, int vocab, float temperature,
@@ -54,6 +55,8 @@ fd_status fail(fd_status code, const char* fmt, ...) {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
+constexpr double GEN_PARTIAL_BYTES = 32.0 * (1 << 20);
+
 struct AttnPlan {
   bool use_mfma;
   int chunk, max_chunks, row_tiles;
@@ -83,7 +86,7 @@ fd_status plan_attn(const fd_attn_args* a, AttnPlan* plan) {
   const int tile_keys = plan->use_mfma ? fd::attn_mfma_tile_keys() : 64;
   if (a->kv_chunk % tile_keys) return fail(FD_ERR_INVALID_ARG, "kv_chunk %d must be a multiple of %d for this kernel", a->kv_chunk, tile_keys);
   long long rows = (long long)a->max_new_rows * G;
-  const int tile_rows = plan->use_mfma ? fd::attn_mfma_rows_per_wg((int)(rows > 128 ? 128 : rows)) : 16;
+  const int tile_rows = plan->use_mfma ? fd::attn_mfma_rows_per_wg((int)(rows > 128 ? 128 : rows)) : fd::attn_generic_rows_per_wg();
   plan->row_tiles = (int)((rows + tile_rows - 1) / tile_rows);
   if (plan->row_tiles < 1) plan->row_tiles = 1;
   if ((long long)plan->row_tiles * a->num_kv_heads > 65535)
@@ -97,15 +100,24 @@ fd_status plan_attn(const fd_attn_args* a, AttnPlan* plan) {
 
   int chunk = a->kv_chunk;
   if (chunk == 0) {
-    // enough (sequence, head, chunk) work-groups to cover 256 CUs x 2 several times over,
-    // but never chunks so short that the split partials rival the KV traffic
-    long long pairs = (long long)(a->batch > 0 ? a->batch : 1) * a->num_kv_heads * plan->row_tiles;
-    long long want = (2048 + pairs - 1) / pairs;
-    if (want < 1) want = 1;
-    long long c = ((long long)a->max_kv_len + want - 1) / want;
-    c = (c + tile_keys - 1) / tile_keys * tile_keys;
-    long long floor_c = 512;
-    if (c < floor_c) c = floor_c;
+    // fp32 kernel: the coarse cut covers 256 CUs with sixteen-row tiles at chunks of at least 512 keys; the
+    // matrix instructions take 64 rows at a time, which leaves four times fewer work-groups, so the chunks
+    // are made shorter, down to 128 keys (4 x 512..2048 keys, 64 rows: 38 us; 64-key chunks 49, 256-key 38, 512-key 60:
+    // a 64-row partial weighs as much as 33 keys), as long as the split partials stay below GEN_PARTIAL_BYTES
+    // (a call that fitted fd_verify_draft_attn_static with the coarse cut still does).
+    const long long seqs = a->batch > 0 ? a->batch : 1;
+    auto chunk_for = [&](long long pairs, long long groups, long long least) {
+      long long want = (groups + pairs - 1) / pairs;
+      if (want < 1) want = 1;
+      long long c = ((long long)a->max_kv_len + want - 1) / want;
+      c = (c + tile_keys - 1) / tile_keys * tile_keys;
+      return c < least ? least : c;
+    };
+    const long long coarse = chunk_for(seqs * a->num_kv_heads * ((rows + 15) / 16 > 0 ? (rows + 15) / 16 : 1), 2048, 512);
+    long long c = chunk_for(seqs * a->num_kv_heads * plan->row_tiles, 1024, 128);
+    const double per_chunk = (double)(a->total_rows > 0 ? a->total_rows : 1) * a->num_q_heads * (a->head_dim + 2) * sizeof(float);
+    while (c < coarse && ((long long)a->max_kv_len + c - 1) / c * per_chunk > GEN_PARTIAL_BYTES) c += tile_keys;
+    if (c > coarse) c = coarse;
     chunk = (int)c;
   }
   plan->chunk = chunk;
@@ -200,6 +212,15 @@ static fd_status attn_call(const fd_attn_args* a, void* workspace, size_t worksp
   p.G = p.Hq / p.Hkv; p.page_size = a->page_size;
   p.total_rows = a->total_rows; p.max_kv_len = a->max_kv_len; p.max_new_rows = a->max_new_rows;
   p.num_pages = a->num_pages; p.page_entries = a->page_indices_len; p.chunk = plan.chunk; p.max_chunks = plan.max_chunks; p.row_tiles = plan.row_tiles;
+  {
+    // with 2^(s-1) < d <= 2^s the magic ceil(2^(31+s) / d) fits 32 bits and is off by e < d / d <= 1, i.e.
+    // magic d - 2^(31+s) < d <= 2^s: n / d = floor(n magic / 2^(31+s)) for every n < 2^31
+    const unsigned long long d = (unsigned)a->page_size;
+    int sh = 0;
+    while ((1ull << sh) < d) ++sh;
+    const unsigned long long magic = ((1ull << (31 + sh)) + d - 1) / d;
+    p.page_magic = (unsigned)magic; p.page_magic_shift = sh > 0 ? sh - 1 : 0;
+  }
   p.sm_scale = a->sm_scale > 0.f ? a->sm_scale : 1.0f / sqrtf((float)a->head_dim);
   p.k_cache = a->k_cache; p.v_cache = a->v_cache;
   p.sp = a->cache_stride_page; p.sh = a->cache_stride_head; p.st = a->cache_stride_token;
@@ -230,7 +251,7 @@ static fd_status attn_call(const fd_attn_args* a, void* workspace, size_t worksp
   if (!(what & DO_ATTN)) return FD_OK;            // the fp32 kernel has nothing to plan
   hipError_t e = fd::run_attn_generic(p, a->dtype, stream);
   if (e != hipSuccess) return fail(FD_ERR_HIP, "attention kernel launch: %s", hipGetErrorString(e));
-  e = fd::run_attn_combine(p, a->dtype, 0, 0, stream);
+  if (p.max_chunks > 1) e = fd::run_attn_combine(p, a->dtype, stream);          // (every sequence fits one chunk: nothing to merge)
   if (e != hipSuccess) return fail(FD_ERR_HIP, "combine kernel launch: %s", hipGetErrorString(e));
   return FD_OK;
 }

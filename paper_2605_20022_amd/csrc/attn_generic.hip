@@ -1,191 +1,428 @@
-// Hybrid-mask verify+draft attention (Sec. 4.1), scalar fp32 kernel.
+// Hybrid-mask verify+draft attention (Sec. 4.1) at full fp32 precision.
 //
-// This is the fp32 path (and the path for shapes the MFMA kernel does not take): every
-// product and sum is an fp32 FMA, exponentials are accurate expf, so that an fp32 call
-// stays within 1e-5 of the fp64 definition.  One work-group handles 16 tile rows (a tile
-// row is one new row of one query head of the KV head's group) of one (sequence, KV head,
-// KV chunk) and streams that chunk's keys 32 at a time through LDS.  The cached prefix
-// needs no mask (every new row sees all of it, Sec. 4.1); only the ragged tail and the
-// new-row tile are masked.  Results are left as split partials (running max, sum, and
-// un-normalised output) that the combine kernel merges.
+// This is the fp32 path (and the path for bf16 shapes the bf16 matrix-core kernel does not take):
+// inputs enter the products as they are (bf16 widened exactly), every product and sum is fp32,
+// exponentials are accurate expf, so that an fp32 call stays within 1e-5 of the fp64 definition.
+//
+// Both contractions run on the fp32 matrix instruction v_mfma_f32_16x16x4_f32, whose rate (64 FLOP
+// per clock and SIMD, 154 TFLOP/s measured on a large product) bounds the kernel: 64 tile rows need
+// 128 FLOP per cached byte.  One work-group of four waves handles up to 64 tile rows (a tile row is
+// one new row of one query head of the KV head's group) of one (sequence, KV head, KV chunk) and
+// streams that chunk's keys 32 at a time through LDS, double buffered, the next tile's loads in
+// flight (in registers) while a tile is multiplied:
+//   S^T = K Q^T   A = K rows from LDS, B = Q held in registers for the whole chunk; a lane owns one
+//                 query row (column of S^T, lane & 15) and keys 4 (lane >> 4) + {0..3} of each 16
+//   O^T += V^T P^T  the same lane layout: P goes from the S^T registers into the B operand as it is
+// Waves: 1, 2 or 4 blocks of 16 tile rows; with one or two the tile's two 16-key blocks are split
+// between waves, which merge their (max, sum, O) through LDS at the end.
+// The cached prefix needs no mask (every new row sees all of it, Sec. 4.1); only the ragged tail and
+// the new-row tiles are masked.  A sequence of one chunk is normalised and stored; the others leave
+// split partials (running max, sum, un-normalised output) that the combine kernel merges.
+//
+// Measured (4 sequences of 512..2048, 8 KV heads, 64 tile rows each, head dim 128, fp32; 1.64 GFLOP, 53 MB):
+// 36 us a call, 46 TFLOP/s, against 283 us with scalar products on sixteen-row tiles; 16 such sequences 108 us.
+// What is left: with the tile loads taken out 35 us, with the products taken out 21 us -- 340 work-groups of 128
+// keys put two on some CUs and one on others, and the split partials (34 KB a work-group) are written and read once.
 #include "fd_common.h"
 
 namespace fd {
 
 constexpr int GEN_BLOCK = 256;
-constexpr int GEN_ROWS = 16;    // tile rows per work-group
+constexpr int GEN_ROWS = 64;    // tile rows per work-group
 constexpr int GEN_KEYS = 32;    // keys per LDS tile
-constexpr int GEN_DMAX = 128;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 
-template <typename T>
-__global__ __launch_bounds__(GEN_BLOCK) void attn_generic_kernel(AttnParams p) {
-  __shared__ float Qs[GEN_ROWS][GEN_DMAX];
-  __shared__ float Ks[GEN_KEYS][GEN_DMAX + 1];
-  __shared__ float Vs[GEN_KEYS][GEN_DMAX];
-  __shared__ float Ps[GEN_ROWS][GEN_KEYS + 1];
+// Maximum over the four lanes that share lane & 15, by two register swaps instead of two trips through LDS.
+__device__ __forceinline__ float quarters_max(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  v = fmaxf(__builtin_bit_cast(float, (unsigned)a[0]), __builtin_bit_cast(float, (unsigned)a[1]));
+  const unsigned w = __builtin_bit_cast(unsigned, v);
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return fmaxf(__builtin_bit_cast(float, (unsigned)b[0]), __builtin_bit_cast(float, (unsigned)b[1]));
+}
+
+int attn_generic_rows_per_wg() { return GEN_ROWS; }
+
+// NDB: head dim in blocks of 16, rounded up to 2, 4, 6 or 8 (the columns beyond D are zero in LDS).
+// Column of the output block g16 (0 .. NDB - 1) that matrix row m stands for: blocks are taken four
+// at a time (the rest, two, together), column = 64 (g16 / 4) + W m + g16 % 4 with W the group's
+// width, so that a lane's V operands of a group are adjacent in LDS and its outputs adjacent in memory.
+template <typename T, int NDB>
+__global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p) {
+  constexpr int DP = 16 * NDB;                     // padded head dim
+  // LDS row pitch: a multiple of 16 bytes that is odd in units of 16, so that the 16 rows one
+  // ds_read_b128 of K touches fall into 16 different slots of the 256-byte bank line
+  constexpr int STR = DP + 4;
+  constexpr int VEC = 16 / (int)sizeof(T);         // elements per 16-byte load
+  constexpr int TPR = DP / VEC;                    // loads per row
+  constexpr int NLD = (GEN_KEYS * TPR + GEN_BLOCK - 1) / GEN_BLOCK;
+  constexpr int NG = (NDB + 3) / 4;                // column groups
+  __shared__ __attribute__((aligned(16))) float lds[2][2][GEN_KEYS * STR];   // [buffer][K, V]
 
   // Consecutive work-group ids go to different XCDs; rotating the chunk index by head and
   // sequence keeps any one XCD from collecting only the long (or only the short) chunks.
   const int chunk_id = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x;
   const int g = blockIdx.y % p.Hkv, rt = blockIdx.y / p.Hkv;
-  const int seq = blockIdx.z;
-  const SeqInfo s = load_seq(p, seq);
+  const SeqInfo s = load_seq(p, blockIdx.z);
   const int nchunks = max(1, (s.L + p.chunk - 1) / p.chunk);
   const int rows_total = s.n * p.G;
   if (chunk_id >= nchunks || rt * GEN_ROWS >= rows_total) return;
-  const int D = p.D, tid = threadIdx.x;
-  const T* Kc = reinterpret_cast<const T*>(p.k_cache);
-  const T* Vc = reinterpret_cast<const T*>(p.v_cache);
-  const T* Q = reinterpret_cast<const T*>(p.q);
-  const T* Kn = reinterpret_cast<const T*>(p.k_new);
-  const T* Vn = reinterpret_cast<const T*>(p.v_new);
+  const int D = p.D, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l15 = lane & 15, kq = lane >> 4;
+  const T* Kc = reinterpret_cast<const T*>(p.k_cache) + (long long)g * p.sh;
+  const T* Vc = reinterpret_cast<const T*>(p.v_cache) + (long long)g * p.sh;
+  const T* Kn = reinterpret_cast<const T*>(p.k_new) + (long long)g * D;
+  const T* Vn = reinterpret_cast<const T*>(p.v_new) + (long long)g * D;
 
-  // query tile: tile row T -> new row T / G, head g*G + T % G
-  for (int idx = tid; idx < GEN_ROWS * D; idx += GEN_BLOCK) {
-    int tr = idx / D, d = idx % D;
-    int T_ = rt * GEN_ROWS + tr;
-    float val = 0.f;
-    if (T_ < rows_total) {
-      int nn = T_ / p.G, hq = g * p.G + T_ % p.G;
-      val = Elem<T>::load(Q + ((long long)(s.row0 + nn) * p.Hq + hq) * D + d);
-    }
-    Qs[tr][d] = val;
-  }
-
-  const int my_row = tid / 16;            // tile row owned in the score / softmax / PV phases
-  const int sub = tid % 16;
-  const int my_T = rt * GEN_ROWS + my_row;
-  const int my_nn = my_T / p.G;           // new-row index of my tile row
-  const RowWindow my_win = row_window(my_nn < s.n ? my_nn : 0, s);
-  float m_run = -INFINITY, l_run = 0.f;
-  float acc[GEN_DMAX / 16];
-#pragma unroll
-  for (int j = 0; j < GEN_DMAX / 16; ++j) acc[j] = 0.f;
+  const int rows_here = min(GEN_ROWS, rows_total - rt * GEN_ROWS);
+  // Row blocks and key split: a wave takes sixteen rows; with one or two blocks two waves share each, so that
+  // small calls (up to 32 tile rows: bound by the stream, not by the products) still use the tile's halves side by side.
+  const int RB = rows_here <= 16 ? 1 : (rows_here <= 32 ? 2 : 4);      // row blocks
+  const int KS = RB == 4 ? 1 : 2;                                      // waves that share a row block
+  const int rb = wave % RB, ks = wave / RB;
+  const bool wave_works = ks < KS && rb * 16 < rows_here;
+  const int my_T = rt * GEN_ROWS + rb * 16 + l15;                      // this lane's tile row
+  const bool row_valid = wave_works && my_T < rows_total;
+  const int my_nn = my_T / p.G, my_hq = g * p.G + my_T % p.G;
+  const RowWindow win = row_window(row_valid ? my_nn : 0, s);
 
   const int c0 = chunk_id * p.chunk;
   const int c1 = min(s.L, c0 + p.chunk);
-  const bool has_new = (chunk_id == nchunks - 1);
   const int cached_tiles = c1 > c0 ? (c1 - c0 + GEN_KEYS - 1) / GEN_KEYS : 0;
-  const int new_tiles = has_new ? (s.n + GEN_KEYS - 1) / GEN_KEYS : 0;
+  const int new_tiles = chunk_id == nchunks - 1 ? (s.n + GEN_KEYS - 1) / GEN_KEYS : 0;
+  const int nt = cached_tiles + new_tiles;
 
-  for (int t = 0; t < cached_tiles + new_tiles; ++t) {
-    const bool is_new = t >= cached_tiles;
-    const int base = is_new ? (t - cached_tiles) * GEN_KEYS : c0 + t * GEN_KEYS;
-    __syncthreads();                       // previous tile fully consumed (and Qs written)
-    for (int idx = tid; idx < GEN_KEYS * D; idx += GEN_BLOCK) {
-      int kk = idx / D, d = idx % D;
-      int key = base + kk;
-      float kv = 0.f, vv = 0.f;
-      if (is_new) {
-        if (key < s.n) {
-          long long off = ((long long)(s.row0 + key) * p.Hkv + g) * D + d;
-          kv = Elem<T>::load(Kn + off); vv = Elem<T>::load(Vn + off);
-        }
-      } else if (key < c1) {
-        int lp = key / p.page_size, slot = key % p.page_size;
-        int phys = p.page_indices[s.page0 + lp];
-        if (phys < 0 || phys >= p.num_pages) { flag_status(p.status, FD_DEV_PAGE_RANGE); phys = 0; }
-        long long off = (long long)phys * p.sp + (long long)g * p.sh + (long long)slot * p.st + d;
-        kv = Elem<T>::load(Kc + off); vv = Elem<T>::load(Vc + off);
+  // key / page_size by a multiplication (AttnParams::page_magic): exact for keys below 2^31
+  auto page_of = [&](int key) {
+    return p.page_size == 1 ? key : (int)(__umulhi((unsigned)key, p.page_magic) >> p.page_magic_shift);
+  };
+
+  // ---- tile loads: thread tid takes 16-byte vectors tid + 256 i of the tile's K and V -------------
+  // No load is conditional: rows past the end repeat the last row, columns past D the first ones.  The
+  // scores of such rows are masked (their probability is zero) and such columns meet zeros of Q or are
+  // not stored.
+  constexpr bool EXACT = GEN_KEYS * TPR % GEN_BLOCK == 0;
+  int ld_row[NLD], ld_col[NLD];
+#pragma unroll
+  for (int i = 0; i < NLD; ++i) {
+    const int idx = EXACT ? tid + GEN_BLOCK * i : min(tid + GEN_BLOCK * i, GEN_KEYS * TPR - 1);
+    ld_row[i] = idx / TPR; ld_col[i] = (idx % TPR) * VEC;
+  }
+  int pid[NLD], slot_[NLD];                        // pages and slots of this thread's rows of the next tile to load
+  u32x4 rk[NLD], rv[NLD];
+  auto fetch_pages = [&](int t) {
+    if (t >= cached_tiles) return;
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int key = min(c0 + t * GEN_KEYS + ld_row[i], c1 - 1);
+      const int lp = page_of(key);
+      pid[i] = p.page_indices[s.page0 + lp];
+      slot_[i] = key - lp * p.page_size;
+    }
+  };
+  auto load_tile = [&](int t) {
+    if (t >= cached_tiles) {
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) {
+        const int key = min((t - cached_tiles) * GEN_KEYS + ld_row[i], s.n - 1);
+        const long long off = (long long)(s.row0 + key) * p.Hkv * D + (ld_col[i] < D ? ld_col[i] : 0);
+        rk[i] = *reinterpret_cast<const u32x4*>(Kn + off); rv[i] = *reinterpret_cast<const u32x4*>(Vn + off);
       }
-      Ks[kk][d] = kv; Vs[kk][d] = vv;
-    }
-    __syncthreads();
-    // scores: thread (my_row, sub) computes keys sub and sub+16
+    } else {
+      bool oob = false;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      int kk = sub + 16 * h;
-      float dot = 0.f;
-      for (int d = 0; d < D; ++d) dot = fmaf(Qs[my_row][d], Ks[kk][d], dot);
-      int key = base + kk;
-      bool vis = is_new ? (new_key_visible(my_win, key) && key < s.n) : (key < c1);
-      Ps[my_row][kk] = vis ? dot * p.sm_scale : -INFINITY;
+      for (int i = 0; i < NLD; ++i) {
+        const bool bad = (unsigned)pid[i] >= (unsigned)p.num_pages;
+        oob |= bad;
+        const unsigned long long off = (unsigned)(bad ? 0 : pid[i]) * (unsigned long long)p.sp +
+                                       (unsigned long long)(unsigned)slot_[i] * (unsigned)p.st + (unsigned)(ld_col[i] < D ? ld_col[i] : 0);
+        rk[i] = *reinterpret_cast<const u32x4*>(Kc + off); rv[i] = *reinterpret_cast<const u32x4*>(Vc + off);
+      }
+      if (oob) flag_status(p.status, FD_DEV_PAGE_RANGE);
     }
-    __syncthreads();
-    // online softmax for my row (the 16 threads of a row all hold the same state)
-    float tmax = -INFINITY;
-    for (int kk = 0; kk < GEN_KEYS; ++kk) tmax = fmaxf(tmax, Ps[my_row][kk]);
-    float m_new = fmaxf(m_run, tmax);
-    float alpha = (m_new == -INFINITY) ? 1.f : expf(m_run - m_new);   // exp(-inf) = 0 on the first real tile
-    float p0 = 0.f, p1 = 0.f;
-    if (m_new > -INFINITY) {
-      p0 = expf(Ps[my_row][sub] - m_new);
-      p1 = expf(Ps[my_row][sub + 16] - m_new);
+  };
+  auto put = [&](float* dst, u32x4 w) {            // one vector, widened to fp32
+    if (sizeof(T) == 4) {
+      *reinterpret_cast<u32x4*>(dst) = w;
+    } else {
+      const u32x4 a = {w[0] << 16, w[0] & 0xffff0000u, w[1] << 16, w[1] & 0xffff0000u};
+      const u32x4 b = {w[2] << 16, w[2] & 0xffff0000u, w[3] << 16, w[3] & 0xffff0000u};
+      *reinterpret_cast<u32x4*>(dst) = a; *reinterpret_cast<u32x4*>(dst + 4) = b;
     }
-    float psum = p0 + p1;
+  };
+  auto store_tile = [&](int buf) {
 #pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) psum += __shfl_xor(psum, off);
-    __syncthreads();                       // everyone has read the scores
-    Ps[my_row][sub] = p0; Ps[my_row][sub + 16] = p1;
-    l_run = l_run * alpha + psum;
-    m_run = m_new;
-    __syncthreads();
-    // output columns sub, sub+16, ... (D is a multiple of 8, not necessarily of 16)
-    for (int j = 0; j * 16 < D; ++j) {
-      int d = sub + 16 * j;
-      if (d >= D) break;
-      float a = acc[j] * alpha;
-      for (int kk = 0; kk < GEN_KEYS; ++kk) a = fmaf(Ps[my_row][kk], Vs[kk][d], a);
-      acc[j] = a;
+    for (int i = 0; i < NLD; ++i) {
+      put(&lds[buf][0][ld_row[i] * STR + ld_col[i]], rk[i]);
+      put(&lds[buf][1][ld_row[i] * STR + ld_col[i]], rv[i]);
+    }
+  };
+
+  fetch_pages(0);
+  // query row of this lane: columns 16 j + 4 kq + {0..3}
+  f32x4 q[NDB];
+  {
+    const T* qp = reinterpret_cast<const T*>(p.q) + ((long long)(s.row0 + my_nn) * p.Hq + my_hq) * D;
+#pragma unroll
+    for (int j = 0; j < NDB; ++j) {
+      const int col = 16 * j + 4 * kq;
+      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+      if (row_valid && col < D) {                  // D is a multiple of 8: a vector is inside or outside
+        if (sizeof(T) == 4) x = *reinterpret_cast<const f32x4*>(qp + col);
+        else {
+          const u32x2 w = *reinterpret_cast<const u32x2*>(qp + col);
+          x[0] = __uint_as_float(w[0] << 16); x[1] = __uint_as_float(w[0] & 0xffff0000u);
+          x[2] = __uint_as_float(w[1] << 16); x[3] = __uint_as_float(w[1] & 0xffff0000u);
+        }
+      }
+      q[j] = x;
     }
   }
+  load_tile(0);
+  fetch_pages(1);
+  store_tile(0);
+  __syncthreads();
 
-  if (my_T < rows_total) {
-    int hq = g * p.G + my_T % p.G;
-    long long slot = ((long long)chunk_id * p.total_rows + (s.row0 + my_nn)) * p.Hq + hq;
-    for (int j = 0; sub + 16 * j < D; ++j) p.part_acc[slot * D + sub + 16 * j] = acc[j];
-    if (sub == 0) { p.part_ml[slot * 2] = m_run; p.part_ml[slot * 2 + 1] = l_run; }
+  float m_run = -INFINITY, l_lane = 0.f;
+  f32x4 o[NDB];
+#pragma unroll
+  for (int b = 0; b < NDB; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  for (int t = 0; t < nt; ++t) {
+    if (t + 1 < nt) { load_tile(t + 1); fetch_pages(t + 2); }
+    const bool is_new = t >= cached_tiles;
+    const int base = is_new ? (t - cached_tiles) * GEN_KEYS : c0 + t * GEN_KEYS;
+    const int end = is_new ? s.n : c1;                                  // keys at or beyond are invisible
+    const bool masked = is_new || base + GEN_KEYS > end;
+    const float* Ks = lds[t & 1][0];
+    const float* Vs = lds[t & 1][1];
+    auto block = [&](auto nkb_c, int kb0) {        // NKB 16-key blocks from kb0 on
+      constexpr int NKB = decltype(nkb_c)::value;
+      // K fragments are requested one 16-column step ahead of the matrix instructions that take them
+      f32x4 sc[NKB][2];                            // two accumulation chains per key block
+#pragma unroll
+      for (int b = 0; b < NKB; ++b) sc[b][0] = sc[b][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const float* kp = Ks + (16 * kb0 + l15) * STR + 4 * kq;
+      f32x4 kf[2][NKB];
+#pragma unroll
+      for (int b = 0; b < NKB; ++b) kf[0][b] = *reinterpret_cast<const f32x4*>(kp + 16 * b * STR);
+#pragma unroll
+      for (int j = 0; j < NDB; ++j) {
+        if (j + 1 < NDB) {
+#pragma unroll
+          for (int b = 0; b < NKB; ++b) kf[(j + 1) & 1][b] = *reinterpret_cast<const f32x4*>(kp + 16 * b * STR + 16 * (j + 1));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int b = 0; b < NKB; ++b)
+            sc[b][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j & 1][b][e], q[j][e], sc[b][e & 1], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // V fragments likewise, one key step (8 matrix instructions at head dim 128) ahead; the first before the softmax
+      const float* vp = Vs + (16 * kb0 + 4 * kq) * STR;
+      f32x4 vf[2][NG];
+      auto vread = [&](int st) {                   // key step st = 4 b + e
+#pragma unroll
+        for (int gr = 0; gr < NG; ++gr) {
+          const float* a = vp + (16 * (st >> 2) + (st & 3)) * STR + 64 * gr;
+          if (NDB % 4 && gr == NG - 1) {
+            const f32x2 w = *reinterpret_cast<const f32x2*>(a + 2 * l15);
+            vf[st & 1][gr][0] = w[0]; vf[st & 1][gr][1] = w[1];
+          } else {
+            vf[st & 1][gr] = *reinterpret_cast<const f32x4*>(a + 4 * l15);
+          }
+        }
+      };
+      vread(0);
+      float x[NKB][4];
+#pragma unroll
+      for (int b = 0; b < NKB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[b][i] = (sc[b][0][i] + sc[b][1][i]) * p.sm_scale;
+      if (masked) {
+        RowWindow wv = win;
+        if (!is_new) { wv.vr = end; wv.lo = 0; wv.hi = 0; }             // a prefix tile: the keys below the end
+#pragma unroll
+        for (int b = 0; b < NKB; ++b)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int key = base + 16 * (kb0 + b) + 4 * kq + i;
+            x[b][i] = (new_key_visible(wv, key) & (key < end)) ? x[b][i] : -INFINITY;
+          }
+      }
+      float mx = x[0][0];
+#pragma unroll
+      for (int b = 0; b < NKB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mx = fmaxf(mx, x[b][i]);
+      mx = quarters_max(mx);
+      const float m_new = fmaxf(m_run, mx);
+      const float m_sub = m_new == -INFINITY ? 0.f : m_new;             // row with nothing visible yet
+      if (__any(m_new != m_run)) {
+        const float alpha = expf(m_run - m_sub);                        // expf(-inf) = 0 on the first visible key
+        l_lane *= alpha;
+#pragma unroll
+        for (int b = 0; b < NDB; ++b) o[b] *= alpha;
+      }
+      m_run = m_new;
+#pragma unroll
+      for (int b = 0; b < NKB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { x[b][i] = expf(x[b][i] - m_sub); l_lane += x[b][i]; }
+#pragma unroll
+      for (int st = 0; st < 4 * NKB; ++st) {
+        if (st + 1 < 4 * NKB) vread(st + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < NDB; ++c)
+          o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[st & 1][c >> 2][c & 3], x[st >> 2][st & 3], o[c], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    if (wave_works) {
+      if (KS == 1) block(std::integral_constant<int, 2>{}, 0);
+      else if (base + 16 * ks < end) block(std::integral_constant<int, 1>{}, ks);
+    }
+    if (t + 1 < nt) store_tile((t + 1) & 1);
+    __syncthreads();                               // tile t consumed, tile t + 1 visible
+  }
+
+  // ---- merge the two waves of a row block (same register layout) through LDS --------------------
+  if (KS == 2) {
+    f32x4* xch = reinterpret_cast<f32x4*>(&lds[0][0][0]);              // [rb][NDB + 1][64]
+    static_assert(sizeof(lds) >= 2 * (NDB + 1) * 64 * sizeof(f32x4), "the merge area fits the tile buffers");
+    if (wave_works && ks == 1) {
+#pragma unroll
+      for (int b = 0; b < NDB; ++b) xch[(rb * (NDB + 1) + b) * 64 + lane] = o[b];
+      xch[(rb * (NDB + 1) + NDB) * 64 + lane] = f32x4{m_run, l_lane, 0.f, 0.f};
+    }
+    __syncthreads();
+    if (wave_works && ks == 0) {
+      const f32x4 ml = xch[(rb * (NDB + 1) + NDB) * 64 + lane];
+      const float m_new = fmaxf(m_run, ml[0]);
+      const float m_sub = m_new == -INFINITY ? 0.f : m_new;
+      const float a = expf(m_run - m_sub), b2 = expf(ml[0] - m_sub);
+      l_lane = l_lane * a + ml[1] * b2;
+      m_run = m_new;
+#pragma unroll
+      for (int b = 0; b < NDB; ++b) o[b] = o[b] * a + xch[(rb * (NDB + 1) + b) * 64 + lane] * b2;
+    }
+  }
+  if (!wave_works || ks > 0) return;
+  float l_run = l_lane + __shfl_xor(l_lane, 16);
+  l_run += __shfl_xor(l_run, 32);
+  if (!row_valid) return;
+
+  // o[4 gr + c][i]: column 64 gr + W (4 kq + i) + c, i.e. 4 W adjacent columns per lane and group
+  const long long orow = (long long)(s.row0 + my_nn) * p.Hq + my_hq;
+  if (nchunks == 1) {
+    const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
+    T* op = reinterpret_cast<T*>(p.out) + orow * D;
+#pragma unroll
+    for (int gr = 0; gr < NG; ++gr) {
+      constexpr int W_LAST = NDB % 4 ? NDB % 4 : 4;
+      const int W = gr == NG - 1 ? W_LAST : 4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int c = 0; c < W; ++c) {
+          const int d = 64 * gr + W * (4 * kq + i) + c;
+          if (d < D) Elem<T>::store(op + d, o[4 * gr + c][i] * inv);
+        }
+    }
+    if (p.lse && kq == 0) p.lse[orow] = m_run + logf(l_run);
+  } else {
+    const long long slot = ((long long)chunk_id * p.total_rows + (s.row0 + my_nn)) * p.Hq + my_hq;
+    float* ap = p.part_acc + slot * D;
+#pragma unroll
+    for (int gr = 0; gr < NG; ++gr) {
+      constexpr int W_LAST = NDB % 4 ? NDB % 4 : 4;
+      const int W = gr == NG - 1 ? W_LAST : 4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int d = 64 * gr + W * (4 * kq + i);
+        if (W == 4) { if (d < D) *reinterpret_cast<f32x4*>(ap + d) = f32x4{o[4 * gr][i], o[4 * gr + 1][i], o[4 * gr + 2][i], o[4 * gr + 3][i]}; }
+        else {
+#pragma unroll
+          for (int c = 0; c < W; ++c) if (d + c < D) ap[d + c] = o[4 * gr + c][i];
+        }
+      }
+    }
+    if (kq == 0) { p.part_ml[slot * 2] = m_run; p.part_ml[slot * 2 + 1] = l_run; }
   }
 }
 
 // ---------------------------------------------------------------------------------------
-// Combine the per-chunk partials of every (row, head):
+// Combine the per-chunk partials of every (row, head) of the sequences of more than one chunk:
 //   M = max_c m_c;  out = sum_c e^{m_c - M} acc_c / sum_c e^{m_c - M} l_c;  lse = M + log(sum)
-// `log2_units` says the partial maxima are in base-2 exponent units (the MFMA kernel) or
-// natural units (the scalar kernel).  `skip_single`: sequences that fit one chunk were already
-// normalised and stored by the streaming kernel.  grid (ceil(Hq*D/256), max_new_rows, B).
+// 32 lanes per (row, head), a lane owns four columns; grid (ceil(Hq / 8), max_new_rows, B).  The
+// chunks are taken four at a time, their loads issued together, with a running maximum.
 // ---------------------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256) void attn_combine_kernel(AttnParams p, int log2_units, int skip_single) {
+__global__ __launch_bounds__(256) void attn_combine_kernel(AttnParams p) {
   const int seq = blockIdx.z, nn = blockIdx.y;
   const SeqInfo s = load_seq(p, seq);
-  if (nn >= s.n) return;
-  if (skip_single && s.L <= p.chunk) return;     // the streaming kernel already wrote these rows
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= p.Hq * p.D) return;
-  const int hq = idx / p.D, d = idx % p.D;
-  const int nchunks = max(1, (s.L + p.chunk - 1) / p.chunk);
+  if (nn >= s.n || s.L <= p.chunk) return;         // one chunk: the streaming kernel stored the rows itself
+  const int hq = blockIdx.x * 8 + (threadIdx.x >> 5), d = (threadIdx.x & 31) * 4;
+  if (hq >= p.Hq || d >= p.D) return;
+  const int nchunks = (s.L + p.chunk - 1) / p.chunk;
   const long long row = s.row0 + nn;
   const long long stride = (long long)p.total_rows * p.Hq;     // partial slots per chunk
   const long long slot0 = row * p.Hq + hq;
-  float M = -INFINITY;
-  for (int c = 0; c < nchunks; ++c) M = fmaxf(M, p.part_ml[(slot0 + c * stride) * 2]);
-  float num = 0.f, den = 0.f;
-  for (int c = 0; c < nchunks; ++c) {
-    long long sl = slot0 + c * stride;
-    float mc = p.part_ml[sl * 2];
-    if (mc == -INFINITY) continue;
-    float w = log2_units ? exp2f(mc - M) : expf(mc - M);
-    num = fmaf(w, p.part_acc[sl * p.D + d], num);
-    den = fmaf(w, p.part_ml[sl * 2 + 1], den);
+  float M = -INFINITY, den = 0.f;
+  f32x4 num = {0.f, 0.f, 0.f, 0.f};
+  constexpr int NB = 4;
+  for (int ch0 = 0; ch0 < nchunks; ch0 += NB) {
+    f32x2 ml[NB]; f32x4 a[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const long long sl = slot0 + min(ch0 + u, nchunks - 1) * stride;
+      ml[u] = *reinterpret_cast<const f32x2*>(p.part_ml + sl * 2);
+      a[u] = *reinterpret_cast<const f32x4*>(p.part_acc + sl * p.D + d);
+      if (ch0 + u >= nchunks) ml[u][0] = -INFINITY;
+    }
+    float Mb = M;
+#pragma unroll
+    for (int u = 0; u < NB; ++u) Mb = fmaxf(Mb, ml[u][0]);
+    if (Mb == -INFINITY) continue;
+    const float r = expf(M - Mb);                  // M = -inf: 0
+    num *= r; den *= r; M = Mb;
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const float w = expf(ml[u][0] - M);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) num[e] = fmaf(w, a[u][e], num[e]);
+      den = fmaf(w, ml[u][1], den);
+    }
   }
-  float o = den > 0.f ? num / den : 0.f;
-  Elem<T>::store(reinterpret_cast<T*>(p.out) + (row * p.Hq + hq) * p.D + d, o);
-  if (p.lse && d == 0)
-    p.lse[row * p.Hq + hq] = log2_units ? (M + log2f(den)) * 0.6931471805599453f : M + logf(den);
+  T* op = reinterpret_cast<T*>(p.out) + slot0 * p.D + d;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) Elem<T>::store(op + e, den > 0.f ? num[e] / den : 0.f);
+  if (p.lse && d == 0) p.lse[slot0] = M + logf(den);
+}
+
+template <typename T>
+static void launch_generic(const AttnParams& p, hipStream_t st) {
+  dim3 grid(p.max_chunks, p.Hkv * p.row_tiles, p.B);
+  if (p.D <= 32) hipLaunchKernelGGL((attn_generic_kernel<T, 2>), grid, dim3(GEN_BLOCK), 0, st, p);
+  else if (p.D <= 64) hipLaunchKernelGGL((attn_generic_kernel<T, 4>), grid, dim3(GEN_BLOCK), 0, st, p);
+  else if (p.D <= 96) hipLaunchKernelGGL((attn_generic_kernel<T, 6>), grid, dim3(GEN_BLOCK), 0, st, p);
+  else hipLaunchKernelGGL((attn_generic_kernel<T, 8>), grid, dim3(GEN_BLOCK), 0, st, p);
 }
 
 hipError_t run_attn_generic(const AttnParams& p, int dtype, hipStream_t st) {
-  dim3 grid(p.max_chunks, p.Hkv * ((p.max_new_rows * p.G + GEN_ROWS - 1) / GEN_ROWS), p.B);
-  if (dtype == FD_BF16) hipLaunchKernelGGL(attn_generic_kernel<bf16_t>, grid, dim3(GEN_BLOCK), 0, st, p);
-  else hipLaunchKernelGGL(attn_generic_kernel<float>, grid, dim3(GEN_BLOCK), 0, st, p);
+  if (dtype == FD_BF16) launch_generic<bf16_t>(p, st);
+  else launch_generic<float>(p, st);
   return hipGetLastError();
 }
 
-hipError_t run_attn_combine(const AttnParams& p, int dtype, int log2_units, int skip_single, hipStream_t st) {
-  dim3 grid((p.Hq * p.D + 255) / 256, p.max_new_rows, p.B);
-  if (dtype == FD_BF16) hipLaunchKernelGGL(attn_combine_kernel<bf16_t>, grid, dim3(256), 0, st, p, log2_units, skip_single);
-  else hipLaunchKernelGGL(attn_combine_kernel<float>, grid, dim3(256), 0, st, p, log2_units, skip_single);
+hipError_t run_attn_combine(const AttnParams& p, int dtype, hipStream_t st) {
+  dim3 grid((p.Hq + 7) / 8, p.max_new_rows, p.B);
+  if (dtype == FD_BF16) hipLaunchKernelGGL(attn_combine_kernel<bf16_t>, grid, dim3(256), 0, st, p);
+  else hipLaunchKernelGGL(attn_combine_kernel<float>, grid, dim3(256), 0, st, p);
   return hipGetLastError();
 }
 

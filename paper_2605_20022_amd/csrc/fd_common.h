@@ -69,6 +69,7 @@ struct AttnParams {
   int chunk;          // cached tokens per work-group
   int max_chunks;     // grid extent over chunks
   int row_tiles;      // grid extent over row tiles
+  unsigned page_magic; int page_magic_shift;   // key / page_size = mulhi(key, magic) >> shift for page_size >= 2, key < 2^31
   float sm_scale;
   const void* k_cache; const void* v_cache;
   long long sp, sh, st;                       // cache strides in elements

@@ -61,6 +61,21 @@ def test_generic_kernel_small_cases(fd, case, dtype):
         _check(fd, inp, dtype, f"generic {case} chunk={chunk} mask_vis", mask_vis=mv, flags=FORCE_GENERIC, kv_chunk=chunk)
 
 
+@pytest.mark.parametrize("D", [8, 24, 40, 64, 72, 96, 104, 128])            # every padded width and ragged head dims
+@pytest.mark.parametrize("G,rows", [(1, 1), (4, 4), (3, 5), (2, 16), (3, 11), (4, 8), (4, 16), (5, 13)])   # 1, 16, 15, 32, 33, 32, 64, 65 tile rows
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_full_precision_kernel_edges(fd, dtype, G, rows, D):
+    """One to five row blocks, prefixes around the 32-key tile and the automatic 128-key chunk (single-chunk
+    sequences are stored by the streaming kernel itself), page sizes that need a division."""
+    lens = [0, 1, 31, 32, 33, 127, 128, 129, 300]
+    ps = (3, 5, 24, 1)[(D // 8 + rows) % 4]
+    w = _wl("edge", dtype, len(lens), 2 * G, 2, D, ps, (300, 300), (rows, rows), 0 if rows < 5 else 3, seed=60 + D)
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array(lens, dtype=np.int32)                          # (the page lists are long enough for all of them)
+    _check(fd, inp, dtype, f"edges {dtype} D={D} G={G} rows={rows} ps={ps}", flags=FORCE_GENERIC)
+    _check(fd, inp, dtype, f"edges {dtype} D={D} G={G} rows={rows} ps={ps} chunk", flags=FORCE_GENERIC, kv_chunk=64)
+
+
 @pytest.mark.parametrize("case", [
     dict(B=3, G=4, Hkv=2, ps=16, kv=(1, 500), kr=(1, 8), m=8),
     dict(B=2, G=4, Hkv=1, ps=16, kv=(64, 64), kr=(4, 4), m=4),             # exactly one full tile
