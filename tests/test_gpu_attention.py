@@ -141,6 +141,27 @@ def test_several_mask_blocks(fd, case):
     assert not np.array_equal(base[blk], moved[blk])
 
 
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("B,Hkv,n,kv,chunk", [
+    (1, 8, 4, (2500, 2500), 64),       # 8 items of up to 40 pieces: four lane groups per row, two batches each
+    (1, 1, 13, (60, 60), 64),          # two pieces
+    (2, 8, 40, (900, 1500), 64),       # 32 items of 128 rows (two row blocks), the second one ragged
+    (3, 24, 5, (200, 900), 64),        # 72 items: one lane group per row, up to 15 pieces
+    (40, 16, 5, (10, 200), 64),        # 640 items: entries by share
+])
+def test_combine_layouts(fd, D, B, Hkv, n, kv, chunk):
+    """Every way the combine kernel is laid out over the split items, short sequences without rows among them."""
+    w = _wl("comb", "bf16", B, 4 * Hkv, Hkv, D, 16, kv, (n, n), 0, seed=70 + B)
+    inp = W.make_attention_inputs(w)
+    _check(fd, inp, "bf16", f"combine B={B} Hkv={Hkv} n={n}", kv_chunk=chunk)
+    if B > 1:                                                             # the last sequence without new rows
+        r0 = int(inp["row_indptr"][-2])
+        inp = dict(inp, **{k: inp[k][:r0] for k in ("q", "k_new", "v_new")})
+        inp["row_indptr"] = inp["row_indptr"].copy(); inp["row_indptr"][-1] = r0
+        inp["verify_len"] = inp["verify_len"].copy(); inp["verify_len"][-1] = 0
+        _check(fd, inp, "bf16", f"combine B={B} Hkv={Hkv} n={n}, one sequence without rows", kv_chunk=chunk)
+
+
 @pytest.mark.parametrize("seed", range(12))
 def test_random_workloads(fd, seed):
     """Seeded random shapes through the MFMA path: batch, head grouping, page size, ragged prefixes
