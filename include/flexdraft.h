@@ -156,7 +156,8 @@ FD_API fd_status fd_verify_draft_attn(const fd_attn_args *args, void *hip_stream
  * Planning for fd_verify_draft_attn, separated out because it depends on the lengths only and the
  * same lengths meet every layer of the model in one decoding step (Sec. 4.1: one forward pass
  * verifies and drafts; Sec. 4.3).  The bf16 kernel for head_dim 128 or 64 cuts the batch's key tiles into
- * equal shares for its persistent work-groups; the plan is, per work-group, where its share
+ * equal shares for its persistent work-groups (or, with few items, each item into equal pieces); the plan is,
+ * per work-group, where its share
  * starts (sequence, offset, the page ids of its first two tiles).  Without a plan every work-group
  * of fd_verify_draft_attn finds its share itself, by a scan over the batch, before it can request
  * its first tile; with args->flags & FD_ATTN_PLANNED it starts from the plan this call left in

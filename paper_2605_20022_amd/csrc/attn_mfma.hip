@@ -92,6 +92,7 @@ constexpr int MF_BLOCKS = MF_TK / 32;     // 32-key MFMA blocks per tile
 constexpr int MF_GROUPS = MF_TK / 16;     // 16-key load groups per tile
 constexpr int MF_XCD_TILT = 40;           // per mille of a share that every share of an odd XCD hands to the even XCD before it
 constexpr int MF_TILT_MIN_SHARE = 64;     // ... in launches whose shares are at least this many units long
+constexpr int MF_PIECE_SLACK = 2;         // tiles by which a piece (find_piece) may be longer than a share of the line
 constexpr float MF_LAZY = 6.f;            // the softmax reference follows the row maximum in steps of at least 2^6
 // What starting an item costs a work-group, in tile times: measured ≈ 6.9 µs (request the next piece's
 // tiles ≈ 2.4, merge and store ≈ 3.4, wait for the first tile ≈ 1.1) against 2.1 µs per tile in the
@@ -112,6 +113,8 @@ struct MfmaSched {
   int reuse;          // != 0: some sequence has several row blocks, i.e. its K/V tiles are read by several items
   int min_share;      // automatic shares are never smaller than this many tiles
   int fixed_share;    // > 0: tiles per work-group asked for by the caller
+  int by_piece;       // 1: items may be cut one by one (find_piece), at most 64 sequences and num_wgs items; 2: they always are
+  int min_piece;      // ... into pieces of at least this many tiles
   unsigned short* part_acc;   // [2 * num_wgs][ROWS_WG][D] fp16: the un-normalised output row divided by its largest magnitude
   float* part_ml;             // [2 * num_wgs][ROWS_WG][4]: running maximum (base 2), row sum, that largest magnitude, unused
   int rt_max;         // row blocks of the largest sequence
@@ -119,8 +122,9 @@ struct MfmaSched {
   // Combine entries [num_wgs + 1].
   //   by share  entry w: the split item that ends in the work-group of share w: (first packed row, head | row block << 16,
   //             tile rows, first slot); first < 0: none.  Entry num_wgs: (shares in use, -, -, -)
-  //   by item   entry (sequence * Hkv + head) * rt_max + row block: (first slot, share it ended in, -, -); first < 0: the
-  //             item was not split.  Written by the work-group that holds the item's last tile.
+  //   by item   entry (sequence * Hkv + head) * rt_max + row block: (first slot, share it ended in, shares from one of its
+  //             pieces to the next, -); first < 0: the item was not split.  Written by the work-group that holds the
+  //             item's last tile.
   int4* entries;
   struct PlanEntry* plan;     // [num_wgs]: written by the planning kernel, read by a planned streaming kernel
 };
@@ -135,7 +139,9 @@ struct PlanEntry {
   int W_eff;                  // shares in use (valid in every entry, also those without a share)
   int share;                  // which share this work-group takes
   int pg0[MF_GROUPS], pg1[MF_GROUPS];          // page ids of the first two tiles of the share's first piece
-  int pad1[8];
+  int pieces;                 // > 0: the share is one piece of an item cut into this many (find_piece); 0: units [g0, g1)
+  int head, rt, tile0, nt;    // ... that piece: tiles [tile0, tile0 + nt)
+  int pad1[3];
 };
 static_assert(sizeof(PlanEntry) == 128, "one plan entry is 128 bytes");
 
@@ -338,6 +344,73 @@ __device__ __forceinline__ bool find_share(const AttnParams& p, const MfmaSched&
   return true;
 }
 
+// Items cut one by one.  With no more items than work-groups, every item is cut into ceil(T / s) pieces of nearly equal
+// tile counts, s the smallest for which all pieces together fit the launch, and a work-group takes exactly one piece:
+// none begins a second item (which costs it about as much as two to four tiles) and none holds start-up units only.
+// Measured against the line (us a call, line -> pieces): 16 sequences of 64..512 keys, 9..16 rows of 4 heads 27.7 -> 16.4;
+// 64 of 50..200, 8 rows 22.7 -> 18.1; 3 of 1000..4000 in full parallel mode (72 rows) 37 -> 30.6; 8 of 2048..8192
+// with 36 rows 75 -> 69.8; 16 of 512..4096 keys: equal.  The line is better where s comes out longer than its shares (400 items
+// for 512 work-groups are whole items here, 4/5 of one there): of more than num_wgs / 2 items, pieces are cut only if
+// s is at most MF_PIECE_SLACK tiles above a share (64-row items of 1000..3000 keys, 320 of them: s is 8 above, 62.7 -> 66.6).
+// Up to num_wgs / 2 items (the host's bound) they always are, at most 2 s0 long, and the streaming kernel is the variant
+// without the line: no walk over items and no second piece, a third of the instructions and no spilled scalars
+// (16 of 512..4096 keys 39.7 -> 37.9, 1 of 2048 14.6 -> 13.2, 4 of 32768 112.7 -> 109.4).
+// Pieces are numbered (sequence, head, piece, row block): the row blocks that read the same tiles are neighbours.
+// Every wave works this out by itself (lane i holds sequence i, then candidate i for s): no LDS, no barrier.
+// Returns false if the call is to be cut along the line; has_piece: this work-group has one.
+struct PieceShare { int w, seq, W_eff, pieces, head, rt, tile0, nt; };
+template <int MAXRB, bool SINGLE>
+__device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched& sc_, int pw, PieceShare& ps, SeqInfo& ws, bool& has_piece) {
+  constexpr int ROWS_WG = 32 * MAXRB;
+  const int lane = threadIdx.x & 63;
+  has_piece = false;
+  SeqInfo s = {}; uint32_t bad = 0; int T = 0, I = 0;
+  if (lane < p.B) {
+    s = load_seq_t<false>(p, lane, &bad);
+    seq_shape(p, s, ROWS_WG, T, I);
+  }
+  const int tiles_all = __builtin_amdgcn_readlane(wave_incl_scan(T * I, lane), 63);
+  const int items_all = __builtin_amdgcn_readlane(wave_incl_scan(I, lane), 63);
+  if (tiles_all == 0) { ps.W_eff = 0; if (bad && threadIdx.x < 64) flag_status(p.status, bad); return true; }
+  // candidate sizes s0 + lane: how many pieces each gives
+  const int s0 = max(sc_.min_piece, (tiles_all + sc_.num_wgs - 1) / sc_.num_wgs);
+  const int step = s0 / 63 + 1;                                    // (up to 2 s0: enough while items <= num_wgs / 2)
+  const int cand = s0 + lane * step;
+  int count = 0;
+  for (int i = 0; i < p.B; ++i) {
+    const int Ti = __builtin_amdgcn_readlane(T, i), Ii = __builtin_amdgcn_readlane(I, i);
+    count += Ii * ((Ti + cand - 1) / cand);
+  }
+  const unsigned long long fits = __ballot(count <= sc_.num_wgs);
+  const int size = s0 + (__ffsll((long long)fits) - 1) * step;
+  const int line = max(sc_.min_share, (tiles_all + mf_start_cost(MAXRB) * items_all + sc_.num_wgs - 1) / sc_.num_wgs);
+  if (fits == 0 || (!SINGLE && size > max(line + MF_PIECE_SLACK, sc_.min_piece))) return false;
+  if (bad && threadIdx.x < 64) flag_status(p.status, bad);
+  const int S = (T + size - 1) / size, n = I * S;
+  const int hi = wave_incl_scan(n, lane), lo = hi - n;
+  ps.W_eff = __builtin_amdgcn_readlane(hi, 63);
+  const int chunk = (ps.W_eff + sc_.xcds - 1) / sc_.xcds;          // (the same assignment of shares to XCDs as on the line)
+  ps.w = pw / sc_.xcds < chunk ? (pw % sc_.xcds) * chunk + pw / sc_.xcds : ps.W_eff;
+  if (ps.w >= ps.W_eff) return true;
+  const int at = __ffsll((long long)__ballot(lo <= ps.w && ps.w < hi)) - 1;
+  if (at < 0) return true;                                         // cannot happen
+  auto from = [&](int v) { return __builtin_amdgcn_readlane(v, at); };
+  ws.L = from(s.L); ws.row0 = from(s.row0); ws.n = from(s.n); ws.k = from(s.k);
+  ws.v = from(s.v); ws.nb = from(s.nb); ws.page0 = from(s.page0); ws.npages = from(s.npages);
+  const int Ts = from(T), Ss = from(S), RT = from(I) / p.Hkv;
+  const int local = ps.w - from(lo);
+  ps.seq = at; ps.pieces = Ss;
+  ps.head = local / (RT * Ss);
+  const int r = local - ps.head * (RT * Ss), j = r / RT;
+  ps.rt = r - j * RT;
+  // piece j: tiles [floor(j T / S), floor((j + 1) T / S)), in 32 bits: T = a S + b
+  const int a = Ts / Ss, b = Ts - a * Ss;
+  ps.tile0 = j * a + (j * b) / Ss;
+  ps.nt = (j + 1) * a + ((j + 1) * b) / Ss - ps.tile0;
+  has_piece = true;
+  return true;
+}
+
 // Planning kernel: one work-group per persistent work-group of the streaming kernel.  Every one
 // repeats the (cheap) scan over the batch, finds its own share and leaves its plan entry.
 // MAXRB: 32-row blocks a work-group can own (2: up to 64 tile rows, 4: up to 128).
@@ -348,18 +421,28 @@ __global__ __launch_bounds__(MF_BLOCK) void attn_mfma_plan_kernel(AttnParams p, 
   const int tid = threadIdx.x;
   const int pw = blockIdx.x;                      // the entry is read by work-group pw of the streaming kernel
   PlanEntry* out = sc_.plan + pw;
-  int w, seq, W_eff; unsigned Pt, g0, g1, sh_q, sh_r; SeqInfo ws;
-  if (!find_share<MAXRB>(p, sc_, pw, w, seq, Pt, ws, g0, g1, sh_q, sh_r, W_eff)) {
-    if (tid == 0) { out->seq = -1; out->W_eff = W_eff; }
-    return;
+  int w, seq, W_eff, tile0; unsigned Pt, g0, g1, sh_q, sh_r; SeqInfo ws;
+  PieceShare ps; bool has_piece;
+  const bool by_piece = sc_.by_piece == 2 ? find_piece<MAXRB, true>(p, sc_, pw, ps, ws, has_piece)
+                                          : sc_.by_piece && find_piece<MAXRB, false>(p, sc_, pw, ps, ws, has_piece);
+  if (by_piece) {
+    if (!has_piece) { if (tid == 0) { out->seq = -1; out->W_eff = ps.W_eff; } return; }
+    w = ps.w; seq = ps.seq; W_eff = ps.W_eff; tile0 = ps.tile0;
+    Pt = g0 = 0; g1 = sh_q = 1; sh_r = 0;                        // (not read)
+  } else {
+    if (!find_share<MAXRB>(p, sc_, pw, w, seq, Pt, ws, g0, g1, sh_q, sh_r, W_eff)) {
+      if (tid == 0) { out->seq = -1; out->W_eff = W_eff; }
+      return;
+    }
+    // the share's first piece lies in the item that holds unit g0
+    int T, I; seq_shape(p, ws, ROWS_WG, T, I);
+    const int Tu = item_units(T, MF_START_COST);
+    if (Tu <= 0) { if (tid == 0) { out->seq = -1; out->W_eff = W_eff; } return; }
+    const int local = (int)(g0 - Pt);
+    const int u = local - (local / Tu) * Tu;
+    tile0 = max(u - MF_START_COST, 0);
   }
-  // page ids of the first two tiles of the share's first piece (it lies in the item that holds unit g0)
-  int T, I; seq_shape(p, ws, ROWS_WG, T, I);
-  const int Tu = item_units(T, MF_START_COST);
-  if (Tu <= 0) { if (tid == 0) { out->seq = -1; out->W_eff = W_eff; } return; }
-  const int local = (int)(g0 - Pt);
-  const int u = local - (local / Tu) * Tu;
-  const int tile0 = max(u - MF_START_COST, 0);
+  // page ids of the first two tiles of the share's first piece
   const int n_ct_all = (ws.L + MF_TK - 1) / MF_TK;
   if (tid < 2 * MF_GROUPS) {
     const int tau = tile0 + tid / MF_GROUPS, j = tid % MF_GROUPS;
@@ -372,13 +455,16 @@ __global__ __launch_bounds__(MF_BLOCK) void attn_mfma_plan_kernel(AttnParams p, 
     out->L = ws.L; out->row0 = ws.row0; out->n = ws.n; out->k = ws.k; out->v = ws.v; out->nb = ws.nb;
     out->page0 = ws.page0; out->npages = ws.npages;
     out->sh_q = sh_q; out->sh_r = sh_r; out->W_eff = W_eff; out->share = w;
+    out->pieces = by_piece ? ps.pieces : 0;
+    if (by_piece) { out->head = ps.head; out->rt = ps.rt; out->tile0 = ps.tile0; out->nt = ps.nt; }
   }
 }
 
 // Streaming kernel.  MAXRB: 32-row blocks a work-group can own (2: up to 64 tile rows, 4: up to 128).
 // PLANNED: the share comes from the plan entry the planning kernel left, else it is found here.
 // DH: head dim (128 or 64).
-template <int MAXRB, bool PLANNED, int DH>
+// SINGLE: the call is cut piece by piece (MfmaSched::by_piece == 2): no line, no second piece.
+template <int MAXRB, bool PLANNED, int DH, bool SINGLE>
 __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, MfmaSched sc_) {
   constexpr int ROWS_WG = 32 * MAXRB;
   constexpr int MF_D = DH;
@@ -404,6 +490,7 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
   const bf16_t* Vn = reinterpret_cast<const bf16_t*>(p.v_new);
 
   int w, seq, W_eff; unsigned Pt, g0, g1, sh_q, sh_r; SeqInfo ws;
+  PieceShare ps; ps.pieces = 0;                  // pieces > 0: the share is this one piece
   int nid0[MF_GROUPS], nid1[MF_GROUPS];          // page ids of the first two tiles of the piece to start
 #pragma unroll
   for (int j = 0; j < MF_GROUPS; ++j) { nid0[j] = 0; nid1[j] = 0; }
@@ -417,16 +504,30 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
     sh_q = (unsigned)sload(pe, 12); sh_r = (unsigned)sload(pe, 13); W_eff = sload(pe, 14); w = sload(pe, 15);
 #pragma unroll
     for (int j = 0; j < MF_GROUPS; ++j) { nid0[j] = sload(pe, 16 + j); nid1[j] = sload(pe, 20 + j); }
+    ps.pieces = sload(pe, 24); ps.head = sload(pe, 25); ps.rt = sload(pe, 26); ps.tile0 = sload(pe, 27); ps.nt = sload(pe, 28);
     // The plan is trusted to describe these arguments.  The checks below only keep a stale or foreign
     // plan from sending an access outside the caller's buffers (its results are then meaningless).
     W_eff = clampi(W_eff, 0, sc_.num_wgs);
     if (pw == 0 && tid == 0 && !sc_.by_item) sc_.entries[sc_.num_wgs] = make_int4(W_eff, 0, 0, 0);       // for the combine kernel
     if (seq < 0 || seq >= p.B || W_eff < 1 || w < 0 || w >= W_eff || g1 <= g0 || Pt > g0 || sh_q == 0) return;
     clamp_seq(p, ws);
+    if (!sc_.by_piece || ps.pieces < 0) ps.pieces = 0;
+    if (SINGLE && ps.pieces == 0) return;        // (not this call's plan)
   } else {
-    const bool has = find_share<MAXRB>(p, sc_, pw, w, seq, Pt, ws, g0, g1, sh_q, sh_r, W_eff);
-    if (pw == 0 && tid == 0 && !sc_.by_item) sc_.entries[sc_.num_wgs] = make_int4(W_eff, 0, 0, 0);
-    if (!has) return;
+    bool has = false;
+    if (SINGLE || sc_.by_piece) {
+      if (find_piece<MAXRB, SINGLE>(p, sc_, pw, ps, ws, has)) { if (!has) return; }
+      else ps.pieces = 0;
+    }
+    if (SINGLE && !has) return;
+    if (SINGLE || has) {
+      w = ps.w; seq = ps.seq; W_eff = ps.W_eff;
+      Pt = g0 = 0; g1 = sh_q = 1; sh_r = 0;      // (not read)
+    } else {
+      has = find_share<MAXRB>(p, sc_, pw, w, seq, Pt, ws, g0, g1, sh_q, sh_r, W_eff);
+      if (pw == 0 && tid == 0 && !sc_.by_item) sc_.entries[sc_.num_wgs] = make_int4(W_eff, 0, 0, 0);
+      if (!has) return;
+    }
   }
   // Slots, entries and every other per-share index below use the share's number w, not blockIdx.x.
   if (tid == 0 && !sc_.by_item) sc_.entries[w] = make_int4(-1, 0, 0, 0);
@@ -655,7 +756,17 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
 
   bool first_piece = true;
   Piece cur;
-  if (!next_piece(cur)) return;
+  if (SINGLE || ps.pieces > 0) {
+    // one piece of an item cut by find_piece (clamped again: a plan entry is not trusted with an access)
+    if (T <= 0) return;
+    cur.s = ws; cur.seq = seq; cur.T = T;
+    cur.head = clampi(ps.head, 0, p.Hkv - 1); cur.rt = clampi(ps.rt, 0, I / p.Hkv - 1);
+    cur.tile0 = clampi(ps.tile0, 0, T - 1); cur.nt = clampi(ps.nt, 1, T - cur.tile0);
+    cur.n_ct_all = (ws.L + MF_TK - 1) / MF_TK;
+    cur.kh = Kc + (long long)cur.head * p.sh; cur.vh = Vc + (long long)cur.head * p.sh;
+    cur.pi = p.page_indices + ws.page0;
+    g = g1;                                       // nothing after it
+  } else if (!next_piece(cur)) return;
   Lane ln = make_lane(cur);
   if (!PLANNED) start_ids(cur, nid0, nid1);       // (a plan entry brings the first piece's page ids with it)
   start_loads(cur, ln, nid0, nid1, !FD_DEFER_T1);
@@ -671,7 +782,7 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
   while (have) {
     // descriptor and page ids of the piece after this one: in flight during the tile loop
     Piece nxt;
-    have = next_piece(nxt);
+    have = SINGLE ? false : next_piece(nxt);
     if (have) start_ids(nxt, nid0, nid1);
     const SeqInfo& s = cur.s;
     const int tile0 = cur.tile0, nt = cur.nt, n_ct_all = cur.n_ct_all, c1 = cur.s.L;
@@ -684,9 +795,16 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
       // Its first piece sits in the work-group wf that owns the item's first tile, in slot 2 wf
       // if nothing of wf's share precedes the item (a share that begins among the item's start-up
       // units has nothing before the item's first tile), else 2 wf + 1; later pieces are in slots 2 w'.
-      const int wf = wg_of_unit(cur.item_u + MF_START_COST);
-      const int first_slot = 2 * wf + (share_start(wf) >= cur.item_u ? 0 : 1);
-      if (sc_.by_item) sc_.entries[item_id] = make_int4(first_slot, w, 0, 0);
+      // Cut piece by piece, piece j is in slot 2 (w - (pieces - 1 - j) row blocks).
+      int first_slot, step = 1;
+      if (SINGLE || ps.pieces > 0) {
+        step = I / p.Hkv;
+        first_slot = 2 * max(0, w - (ps.pieces - 1) * step);
+      } else {
+        const int wf = wg_of_unit(cur.item_u + MF_START_COST);
+        first_slot = 2 * wf + (share_start(wf) >= cur.item_u ? 0 : 1);
+      }
+      if (sc_.by_item) sc_.entries[item_id] = make_int4(first_slot, w, step, 0);
       else sc_.entries[w] = make_int4(cur.s.row0, cur.head | (cur.rt << 16), min(ROWS_WG, cur.s.n * p.G - cur.rt * ROWS_WG), first_slot);
     }
     const int RB = ln.RB, KQ = ln.KQ, rb = ln.rb, kq = ln.kq, trow = ln.trow, nn = ln.nn, hq = ln.hq;
@@ -944,8 +1062,8 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
 // ---------------------------------------------------------------------------------------
 // Merge the split partials of every item that was cut by a share boundary:
 //   M = max m;  out = sum 2^{m - M} acc / sum 2^{m - M} l;  lse = (M + log2 sum) ln 2.
-// The pieces of an item sit in its first slot, then in the first slot (2w) of every later
-// work-group up to the one it ended in.  Sixteen lanes per tile row, a lane owns eight adjacent
+// The pieces of an item sit in its first slot, then in the first slot (2w) of every later (cut piece by
+// piece: every step-th later) work-group up to the one it ended in.  Sixteen lanes per tile row, a lane owns eight adjacent
 // output columns; PG sixteen-lane groups share a row and take every PG-th piece.
 //   grid (items or shares, ROWS_WG PG / 16)
 // A block that finds nothing to merge costs as much as its launch, and the kernel follows another one on
@@ -961,11 +1079,11 @@ __global__ __launch_bounds__(256) void attn_mfma_combine_kernel(AttnParams p, Mf
   const int pg = PG == 1 ? 0 : lane >> 4;                      // piece group
   const int4* ep4 = sc_.entries + blockIdx.x;
   const int* ep = reinterpret_cast<const int*>(ep4);
-  int row0, head, rt, rows_here, first_slot, wl;
+  int row0, head, rt, rows_here, first_slot, wl, step = 1;     // step: shares from a piece to the next
   if (sc_.by_item) {
     const int sh = blockIdx.x / sc_.rt_max, seq = sh / p.Hkv;
     rt = blockIdx.x - sh * sc_.rt_max; head = sh - seq * p.Hkv;
-    first_slot = sload(ep, 0); wl = sload(ep, 1);
+    first_slot = sload(ep, 0); wl = sload(ep, 1); step = max(1, sload(ep, 2));
     const int r0 = sload(p.row_indptr, seq), r1 = sload(p.row_indptr, seq + 1);          // (clamped as load_seq does)
     row0 = clampi(r0, 0, p.total_rows);
     const int n = min(clampi(r1 - r0, 0, p.max_new_rows), p.total_rows - row0);
@@ -986,13 +1104,13 @@ __global__ __launch_bounds__(256) void attn_mfma_combine_kernel(AttnParams p, Mf
   const int T_row = rt * ROWS_WG + trow;
   const int nn = T_row / p.G, hq = head * p.G + T_row % p.G;
   if (row0 + nn >= p.total_rows) return;
-  const int np = wl - wf + 1;                     // pieces: slot first_slot, then 2 (wf + 1) .. 2 wl
+  const int np = (step == 1 ? wl - wf : (wl - wf) / step) + 1;     // pieces: slot first_slot, then 2 (wf + step) .. 2 wl
   auto ml_of = [&](int pi) -> const f32x4* {               // (max, sum, scale, -)
-    const long long slot = pi == 0 ? first_slot : 2 * (wf + pi);
+    const long long slot = pi == 0 ? first_slot : 2 * (wf + pi * step);
     return reinterpret_cast<const f32x4*>(sc_.part_ml + (slot * ROWS_WG + trow) * 4);
   };
   auto acc_of = [&](int pi) -> const u32x4* {               // eight fp16 columns of the scaled row
-    const long long slot = pi == 0 ? first_slot : 2 * (wf + pi);
+    const long long slot = pi == 0 ? first_slot : 2 * (wf + pi * step);
     return reinterpret_cast<const u32x4*>(sc_.part_acc + (slot * ROWS_WG + trow) * MF_D) + l16;
   };
   float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -1116,6 +1234,11 @@ static void fill_sched(const AttnParams& p, void* workspace, int kv_chunk, MfmaS
   sc.reuse = (long long)p.max_new_rows * p.G > rows_wg ? 1 : 0;
   sc.rt_max = (int)(((long long)p.max_new_rows * p.G + rows_wg - 1) / rows_wg);
   sc.by_item = (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs ? 1 : 0;
+  sc.by_piece = sc.by_item && p.B <= 64 && sc.fixed_share == 0 ? 1 : 0;
+  if (sc.by_piece && (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs / 2) sc.by_piece = 2;
+  // Pieces of one tile only where an item has at most eight (one pass of the combine kernel): 1 x 300 keys 11.8 -> 10.7 us;
+  // 1 x 2048 keys, 33 tiles: 14.6 us in twos, 16.0 one by one, 15.6 in threes.
+  sc.min_piece = p.max_kv_len <= 7 * MF_TK && p.max_new_rows <= MF_TK ? 1 : 2;
   size_t off_ml, off_en, off_pl;
   attn_mfma_workspace(sc.num_wgs, rows_wg, &off_ml, &off_en, &off_pl);
   char* base = reinterpret_cast<char*>(workspace);
@@ -1126,14 +1249,14 @@ static void fill_sched(const AttnParams& p, void* workspace, int kv_chunk, MfmaS
 }
 
 // The streaming kernel's LDS request is above the default limit: raised once per device.
-template <int MAXRB, bool PLANNED, int DH>
+template <int MAXRB, bool PLANNED, int DH, bool SINGLE>
 static hipError_t configure_mfma() {
   static std::atomic<unsigned long long> done{0};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 64 && (done.load(std::memory_order_acquire) >> dev & 1ull)) return hipSuccess;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_mfma_kernel<MAXRB, PLANNED, DH>),
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_mfma_kernel<MAXRB, PLANNED, DH, SINGLE>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)MfLds<DH>::BYTES);
   if (e == hipSuccess && dev < 64) done.fetch_or(1ull << dev, std::memory_order_release);
   return e;
@@ -1149,17 +1272,17 @@ hipError_t run_attn_mfma_plan(const AttnParams& p, void* workspace, int kv_chunk
   return hipGetLastError();
 }
 
-template <int MAXRB, bool PLANNED, int DH>
+template <int MAXRB, bool PLANNED, int DH, bool SINGLE>
 static hipError_t launch_mfma_d(const AttnParams& p, const MfmaSched& sc, hipStream_t st) {
-  hipError_t e = configure_mfma<MAXRB, PLANNED, DH>();
+  hipError_t e = configure_mfma<MAXRB, PLANNED, DH, SINGLE>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_mfma_kernel<MAXRB, PLANNED, DH>), dim3(sc.num_wgs), dim3(MF_BLOCK), MfLds<DH>::BYTES, st, p, sc);
+  hipLaunchKernelGGL((attn_mfma_kernel<MAXRB, PLANNED, DH, SINGLE>), dim3(sc.num_wgs), dim3(MF_BLOCK), MfLds<DH>::BYTES, st, p, sc);
   return hipGetLastError();
 }
 template <int MAXRB, bool PLANNED>
 static hipError_t launch_mfma(const AttnParams& p, const MfmaSched& sc, hipStream_t st) {
-  if (p.D == 64) return launch_mfma_d<MAXRB, PLANNED, 64>(p, sc, st);
-  if (p.D == 128) return launch_mfma_d<MAXRB, PLANNED, 128>(p, sc, st);
+  if (p.D == 64) return sc.by_piece == 2 ? launch_mfma_d<MAXRB, PLANNED, 64, true>(p, sc, st) : launch_mfma_d<MAXRB, PLANNED, 64, false>(p, sc, st);
+  if (p.D == 128) return sc.by_piece == 2 ? launch_mfma_d<MAXRB, PLANNED, 128, true>(p, sc, st) : launch_mfma_d<MAXRB, PLANNED, 128, false>(p, sc, st);
   return hipErrorInvalidValue;                  // (attn_mfma_supports keeps other head dims away)
 }
 

@@ -162,6 +162,32 @@ def test_combine_layouts(fd, D, B, Hkv, n, kv, chunk):
         _check(fd, inp, "bf16", f"combine B={B} Hkv={Hkv} n={n}, one sequence without rows", kv_chunk=chunk)
 
 
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("B,Hkv,n,kv", [
+    (1, 1, 3, (20, 20)),               # one item of two tiles: the smallest pieces
+    (1, 8, 4, (384, 448)),             # at most eight tiles an item: pieces of one tile
+    (1, 8, 70, (449, 449)),            # three row blocks of 128 and two tiles of new keys: pieces at least two tiles long
+    (4, 64, 4, (0, 700)),              # 256 items: always cut piece by piece, whole items among them
+    (5, 64, 4, (500, 700)),            # 320 items of like length: s above a share, along the line
+    (64, 8, 4, (1, 130)),              # 512 items in 64 sequences: one work-group each
+    (65, 2, 4, (1, 130)),              # 65 sequences: along the line
+])
+def test_items_cut_piece_by_piece(fd, D, B, Hkv, n, kv):
+    """Both cuts of the work at the sizes where the rule changes; planned and self-planning calls agree bit for bit."""
+    w = _wl("pieces", "bf16", B, 4 * Hkv, Hkv, D, 16, kv, (max(1, n - 2), n), 2, seed=170 + B + n)
+    inp = W.make_attention_inputs(w)
+    call = AttnCall(fd, inp)
+    out, lse = call.run()
+    ref, ref_lse = oracle_attention(inp)
+    assert_attn_close(out, ref, "bf16", f"pieces B={B} Hkv={Hkv} n={n}")
+    assert np.abs(lse - ref_lse).max() <= 2e-2
+    fd.fd_verify_draft_plan(call.args)
+    call.args.flags |= fd.FD_ATTN_PLANNED
+    call.out.fill_(float("nan"))
+    out2, lse2 = call.run()
+    assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
+
+
 @pytest.mark.parametrize("seed", range(12))
 def test_random_workloads(fd, seed):
     """Seeded random shapes through the MFMA path: batch, head grouping, page size, ragged prefixes
