@@ -33,6 +33,8 @@
 //                      with lane^32 and the row sum none until the end
 //   O^T += V^T P^T     A = V^T fragments fetched with ds_read_b64_tr_b16 (the LDS transpose
 //                      read of gfx950), B = P packed to bf16 straight from the S^T registers
+// The 128-row, head dim 128 variant differs: tiles go from memory straight into LDS (MfTileLds, load_group_to_lds), one
+// tile ahead, and the 64 registers that staged them hold LDS fragments instead (iteration_direct).
 // The next piece's page ids are requested before the current piece's tile loop, its first two
 // tiles and query rows before the current piece is merged and stored.
 //
@@ -51,6 +53,9 @@
 // (3 and 3: measured best of 2..4; more costs registers the 64-row variant does not have)
 #ifndef FD_PF_K
 #define FD_PF_K 3
+#endif
+#ifndef FD_PF_KD
+#define FD_PF_KD 8                        // ... in the variant whose tiles go straight to LDS
 #endif
 #ifndef FD_PF_V
 #define FD_PF_V 3
@@ -87,6 +92,16 @@ template <int DH> struct MfLds {
   static constexpr int V_ELEMS = MF_TK * VSTR;
   static constexpr int BUF_ELEMS = K_ELEMS + V_ELEMS;      // one K+V tile
   static constexpr size_t BYTES = (size_t)2 * BUF_ELEMS * sizeof(bf16_t);   // double buffered
+};
+// Tiles of the 128-row, head dim 128 variant go from memory straight into LDS (buffer_load ... lds): a wave instruction
+// writes 1 KB in lane order, four 256-byte rows without padding, and the bank conflicts that the padding avoids are
+// avoided by what each lane fetches instead: the 16-byte slot s of row r holds columns 8 (s ^ f(r)) .., with f(r) = r mod 16
+// for K (sixteen rows, one column: sixteen slots) and 4 (r mod 4) + (r / 4) mod 4 for V (a transposing read takes 64
+// bytes of four consecutive rows).
+constexpr int MF_DIRECT_BUF = 2 * MF_TK * 128;           // elements of one K+V tile
+template <int MAXRB, int DH> struct MfTileLds {
+  static constexpr bool DIRECT = MAXRB == 4 && DH == 128;
+  static constexpr size_t BYTES = DIRECT ? (size_t)2 * MF_DIRECT_BUF * sizeof(bf16_t) : MfLds<DH>::BYTES;
 };
 constexpr int MF_BLOCKS = MF_TK / 32;     // 32-key MFMA blocks per tile
 constexpr int MF_GROUPS = MF_TK / 16;     // 16-key load groups per tile
@@ -167,6 +182,39 @@ __device__ __forceinline__ void unpack_f16x4(u32x2 w, float (&x)[4]) {
   const f16x4 hv = __builtin_bit_cast(f16x4, w);
 #pragma unroll
   for (int e = 0; e < 4; ++e) x[e] = (float)hv[e];
+}
+
+// A wave's 4 KB of K and 4 KB of V (four times 64 lanes of 16 bytes each, lane after lane) from two buffers straight into
+// LDS, V 16 KB above K; NT: streaming.  As inline assembly, because after the builtin the compiler holds back every
+// transposing LDS read until the loads have landed, whichever part of LDS they write.  No register waits for
+// them: s_waitcnt vmcnt, then the barrier that hands the tile over.  m0, the LDS address, is put back.
+template <bool NT>
+__device__ __forceinline__ void load_group_to_lds(u32x4 rk, u32x4 rv, const unsigned (&k)[4], const unsigned (&v)[4], unsigned lds_byte) {
+  unsigned keep;
+#define FD_LDS_LOADS(CACHE)                                                                                     \
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"                                           \
+               "buffer_load_dwordx4 %4, %2, 0 offen" CACHE " lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"    \
+               "buffer_load_dwordx4 %5, %2, 0 offen" CACHE " lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"    \
+               "buffer_load_dwordx4 %6, %2, 0 offen" CACHE " lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"    \
+               "buffer_load_dwordx4 %7, %2, 0 offen" CACHE " lds\n\ts_add_u32 m0, m0, 0x3400\n\ts_nop 0\n\t"   \
+               "buffer_load_dwordx4 %8, %3, 0 offen" CACHE " lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"    \
+               "buffer_load_dwordx4 %9, %3, 0 offen" CACHE " lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"    \
+               "buffer_load_dwordx4 %10, %3, 0 offen" CACHE " lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"   \
+               "buffer_load_dwordx4 %11, %3, 0 offen" CACHE " lds\n\ts_mov_b32 m0, %0"                           \
+               : "=&s"(keep) : "s"(lds_byte), "s"(rk), "s"(rv), "v"(k[0]), "v"(k[1]), "v"(k[2]), "v"(k[3]),    \
+                 "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]) : "memory", "scc")
+  if (NT) FD_LDS_LOADS(" nt"); else FD_LDS_LOADS("");
+#undef FD_LDS_LOADS
+}
+// Buffer descriptor (base, no stride, size in bytes) of a base equal in every lane, in scalar registers.
+__device__ __forceinline__ u32x4 buffer_words(const void* base, int bytes) {
+  const unsigned long long a = (unsigned long long)(uintptr_t)base;
+  const u32x4 r = {(unsigned)__builtin_amdgcn_readfirstlane((unsigned)a), (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xffffu),
+                   (unsigned)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
+  return r;
+}
+__device__ __forceinline__ unsigned lds_offset(const void* p) {
+  return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
 }
 
 // Tiles of one item of this sequence, and how many items (heads x row blocks) it has.
@@ -476,6 +524,7 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
   constexpr int RPL = 64 / LPR;                  // rows one load instruction of a wave covers
   constexpr int NLD = 16 / RPL;                  // load instructions per tensor for a wave's 16-key group
   typedef TileRegsT<NLD> TileRegs;
+  constexpr bool DIRECT = MfTileLds<MAXRB, DH>::DIRECT;
   constexpr int MF_START_COST = mf_start_cost(MAXRB);
   constexpr int PF_K = FD_PF_K, PF_V = FD_PF_V;   // LDS fragment requests run this many MFMAs ahead
   extern __shared__ __attribute__((aligned(16))) bf16_t lds[];
@@ -659,6 +708,20 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
       }
     }
   };
+  // DIRECT: a tile's rows go to LDS buffer `buf`; the wave waits for them with tile_landed().  Lane l of load i takes slot
+  // l & 15 of row 4 i + (l >> 4) of the wave's 16-key group; rows past the descriptor's size are written as zeros.
+  auto load_rows_lds = [&](const bf16_t* kbase, const bf16_t* vbase, int nrec, unsigned pitch, int buf) {
+    const u32x4 rk_ = buffer_words(kbase, nrec), rv_ = buffer_words(vbase, nrec);
+    const unsigned kd = __builtin_amdgcn_readfirstlane(lds_offset(lds) + 2u * (buf * MF_DIRECT_BUF + 16 * wave * 128));
+    const unsigned r4 = lane >> 4, ck = 16u * (l16 ^ r4), cv = 16u * (l16 ^ (r4 << 2));
+    unsigned vk[4], vv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned row = (r4 + 4u * i) * (2u * pitch);
+      vk[i] = row + (ck ^ (64u * i)); vv[i] = row + (cv ^ (16u * i));
+    }
+    if (sc_.reuse) load_group_to_lds<false>(rk_, rv_, vk, vv, kd); else load_group_to_lds<true>(rk_, rv_, vk, vv, kd);
+  };
   auto nrec_of = [&](int valid, unsigned pitch) -> int {                 // valid rows of a 16-row group
     const int v16 = valid < 0 ? 0 : (valid > 16 ? 16 : valid);
     return v16 > 0 ? (int)(((unsigned)(v16 - 1) * pitch + MF_D) * 2u) : 0;
@@ -667,7 +730,7 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
   // 32 x 32 -> 64 bit product instead of a 64 x 64 one
   const unsigned sp32 = (unsigned)p.sp, st32 = (unsigned)p.st;
   const int nrec_full = (int)((15u * st32 + MF_D) * 2u);
-  auto load_tile = [&](const Piece& pc, int tau, const int (&pg)[MF_GROUPS], TileRegs& r) {
+  auto load_tile = [&](const Piece& pc, int tau, const int (&pg)[MF_GROUPS], auto&& load, auto&& load_new) {
     const int gi = __builtin_amdgcn_readfirstlane(wave);   // this wave's 16-key group of the tile
     if (tau < pc.n_ct_all) {
       const int gs = tau * MF_TK + 16 * gi;
@@ -677,13 +740,22 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
       ph = oob ? 0u : ph;
       const unsigned long long ub = (unsigned long long)ph * sp32 + (unsigned)(gs & page_mask) * st32;
       const int nrec = gs + 16 <= pc.s.L ? nrec_full : nrec_of(pc.s.L - gs, st32);   // rows past the prefix read as zero
-      load_rows(pc.kh + ub, pc.vh + ub, nrec, voff_c, r);
+      load(pc.kh + ub, pc.vh + ub, nrec);
     } else {
       const int key0 = (tau - pc.n_ct_all) * MF_TK + 16 * gi;
       const long long ub = ((long long)(pc.s.row0 + key0) * p.Hkv + pc.head) * MF_D;
-      load_rows(Kn + ub, Vn + ub, nrec_of(pc.s.n - key0, (unsigned)new_pitch), voff_n, r);
+      load_new(Kn + ub, Vn + ub, nrec_of(pc.s.n - key0, (unsigned)new_pitch));
     }
   };
+  auto load_tile_regs = [&](const Piece& pc, int tau, const int (&pg)[MF_GROUPS], TileRegs& r) {
+    load_tile(pc, tau, pg, [&](const bf16_t* k, const bf16_t* v, int nrec) { load_rows(k, v, nrec, voff_c, r); },
+              [&](const bf16_t* k, const bf16_t* v, int nrec) { load_rows(k, v, nrec, voff_n, r); });
+  };
+  auto load_tile_lds = [&](const Piece& pc, int tau, const int (&pg)[MF_GROUPS], int buf) {
+    load_tile(pc, tau, pg, [&](const bf16_t* k, const bf16_t* v, int nrec) { load_rows_lds(k, v, nrec, st32, buf); },
+              [&](const bf16_t* k, const bf16_t* v, int nrec) { load_rows_lds(k, v, nrec, (unsigned)new_pitch, buf); });
+  };
+  auto tile_landed = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
   auto store_tile = [&](int buf, const TileRegs& r) {
     bf16_t* Kb = lds + buf * MF_BUF_ELEMS;
     bf16_t* Vb = Kb + MF_K_ELEMS;
@@ -749,9 +821,15 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
 #pragma unroll
       for (int st = 0; st < NST; ++st) qf[st] = as_bf16x8(zero);
     }
-    load_tile(pc, pc.tile0, id0, rA);
-    if (pc.nt > 1 && second_tile) load_tile(pc, pc.tile0 + 1, id1, rB);
-    fetch_pages(pc, pc.tile0 + 2, pg);
+    if (DIRECT) {
+      load_tile_lds(pc, pc.tile0, id0, 0);
+#pragma unroll
+      for (int j = 0; j < MF_GROUPS; ++j) pg[j] = id1[j];
+    } else {
+      load_tile_regs(pc, pc.tile0, id0, rA);
+      if (pc.nt > 1 && second_tile) load_tile_regs(pc, pc.tile0 + 1, id1, rB);
+      fetch_pages(pc, pc.tile0 + 2, pg);
+    }
   };
 
   bool first_piece = true;
@@ -818,10 +896,13 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
 #pragma unroll
       for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
 
-    store_tile(0, rA);                             // waits for the piece's first tile
+    if (DIRECT) tile_landed();
+    else {
+      store_tile(0, rA);                           // waits for the piece's first tile
 #if FD_DEFER_T1
-    if (first_piece && nt > 1) load_tile(cur, tile0 + 1, t1ids, rB);
+      if (first_piece && nt > 1) load_tile_regs(cur, tile0 + 1, t1ids, rB);
 #endif
+    }
     __syncthreads();
 
     // Two tiles are kept in registers: while tile t is multiplied out of LDS, tile t+2 is requested and
@@ -840,7 +921,7 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
       const bf16_t* Ks = lds + (t & 1) * MF_BUF_ELEMS;
       const bf16_t* Vs = Ks + MF_K_ELEMS;
       if (t + 2 < nt) {
-        load_tile(cur, tau + 2, pg, r_load);
+        load_tile_regs(cur, tau + 2, pg, r_load);
         fetch_pages(cur, tau + 3, pg);
       }
 
@@ -961,9 +1042,122 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
       if (t + 1 < nt) store_tile((t + 1) & 1, r_store);
       __syncthreads();                           // tile t fully consumed, tile t+1 visible
     };
+    // DIRECT: while tile t is multiplied out of one LDS buffer, tile t+1 flies into the other.  A wave takes both 32-key blocks
+    // of the tile under one softmax step: the sixteen MFMAs of S on two chains, and the exponentials of the second
+    // block between the P V MFMAs of the first.  The registers that staged tiles hold LDS fragments instead, eight MFMAs
+    // ahead of their use.  Against staging through registers, block by block (us a call): 2 sequences of 272 rows of 4
+    // heads 76.1 -> 71.4, 8 of 36 rows 68.1 -> 65.9, 4 of 32 rows over 32768 keys 109.4 -> 107.4.  Bound by issue: of 72 us
+    // at the first size the MFMAs alone take 23, the softmax 13 on top (an MFMA in flight keeps the vector pipe of its
+    // SIMD busy for most of its time), waiting for tiles 10; the LDS reads hide behind the MFMAs.
+    auto iteration_direct = [&](int t, int buf) {
+      const int tau = tile0 + t;
+      if (((t & 1) != 0) != late_wg) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
+      if (t + 1 < nt) {
+        load_tile_lds(cur, tau + 1, pg, buf ^ 1);
+        fetch_pages(cur, tau + 2, pg);
+      }
+      const bool is_new = tau >= n_ct_all;
+      const int tile_base = is_new ? (tau - n_ct_all) * MF_TK : tau * MF_TK;
+      const int tile_end = is_new ? s.n : c1;                     // keys at or beyond are invisible
+      const bool masked = is_new | (tile_base + MF_TK > tile_end);
+      if (wave_has_rows) {
+        const char* Kb = reinterpret_cast<const char*>(lds + buf * MF_DIRECT_BUF);
+        const char* Vb = Kb + 2 * MF_TK * 128;
+        const unsigned ka = c32 * 256 + 16 * (h ^ l16);            // K row c32, columns 8 h ..: slot (2 st + h) ^ (row mod 16)
+        auto kread = [&](int f) { return *reinterpret_cast<const u32x4*>(Kb + (f & 1) * 8192 + (ka ^ (32u * (f >> 1)))); };
+        // V row 16 q + 8 j + 4 h + (l16 >> 2), columns 32 d + 16 (c32 >> 4) + 4 (l16 & 3)
+        const unsigned va = (4 * h + (l16 >> 2)) * 256 + 16 * ((2 * (c32 >> 4) + ((l16 & 3) >> 1)) ^ ((l16 >> 2) << 2) ^ h) + 8 * (l16 & 1);
+        s16x4 vf[4 * NDB];
+        auto vread = [&](int kb, int g) {
+          const char* vp = Vb + kb * 8192 + (g / NDB) * 4096;
+          vf[2 * g] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp + (va ^ (64u * (g % NDB)))));
+          vf[2 * g + 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp + 2048 + (va ^ (64u * (g % NDB) + 32u))));
+        };
+        f32x16 sc[2];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sc[0][i] = sc[1][i] = 0.f;
+        u32x4 kf[2 * NST];
+#pragma unroll
+        for (int f = 0; f < FD_PF_KD; ++f) kf[f] = kread(f);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = 0; f < 2 * NST; ++f) {
+          sc[f & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[f]), qf[f >> 1], sc[f & 1], 0, 0, 0);
+          if (f + FD_PF_KD < 2 * NST) kf[f + FD_PF_KD] = kread(f + FD_PF_KD);
+          else if (f + FD_PF_KD - 2 * NST < 2 * NDB) vread(0, f + FD_PF_KD - 2 * NST);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (masked) {
+          RowWindow wv = ln.win;
+          if (!is_new) { wv.vr = c1; wv.lo = 0; wv.hi = 0; }       // a prefix tile: the keys below the prefix length
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+              const int key = tile_base + 32 * kb + 8 * (i >> 2) + 4 * h + (i & 3);
+              sc[kb][i] = new_key_visible(wv, key) ? sc[kb][i] : -INFINITY;
+            }
+        }
+        float mx = fmaxf(sc[0][0], sc[1][0]);
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = fmaxf(fmaxf(mx, sc[0][i]), sc[1][i]);
+        {
+          const unsigned mu = __builtin_bit_cast(unsigned, mx);
+          const auto sw = __builtin_amdgcn_permlane32_swap(mu, mu, false, false);
+          mx = fmaxf(__builtin_bit_cast(float, (unsigned)sw[0]), __builtin_bit_cast(float, (unsigned)sw[1]));
+        }
+        const float m_cand = fmaxf(m_run, mx * cs);                // (MF_LAZY: as in softmax_block)
+        const float m_new = m_cand > m_run + MF_LAZY ? m_cand : m_run;
+        const float m_sub = (m_new == -INFINITY) ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_sub);
+        m_run = m_new;
+        if (__any(alpha != 1.f)) {
+          l_lane *= alpha;
+#pragma unroll
+          for (int b = 0; b < NDB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
+        }
+        float l0 = 0.f, l1 = 0.f;
+        unsigned pk[2][8];
+        auto exp_pair = [&](int kb, int i) {
+          const float a = __builtin_amdgcn_exp2f(fmaf(sc[kb][2 * i], cs, -m_sub));
+          const float b = __builtin_amdgcn_exp2f(fmaf(sc[kb][2 * i + 1], cs, -m_sub));
+          l0 += a; l1 += b;
+          pk[kb][i] = pack_bf16x2(a, b);
+        };
+        auto pv = [&](int kb, int g) {
+          const int q = g / NDB;
+          const u32x4 pw4 = {pk[kb][4 * q], pk[kb][4 * q + 1], pk[kb][4 * q + 2], pk[kb][4 * q + 3]};
+          const s16x8 vv = {vf[2 * g][0], vf[2 * g][1], vf[2 * g][2], vf[2 * g][3],
+                            vf[2 * g + 1][0], vf[2 * g + 1][1], vf[2 * g + 1][2], vf[2 * g + 1][3]};
+          o[g % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv), as_bf16x8(pw4), o[g % NDB], 0, 0, 0);
+        };
+#pragma unroll
+        for (int i = 0; i < 8; ++i) exp_pair(0, i);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < 2 * NDB; ++g) {
+          pv(0, g);
+          vread(1, g);
+          exp_pair(1, g);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        l_lane += l0 + l1;
+#pragma unroll
+        for (int g = 0; g < 2 * NDB; ++g) pv(1, g);
+      }
+      tile_landed();
+      __syncthreads();                           // tile t fully consumed, tile t+1 visible
+    };
     for (int t = 0; t < nt; t += 2) {
-      iteration(t, rB, rA);
-      if (t + 1 < nt) iteration(t + 1, rA, rB);
+      if constexpr (DIRECT) {
+        iteration_direct(t, 0);
+        if (t + 1 < nt) iteration_direct(t + 1, 1);
+      } else {
+        iteration(t, rB, rA);
+        if (t + 1 < nt) iteration(t + 1, rA, rB);
+      }
     }
 
     // ---- next piece: get its loads going before this one is merged and stored --------------
@@ -1257,7 +1451,7 @@ static hipError_t configure_mfma() {
   if (e != hipSuccess) return e;
   if (dev < 64 && (done.load(std::memory_order_acquire) >> dev & 1ull)) return hipSuccess;
   e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_mfma_kernel<MAXRB, PLANNED, DH, SINGLE>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)MfLds<DH>::BYTES);
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)MfTileLds<MAXRB, DH>::BYTES);
   if (e == hipSuccess && dev < 64) done.fetch_or(1ull << dev, std::memory_order_release);
   return e;
 }
@@ -1276,7 +1470,7 @@ template <int MAXRB, bool PLANNED, int DH, bool SINGLE>
 static hipError_t launch_mfma_d(const AttnParams& p, const MfmaSched& sc, hipStream_t st) {
   hipError_t e = configure_mfma<MAXRB, PLANNED, DH, SINGLE>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_mfma_kernel<MAXRB, PLANNED, DH, SINGLE>), dim3(sc.num_wgs), dim3(MF_BLOCK), MfLds<DH>::BYTES, st, p, sc);
+  hipLaunchKernelGGL((attn_mfma_kernel<MAXRB, PLANNED, DH, SINGLE>), dim3(sc.num_wgs), dim3(MF_BLOCK), (MfTileLds<MAXRB, DH>::BYTES), st, p, sc);
   return hipGetLastError();
 }
 template <int MAXRB, bool PLANNED>

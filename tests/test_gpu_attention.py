@@ -188,6 +188,21 @@ def test_items_cut_piece_by_piece(fd, D, B, Hkv, n, kv):
     assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
 
 
+@pytest.mark.parametrize("n, kv, page", [
+    (17, (0, 1), 16),        # 68 rows: the last wave has none, empty and one-key prefixes
+    (32, (63, 65), 16),      # 128 rows, one key either side of a tile
+    (32, (127, 129), 32),
+    (24, (17, 49), 64),      # groups of sixteen keys beyond the end of the only tile
+    (33, (500, 700), 16),    # 132 rows: a second row block of four
+    (70, (200, 330), 16),    # new rows of their own in two tiles
+])
+@pytest.mark.parametrize("B", [3, 70])                               # cut piece by piece, along the line
+def test_128_row_tiles(fd, B, n, kv, page):
+    w = _wl("rows128", "bf16", B, 8, 2, 128, page, kv, (5, 5), n - 5, seed=91)
+    inp = W.make_attention_inputs(w)
+    _check(fd, inp, "bf16", f"{B} sequences, {n} rows, kv {kv}, page {page}")
+
+
 @pytest.mark.parametrize("seed", range(12))
 def test_random_workloads(fd, seed):
     """Seeded random shapes through the MFMA path: batch, head grouping, page size, ragged prefixes
