@@ -1207,7 +1207,67 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
     // ---- epilogue of the piece ------------------------------------------------------------
     if (kq == 0) {
       const float l_tot = l_lane + __shfl_xor(l_lane, 32);
-      if (row_valid) {
+      // A lane holds eight bytes of every sixteen of its row.  Stored from there, every instruction touches 32 rows.  With
+      // 128 rows (every wave stores) the wave's rows go through LDS (its own 32 rows, no barrier; slot ^ row against bank
+      // conflicts) and leave as whole rows: 8 sequences of 36 rows of 4 heads 65.9 -> 60.7 us a call, 4 x 32768 keys
+      // 107.4 -> 102.9, 2 of 272 rows 71.4 -> 68.3.  With 64 rows (half of the waves or one of them) it gains nothing: 16
+      // sequences of 512..4096 keys 37.3 -> 37.0, one of 2048 13.1 -> 13.3, 128 of 1024..8192 409 -> 414.
+      if constexpr (MAXRB == 4) {
+        const long long prow = (long long)slot * ROWS_WG + rb * 32;  // first row of this wave's split partial
+        float scale;
+        if (whole) {                                // whole item seen here: normalise and store
+          scale = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+          if (row_valid && p.lse && h == 0)
+            p.lse[(long long)(s.row0 + nn) * p.Hq + hq] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
+        } else {
+          // split partial for the combine kernel: the row scaled to [-1, 1] in fp16 (rounding 2^-11 of
+          // the row's largest entry, a quarter of what the bf16 result carries) plus (max, sum, scale)
+          float amax = 0.f;
+#pragma unroll
+          for (int b = 0; b < NDB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) amax = fmaxf(amax, fabsf(o[b][i]));
+          amax = fmaxf(amax, __shfl_xor(amax, 32));
+          scale = amax > 0.f ? 1.0f / amax : 0.f;
+          if (row_valid && h == 0) {
+            f32x4 ml4 = {m_run, l_tot, amax, 0.f};
+            *reinterpret_cast<f32x4*>(sc_.part_ml + (prow + c32) * 4) = ml4;
+          }
+        }
+        constexpr int SL = DH / 8;                  // 16-byte slots of a row
+        char* st = reinterpret_cast<char*>(lds + (DIRECT ? MF_DIRECT_BUF : 0) + wave * (32 * DH));     // (DIRECT: buffer 0 takes the next piece's first tile)
+        unsigned wr = c32 * (2 * DH) + 16 * (c32 & (SL - 1)) + 8 * h, rd = (lane / SL) * (2 * DH) + 16 * ((lane % SL) ^ (lane / SL));
+        asm volatile("" : "+v"(wr), "+v"(rd));      // (computed here: as loop invariants the addresses would hold registers through the tile loop)
+        auto stage = [&](auto pack) {
+#pragma unroll
+          for (int b = 0; b < NDB; ++b)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+              const u32x2 wv = {pack(o[b][4 * a] * scale, o[b][4 * a + 1] * scale), pack(o[b][4 * a + 2] * scale, o[b][4 * a + 3] * scale)};
+              *reinterpret_cast<u32x2*>(st + (wr ^ (16u * (4 * b + a)))) = wv;
+            }
+        };
+        if (whole) stage([](float lo, float hi) { return pack_bf16x2(lo, hi); }); else stage([](float lo, float hi) { return pack_f16x2(lo, hi); });
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int row0_w = cur.rt * ROWS_WG + rb * 32, rows_w = s.n * p.G - row0_w;
+#pragma unroll
+        for (int i = 0; i < SL / 2; ++i) {
+          const int r = i * (64 / SL) + lane / SL, c = lane % SL;
+          const u32x4 val = *reinterpret_cast<const u32x4*>(st + i * 1024 + (rd ^ (16u * (i * (64 / SL) % SL))));
+          if (r < rows_w) {
+            if (whole) {
+              const int T_row = row0_w + r;
+              const int rn = sc_.group_shift >= 0 ? T_row >> sc_.group_shift : T_row / p.G;
+              const int rh = cur.head * p.G + (T_row - rn * p.G);
+              reinterpret_cast<u32x4*>(reinterpret_cast<bf16_t*>(p.out) + ((long long)(s.row0 + rn) * p.Hq + rh) * MF_D)[c] = val;
+            } else {
+              reinterpret_cast<u32x4*>(sc_.part_acc + (prow + r) * MF_D)[c] = val;
+            }
+          }
+        }
+      } else if (row_valid) {
         if (whole) {                              // whole item seen here: normalise and store
           const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
           bf16_t* op = reinterpret_cast<bf16_t*>(p.out) + ((long long)(s.row0 + nn) * p.Hq + hq) * MF_D + 4 * h;
