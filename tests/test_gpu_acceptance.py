@@ -67,6 +67,29 @@ def test_greedy_row_stride_and_unaligned_rows(fd):
     _greedy_case(fd, vals, [0, 2, 6], toks, vocab=1001)
 
 
+@pytest.mark.parametrize("V", [3, 8, 15, 2047, 2049, 4097, 10243, 20489])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_row_shares_end_anywhere(fd, dtype, V):
+    """Rows that end inside a vector, one after a share or before eight logits, at an odd pitch: the last of a row is its maximum."""
+    rng = np.random.default_rng(V)
+    indptr = np.array([0, 4, 5, 21], dtype=np.int32)
+    pitch = V + 1 + V % 2                                    # odd: rows start at every alignment
+    vals = (rng.standard_normal((21, pitch)) * 2).astype(np.float32)
+    vals[:, V:] = 99.0                                       # beyond the vocabulary
+    vals[::3, V - 1] = 12.0
+    logits = W.f32_to_bf16_bits(vals) if dtype == "bf16" else vals
+    _greedy_case(fd, logits, indptr, rng.integers(0, V, size=21).astype(np.int32), vocab=V)
+    _draft_select_case(fd, logits, indptr, 0.8, 0.2, vocab=V)
+    dv = (vals + 0.6 * rng.standard_normal(vals.shape)).astype(np.float32)
+    draft = W.f32_to_bf16_bits(dv) if dtype == "bf16" else dv
+    toks = rng.integers(0, V, size=21).astype(np.int32); toks[1::2] = V - 1
+    ua, ur = rng.random(21, dtype=np.float32), rng.random(21, dtype=np.float32)
+    ref = (logits[:, :V], draft[:, :V], indptr, toks, ua, ur, 0.8)
+    o_acc, o_bon, info = oc.accept_sample(*ref)
+    acc, bon = run_sample(fd, logits, draft, indptr, toks, ua, ur, 0.8, vocab=V)
+    compare_sampling(acc, bon, o_acc, o_bon, info, indptr, *ref[:2], toks, ua, ur, 0.8)
+
+
 def test_cfg3_greedy_vocab_151936(fd):
     w, a = W.CONFIGS["cfg3"]
     lens = W.make_lengths(w)
