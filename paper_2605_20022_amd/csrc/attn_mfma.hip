@@ -55,7 +55,7 @@
 #define FD_PF_K 3
 #endif
 #ifndef FD_PF_KD
-#define FD_PF_KD 8                        // ... in the variant whose tiles go straight to LDS
+#define FD_PF_KD 4                        // ... in the variant whose tiles go straight to LDS (4, 6, 8: within 1 %)
 #endif
 #ifndef FD_PF_V
 #define FD_PF_V 3
@@ -1044,14 +1044,15 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
     };
     // DIRECT: while tile t is multiplied out of one LDS buffer, tile t+1 flies into the other.  A wave takes both 32-key blocks
     // of the tile under one softmax step: the sixteen MFMAs of S on two chains, and the exponentials of the second
-    // block between the P V MFMAs of the first.  The registers that staged tiles hold LDS fragments instead, eight MFMAs
-    // ahead of their use.  Against staging through registers, block by block (us a call): 2 sequences of 272 rows of 4
+    // block between the P V MFMAs of the first.  The registers that staged tiles hold LDS fragments instead.  Against staging through registers, block by block (us a call): 2 sequences of 272 rows of 4
     // heads 76.1 -> 71.4, 8 of 36 rows 68.1 -> 65.9, 4 of 32 rows over 32768 keys 109.4 -> 107.4.  Bound by issue: of 72 us
     // at the first size the MFMAs alone take 23, the softmax 13 on top (an MFMA in flight keeps the vector pipe of its
     // SIMD busy for most of its time), waiting for tiles 10; the LDS reads hide behind the MFMAs.
     auto iteration_direct = [&](int t, int buf) {
       const int tau = tile0 + t;
-      if (((t & 1) != 0) != late_wg) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
+      // Waves in their MFMA phases go before waves in their softmax (with the turns of the other variant: 2 sequences of 272 rows
+      // 70.5 -> 68.2 us a call, 8 of 36 rows 64 -> 58.1, 4 x 32768 keys 104 -> 99.1).
+      __builtin_amdgcn_s_setprio(1);
       if (t + 1 < nt) {
         load_tile_lds(cur, tau + 1, pg, buf ^ 1);
         fetch_pages(cur, tau + 2, pg);
@@ -1087,6 +1088,9 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
           else if (f + FD_PF_KD - 2 * NST < 2 * NDB) vread(0, f + FD_PF_KD - 2 * NST);
           __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int g = FD_PF_KD; g < 2 * NDB; ++g) vread(0, g);
+        __builtin_amdgcn_s_setprio(0);
         if (masked) {
           RowWindow wv = ln.win;
           if (!is_new) { wv.vr = c1; wv.lo = 0; wv.hi = 0; }       // a prefix tile: the keys below the prefix length
@@ -1136,6 +1140,7 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
 #pragma unroll
         for (int i = 0; i < 8; ++i) exp_pair(0, i);
         __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int g = 0; g < 2 * NDB; ++g) {
           pv(0, g);
