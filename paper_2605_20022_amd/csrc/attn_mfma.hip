@@ -107,6 +107,7 @@ constexpr int MF_BLOCKS = MF_TK / 32;     // 32-key MFMA blocks per tile
 constexpr int MF_GROUPS = MF_TK / 16;     // 16-key load groups per tile
 constexpr int MF_XCD_TILT = 40;           // per mille of a share that every share of an odd XCD hands to the even XCD before it
 constexpr int MF_TILT_MIN_SHARE = 64;     // ... in launches whose shares are at least this many units long
+constexpr int MF_ALONE = 5;      // tiles up to which a piece has a compute unit to itself (find_piece)
 constexpr int MF_PIECE_SLACK = 2;         // tiles by which a piece (find_piece) may be longer than a share of the line
 constexpr float MF_LAZY = 6.f;            // the softmax reference follows the row maximum in steps of at least 2^6
 // What starting an item costs a work-group, in tile times: measured ≈ 6.9 µs (request the next piece's
@@ -430,7 +431,12 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
     count += Ii * ((Ti + cand - 1) / cand);
   }
   const unsigned long long fits = __ballot(count <= sc_.num_wgs);
-  const int size = s0 + (__ffsll((long long)fits) - 1) * step;
+  // One piece per compute unit where that takes at most MF_ALONE tiles each: pieces half as long on both work-groups of a CU
+  // begin, store and are merged twice as often.  us a call, two per CU -> one: 128 rows, 24 items of 34 tiles 18.3 -> 17.4 (a step
+  // of four layers 125 -> 116), 32 of 33 21.4 -> 18.9, 8 of 129 21.7 -> 18.8; 64 rows, 16 of 33 16.1 -> 14.2, 32 of 17
+  // 16.2 -> 13.8, 8 of 65 13.2 -> 12.1.  Longer ones are better cut: 24 items of 66 tiles, 4 tiles each 21.3, 8 each 22.4.
+  const unsigned long long alone = __ballot(cand <= MF_ALONE && count <= sc_.num_wgs / FD_WGS_PER_CU);
+  const int size = s0 + (__ffsll((long long)(alone ? alone : fits)) - 1) * step;
   const int line = max(sc_.min_share, (tiles_all + mf_start_cost(MAXRB) * items_all + sc_.num_wgs - 1) / sc_.num_wgs);
   if (fits == 0 || (!SINGLE && size > max(line + MF_PIECE_SLACK, sc_.min_piece))) return false;
   if (bad && threadIdx.x < 64) flag_status(p.status, bad);

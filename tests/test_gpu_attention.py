@@ -171,6 +171,9 @@ def test_combine_layouts(fd, D, B, Hkv, n, kv, chunk):
     (5, 64, 4, (500, 700)),            # 320 items of like length: s above a share, along the line
     (64, 8, 4, (1, 130)),              # 512 items in 64 sequences: one work-group each
     (65, 2, 4, (1, 130)),              # 65 sequences: along the line
+    (2, 8, 16, (2000, 2048)),          # 16 items of 33 tiles: pieces of three, one per compute unit
+    (4, 8, 32, (2000, 2048)),          # 32 items of 33 tiles of 128 rows: pieces of five, the longest that go alone
+    (4, 8, 32, (2600, 2700)),          # 43 tiles: six would be needed, two work-groups per compute unit
 ])
 def test_items_cut_piece_by_piece(fd, D, B, Hkv, n, kv):
     """Both cuts of the work at the sizes where the rule changes; planned and self-planning calls agree bit for bit."""
