@@ -189,11 +189,15 @@ __device__ __forceinline__ void unpack_f16x4(u32x2 w, float (&x)[4]) {
 // LDS, V 16 KB above K; NT: streaming.  As inline assembly, because after the builtin the compiler holds back every
 // transposing LDS read until the loads have landed, whichever part of LDS they write.  No register waits for
 // them: s_waitcnt vmcnt, then the barrier that hands the tile over.  m0, the LDS address, is put back.
+// A vector-memory instruction must not read a scalar register within five wait states of a vector instruction that wrote it, and
+// the hardware does not wait by itself.  The descriptors may come straight from v_readfirstlane or, where they were
+// spilled, v_readlane, and the compiler, which keeps that distance for its own loads, does not look in here: s_nop 4 keeps
+// it whatever precedes (and the wait state that a load to LDS needs after a write of m0).
 template <bool NT>
 __device__ __forceinline__ void load_group_to_lds(u32x4 rk, u32x4 rv, const unsigned (&k)[4], const unsigned (&v)[4], unsigned lds_byte) {
   unsigned keep;
 #define FD_LDS_LOADS(CACHE)                                                                                     \
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"                                           \
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 4\n\t"                                           \
                "buffer_load_dwordx4 %4, %2, 0 offen" CACHE " lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"    \
                "buffer_load_dwordx4 %5, %2, 0 offen" CACHE " lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"    \
                "buffer_load_dwordx4 %6, %2, 0 offen" CACHE " lds\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"    \

@@ -206,6 +206,27 @@ def test_128_row_tiles(fd, B, n, kv, page):
     _check(fd, inp, "bf16", f"{B} sequences, {n} rows, kv {kv}, page {page}")
 
 
+@pytest.mark.parametrize("B, Hkv, n, kv", [
+    (70, 8, 32, (300, 600)),     # 560 items for 512 work-groups: shares hold several pieces, and a tile serves one item
+    (70, 4, 40, (100, 400)),     # two row blocks a sequence: a tile serves two items
+    (45, 8, 20, (500, 700)),     # 360 items of like length: along the line because pieces would be longer
+])
+def test_128_row_tiles_planned_along_the_line(fd, B, Hkv, n, kv):
+    """A share of several pieces: the next piece's first tile lands while the finished piece's rows are stored."""
+    w = _wl("rows128", "bf16", B, 4 * Hkv, Hkv, 128, 16, kv, (5, 5), n - 5, seed=92)
+    inp = W.make_attention_inputs(w)
+    call = AttnCall(fd, inp)
+    out, lse = call.run()
+    ref, ref_lse = oracle_attention(inp)
+    assert_attn_close(out, ref, "bf16", f"line B={B} Hkv={Hkv} n={n}")
+    assert np.abs(lse - ref_lse).max() <= 2e-2
+    fd.fd_verify_draft_plan(call.args)
+    call.args.flags |= fd.FD_ATTN_PLANNED
+    call.out.fill_(float("nan"))
+    out2, lse2 = call.run()
+    assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
+
+
 @pytest.mark.parametrize("seed", range(12))
 def test_random_workloads(fd, seed):
     """Seeded random shapes through the MFMA path: batch, head grouping, page size, ragged prefixes
