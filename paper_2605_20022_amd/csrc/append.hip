@@ -1,9 +1,9 @@
 // Commit of verified rows to the paged KV cache (Sec. 4.3, decoupled execution: the cache
 // written by target verification is what the next draft step reuses).
 //
-// One work-group per sequence, one launch: the work-group reads the sequence's length once, copies
+// One work-group per sequence, one launch: every wave reads the sequence's length, the work-group copies
 // new rows 0 .. accept_len (K and V, all KV heads, 16-byte accesses) to logical positions
-// kv_len + j, and writes the new length last -- so the output array may be the input array.  Only
+// kv_len + j, and, past a barrier, writes the new length last -- so the output array may be the input array.  Only
 // verify rows are ever written: mask tokens stay invisible to the clean prefix (Sec. 4.1), so a
 // sequence without verify rows commits nothing and accept_len is held below the number of verify rows.
 #include "fd_common.h"
@@ -45,8 +45,9 @@ __global__ __launch_bounds__(256) void append_kv_kernel(AttnParams p, T* __restr
       *reinterpret_cast<u32x4*>((is_v ? vc : kc) + (long long)h * p.sh + e) = val;
     }
   }
-  // every thread has read what it needs of this sequence's old length by now (s is in registers);
-  // no other work-group reads kv_len[seq]
+  // The output may be the input array, and each of the four waves reads the old length for itself: the new one waits until
+  // all of them have used it.  No other work-group reads kv_len[seq].
+  __syncthreads();
   if (threadIdx.x == 0) kv_len_out[seq] = s.L + rows;
 }
 

@@ -75,3 +75,16 @@ def test_memory_instructions_keep_their_distance_to_vector_written_scalars(kerne
     assert any(" lds" in ins for name, code in kernels.items() if "attn_mfma_kernel" in name for ins in code)
     bad = {name: ins for name, code in kernels.items() for ins in [_early_scalar_reads(code)] if ins}
     assert not bad, bad
+
+
+def test_new_length_is_stored_past_a_barrier(kernels):
+    """fd_append_kv in place: every wave reads the old length before any wave may store the new one."""
+    found = [code for name, code in kernels.items() if "append_kv_kernel" in name]
+    assert len(found) == 2                                   # one per data type
+    for code in found:
+        store = [i for i, ins in enumerate(code) if re.match(r"global_store_dword ", ins)]          # (cache rows are dwordx4)
+        assert len(store) == 1
+        barrier = [i for i, ins in enumerate(code) if ins.startswith("s_barrier")]
+        assert barrier and barrier[0] < store[0]
+        copies = [i for i, ins in enumerate(code) if ins.startswith("global_store_dwordx4")]
+        assert copies and max(copies) < barrier[0]
