@@ -243,11 +243,18 @@ __device__ __forceinline__ long long uniform_ll(long long v) {
   return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) { int o = __shfl_up(v, off); if (lane >= off) v += o; }
+// Inclusive scan over the wave, all lanes active.  By the register file's own lane shifts: planning consists of little else, and six trips
+// through LDS (__shfl_up) are six latencies of LDS.
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // from the lane 1, 2, 4, 8 below in the row of sixteen
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // rows 1 and 3: the last lane of the row below
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // rows 2 and 3: lane 31
   return v;
 }
+__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_incl_scan(v), 63); }
 
 // Where work-group w's share of the line starts.  Every thread of the work-group calls this; the
 // results are uniform.  Tile counts fit 32 bits (the host checks the bound), so no 64-bit division
@@ -315,7 +322,7 @@ __device__ __forceinline__ bool find_share(const AttnParams& p, const MfmaSched&
       int T_, I_; seq_shape(p, s_mine, ROWS_WG, T_, I_);
       vt = item_units(T_, MF_START_COST) * I_;
     }
-    const int it = wave_incl_scan(vt, lane);
+    const int it = wave_incl_scan(vt);
     if (lane == 63) sh_w[wave] = it;
     if (tid == 0) sh_found[0] = -1;
     __syncthreads();
@@ -354,7 +361,7 @@ __device__ __forceinline__ bool find_share(const AttnParams& p, const MfmaSched&
       int T_, I_; seq_shape(p, s, ROWS_WG, T_, I_);
       part += item_units(T_, MF_START_COST) * I_;
     }
-    part = wave_incl_scan(part, lane);
+    part = wave_incl_scan(part);
     if (lane == 63) sh_w[wave] = part;
     __syncthreads();
 #pragma unroll
@@ -373,7 +380,7 @@ __device__ __forceinline__ bool find_share(const AttnParams& p, const MfmaSched&
       int T_ = 0, I_ = 0;
       if (i < p.B) { SeqInfo s = load_seq_t<false>(p, i); seq_shape(p, s, ROWS_WG, T_, I_); }
       const int vt = item_units(T_, MF_START_COST) * I_;
-      const int it = wave_incl_scan(vt, lane);
+      const int it = wave_incl_scan(vt);
       if (lane == 63) sh_w[wave] = it;
       __syncthreads();
       unsigned wt = 0, bt = 0;
@@ -409,7 +416,7 @@ __device__ __forceinline__ bool find_share(const AttnParams& p, const MfmaSched&
 // without the line: no walk over items and no second piece, a third of the instructions and no spilled scalars
 // (16 of 512..4096 keys 39.7 -> 37.9, 1 of 2048 14.6 -> 13.2, 4 of 32768 112.7 -> 109.4).
 // Pieces are numbered (sequence, head, piece, row block): the row blocks that read the same tiles are neighbours.
-// Every wave works this out by itself (lane i holds sequence i, then candidate i for s): no LDS, no barrier.
+// Every wave works this out by itself (lane i holds sequence i): no LDS, no barrier.
 // Returns false if the call is to be cut along the line; has_piece: this work-group has one.
 struct PieceShare { int w, seq, W_eff, pieces, head, rt, tile0, nt; };
 template <int MAXRB, bool SINGLE>
@@ -422,30 +429,35 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
     s = load_seq_t<false>(p, lane, &bad);
     seq_shape(p, s, ROWS_WG, T, I);
   }
-  const int tiles_all = __builtin_amdgcn_readlane(wave_incl_scan(T * I, lane), 63);
-  const int items_all = __builtin_amdgcn_readlane(wave_incl_scan(I, lane), 63);
+  const int tiles_all = wave_total(T * I), items_all = wave_total(I);
   if (tiles_all == 0) { ps.W_eff = 0; if (bad && threadIdx.x < 64) flag_status(p.status, bad); return true; }
-  // candidate sizes s0 + lane: how many pieces each gives
   const int s0 = max(sc_.min_piece, (tiles_all + sc_.num_wgs - 1) / sc_.num_wgs);
-  const int step = s0 / 63 + 1;                                    // (up to 2 s0: enough while items <= num_wgs / 2)
-  const int cand = s0 + lane * step;
-  int count = 0;
-  for (int i = 0; i < p.B; ++i) {
-    const int Ti = __builtin_amdgcn_readlane(T, i), Ii = __builtin_amdgcn_readlane(I, i);
-    count += Ii * ((Ti + cand - 1) / cand);
-  }
-  const unsigned long long fits = __ballot(count <= sc_.num_wgs);
+  const int line = max(sc_.min_share, (tiles_all + mf_start_cost(MAXRB) * items_all + sc_.num_wgs - 1) / sc_.num_wgs);
+  const int longest = max(line + MF_PIECE_SLACK, sc_.min_piece);   // size up to which pieces are cut (!SINGLE)
+  auto pieces_at = [&](int c) { return wave_total(I * (int)((unsigned)(T + c - 1) / (unsigned)c)); };
+  int size = 0;
   // One piece per compute unit where that takes at most MF_ALONE tiles each: pieces half as long on both work-groups of a CU
   // begin, store and are merged twice as often.  us a call, two per CU -> one: 128 rows, 24 items of 34 tiles 18.3 -> 17.4 (a step
   // of four layers 125 -> 116), 32 of 33 21.4 -> 18.9, 8 of 129 21.7 -> 18.8; 64 rows, 16 of 33 16.1 -> 14.2, 32 of 17
   // 16.2 -> 13.8, 8 of 65 13.2 -> 12.1.  Longer ones are better cut: 24 items of 66 tiles, 4 tiles each 21.3, 8 each 22.4.
-  const unsigned long long alone = __ballot(cand <= MF_ALONE && count <= sc_.num_wgs / FD_WGS_PER_CU);
-  const int size = s0 + (__ffsll((long long)(alone ? alone : fits)) - 1) * step;
-  const int line = max(sc_.min_share, (tiles_all + mf_start_cost(MAXRB) * items_all + sc_.num_wgs - 1) / sc_.num_wgs);
-  if (fits == 0 || (!SINGLE && size > max(line + MF_PIECE_SLACK, sc_.min_piece))) return false;
+  for (int c = s0; c <= MF_ALONE && size == 0; ++c) if (pieces_at(c) <= sc_.num_wgs / FD_WGS_PER_CU) size = c;
+  if (size == 0) {
+    // The smallest of the sizes s0 + i step that fits the launch: the larger, the fewer pieces.  Six sums over the sequences at
+    // most; every size tried against every sequence took a call that plans for itself 7 us at 64 sequences (48 sequences of
+    // 1000..3000 keys, cut along the line in the end: 88.7 -> 83.3 us; 64 of 900..1000 in pieces: 58.0 -> 52.6).
+    const int step = s0 / 63 + 1;
+    int lo = 0, hi = SINGLE ? (s0 + step - 1) / step : min(63, (longest - s0) / step);      // (2 s0 fits while items <= num_wgs / 2)
+    if (pieces_at(s0 + hi * step) > sc_.num_wgs) return false;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (pieces_at(s0 + mid * step) <= sc_.num_wgs) hi = mid; else lo = mid + 1;
+    }
+    size = s0 + hi * step;
+  }
+  if (!SINGLE && size > longest) return false;
   if (bad && threadIdx.x < 64) flag_status(p.status, bad);
   const int S = (T + size - 1) / size, n = I * S;
-  const int hi = wave_incl_scan(n, lane), lo = hi - n;
+  const int hi = wave_incl_scan(n), lo = hi - n;
   ps.W_eff = __builtin_amdgcn_readlane(hi, 63);
   const int chunk = (ps.W_eff + sc_.xcds - 1) / sc_.xcds;          // (the same assignment of shares to XCDs as on the line)
   ps.w = pw / sc_.xcds < chunk ? (pw % sc_.xcds) * chunk + pw / sc_.xcds : ps.W_eff;

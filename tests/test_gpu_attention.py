@@ -191,6 +191,29 @@ def test_items_cut_piece_by_piece(fd, D, B, Hkv, n, kv):
     assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
 
 
+@pytest.mark.parametrize("B,Hkv,n,kv", [
+    (33, 8, 4, (900, 1000)),           # 264 items of sixteen tiles: pieces would be longer than a share by more than the slack
+    (48, 8, 4, (0, 2000)),             # ragged, along the line
+    (64, 8, 4, (440, 448)),            # as many items as work-groups, whole ones
+    (63, 2, 40, (0, 500)),             # two row blocks, the sizes tried up to the slack
+    (20, 8, 4, (100, 3000)),           # always pieces, the size found among many
+])
+def test_piece_size_is_found_among_many_sequences(fd, B, Hkv, n, kv):
+    """The search for the piece size, sequences without rows among them: planned and self-planning calls agree bit for bit."""
+    w = _wl("search", "bf16", B, 4 * Hkv, Hkv, 128, 16, kv, (0, n), 0, seed=270 + B)
+    inp = W.make_attention_inputs(w)
+    call = AttnCall(fd, inp)
+    out, lse = call.run()
+    ref, ref_lse = oracle_attention(inp)
+    assert_attn_close(out, ref, "bf16", f"search B={B} Hkv={Hkv} n={n}")
+    assert np.abs(lse - ref_lse).max() <= 2e-2
+    fd.fd_verify_draft_plan(call.args)
+    call.args.flags |= fd.FD_ATTN_PLANNED
+    call.out.fill_(float("nan"))
+    out2, lse2 = call.run()
+    assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
+
+
 @pytest.mark.parametrize("n, kv, page", [
     (17, (0, 1), 16),        # 68 rows: the last wave has none, empty and one-key prefixes
     (32, (63, 65), 16),      # 128 rows, one key either side of a tile
