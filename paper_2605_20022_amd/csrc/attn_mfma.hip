@@ -459,8 +459,29 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
   const int S = (T + size - 1) / size, n = I * S;
   const int hi = wave_incl_scan(n), lo = hi - n;
   ps.W_eff = __builtin_amdgcn_readlane(hi, 63);
-  const int chunk = (ps.W_eff + sc_.xcds - 1) / sc_.xcds;          // (the same assignment of shares to XCDs as on the line)
+  // Which piece a work-group takes: neighbours on one XCD, as on the line, unless that leaves an XCD more than a quarter above the
+  // average.  One work-group holds one piece however short it is, so where one sequence is much longer than the
+  // others half of the XCDs had nothing but its pieces and the other half next to nothing to do; in turn, every
+  // compute unit gets some of both.  us a call, in runs / in turn: 31 sequences of 256 keys and one of 32768, 16 rows 56.0 / 48.6 (line:
+  // 50), 24 of 1000 and eight of 16384 129.8 / 110, 28 of 300 and four of 8192 49.0 / 43.5.  Even batches stay in runs (one sequence of
+  // 2048 keys: 11.5 / 12.5, the combine kernel finds a head's partial rows on its own XCD), and so do calls with several row blocks, which
+  // read the same tiles.
+  const int chunk = (ps.W_eff + sc_.xcds - 1) / sc_.xcds;
   ps.w = pw / sc_.xcds < chunk ? (pw % sc_.xcds) * chunk + pw / sc_.xcds : ps.W_eff;
+  if (!sc_.reuse && 4ll * tiles_all < 3ll * ps.W_eff * size) {     // (many pieces are far shorter than the longest)
+    const float mean = S > 0 ? (float)T / (float)S : 0.f;          // tiles of a piece of this lane's sequence
+    const float before = (float)(wave_incl_scan(T * I) - T * I);   // tiles before the sequence
+    float most = 0.f, upto = 0.f;
+    for (int x = 1; x <= sc_.xcds; ++x) {
+      const int last = min(x * chunk, ps.W_eff) - 1;               // the XCD's last piece
+      const int q = __ffsll((long long)__ballot(lo <= last && last < hi)) - 1;
+      if (q < 0) break;                                            // cannot happen
+      const float here = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(before + (float)(last + 1 - lo) * mean), q));
+      most = fmaxf(most, here - upto);
+      upto = here;
+    }
+    if (most * (float)sc_.xcds > 1.25f * (float)tiles_all) ps.w = pw;
+  }
   if (ps.w >= ps.W_eff) return true;
   const int at = __ffsll((long long)__ballot(lo <= ps.w && ps.w < hi)) - 1;
   if (at < 0) return true;                                         // cannot happen

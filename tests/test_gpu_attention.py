@@ -214,6 +214,31 @@ def test_piece_size_is_found_among_many_sequences(fd, B, Hkv, n, kv):
     assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
 
 
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("lens,Hkv,n", [
+    ([100] * 31 + [5000], 8, 4),       # one long sequence at the end, 64-row items
+    ([5000] + [100] * 31, 8, 32),      # at the beginning, 128 rows
+    ([40] * 40 + [900], 8, 4),         # 328 items: pieces only up to the slack
+    ([30, 3000, 30], 1, 4),            # fewer pieces than XCDs share evenly
+    ([0] * 20 + [4000, 0, 4000], 4, 33),     # several row blocks read the same tiles: neighbours stay together
+])
+def test_one_sequence_much_longer_than_the_others(fd, lens, Hkv, n, D):
+    """Pieces of very unequal lengths are dealt out to the work-groups in turn; planned and self-planning calls agree bit for bit."""
+    w = _wl("uneven", "bf16", len(lens), 4 * Hkv, Hkv, D, 16, (max(lens), max(lens)), (n, n), 0, seed=290 + n)
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array(lens, dtype=np.int32)                 # (the page lists are long enough for all of them)
+    call = AttnCall(fd, inp)
+    out, lse = call.run()
+    ref, ref_lse = oracle_attention(inp)
+    assert_attn_close(out, ref, "bf16", f"uneven {lens[:2]}.. Hkv={Hkv} n={n} D={D}")
+    assert np.abs(lse - ref_lse).max() <= 2e-2
+    fd.fd_verify_draft_plan(call.args)
+    call.args.flags |= fd.FD_ATTN_PLANNED
+    call.out.fill_(float("nan"))
+    out2, lse2 = call.run()
+    assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
+
+
 @pytest.mark.parametrize("n, kv, page", [
     (17, (0, 1), 16),        # 68 rows: the last wave has none, empty and one-key prefixes
     (32, (63, 65), 16),      # 128 rows, one key either side of a tile
