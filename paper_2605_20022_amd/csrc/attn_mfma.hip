@@ -554,10 +554,12 @@ __global__ __launch_bounds__(MF_BLOCK) void attn_mfma_plan_kernel(AttnParams p, 
 // Streaming kernel.  MAXRB: 32-row blocks a work-group can own (2: up to 64 tile rows, 4: up to 128).
 // PLANNED: the share comes from the plan entry the planning kernel left, else it is found here.
 // DH: head dim (128 or 64).
-// SINGLE: the call is cut piece by piece (MfmaSched::by_piece == 2): no line, no second piece.
-template <int MAXRB, bool PLANNED, int DH, bool SINGLE>
+// CUT: MfmaSched::by_piece.  2: piece by piece, no line and no second piece.  0: along the line, without the few scalars more that
+// a choice between both costs (the scalars of this variant spill; 100 sequences of 512..2048 keys at head dim 64: 67.7 -> 66.4 us).
+template <int MAXRB, bool PLANNED, int DH, int CUT>
 __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, MfmaSched sc_) {
   constexpr int ROWS_WG = 32 * MAXRB;
+  constexpr bool SINGLE = CUT == 2;
   constexpr int MF_D = DH;
   constexpr int MF_KSTR = MfLds<DH>::KSTR, MF_VSTR = MfLds<DH>::VSTR;
   constexpr int MF_K_ELEMS = MfLds<DH>::K_ELEMS, MF_BUF_ELEMS = MfLds<DH>::BUF_ELEMS;
@@ -596,23 +598,23 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
     sh_q = (unsigned)sload(pe, 12); sh_r = (unsigned)sload(pe, 13); W_eff = sload(pe, 14); w = sload(pe, 15);
 #pragma unroll
     for (int j = 0; j < MF_GROUPS; ++j) { nid0[j] = sload(pe, 16 + j); nid1[j] = sload(pe, 20 + j); }
-    ps.pieces = sload(pe, 24); ps.head = sload(pe, 25); ps.rt = sload(pe, 26); ps.tile0 = sload(pe, 27); ps.nt = sload(pe, 28);
+    if (CUT) { ps.pieces = sload(pe, 24); ps.head = sload(pe, 25); ps.rt = sload(pe, 26); ps.tile0 = sload(pe, 27); ps.nt = sload(pe, 28); }
     // The plan is trusted to describe these arguments.  The checks below only keep a stale or foreign
     // plan from sending an access outside the caller's buffers (its results are then meaningless).
     W_eff = clampi(W_eff, 0, sc_.num_wgs);
     if (pw == 0 && tid == 0 && !sc_.by_item) sc_.entries[sc_.num_wgs] = make_int4(W_eff, 0, 0, 0);       // for the combine kernel
     if (seq < 0 || seq >= p.B || W_eff < 1 || w < 0 || w >= W_eff || g1 <= g0 || Pt > g0 || sh_q == 0) return;
     clamp_seq(p, ws);
-    if (!sc_.by_piece || ps.pieces < 0) ps.pieces = 0;
+    if (!CUT || ps.pieces < 0) ps.pieces = 0;
     if (SINGLE && ps.pieces == 0) return;        // (not this call's plan)
   } else {
     bool has = false;
-    if (SINGLE || sc_.by_piece) {
+    if (CUT) {
       if (find_piece<MAXRB, SINGLE>(p, sc_, pw, ps, ws, has)) { if (!has) return; }
       else ps.pieces = 0;
     }
     if (SINGLE && !has) return;
-    if (SINGLE || has) {
+    if (SINGLE || (CUT && has)) {
       w = ps.w; seq = ps.seq; W_eff = ps.W_eff;
       Pt = g0 = 0; g1 = sh_q = 1; sh_r = 0;      // (not read)
     } else {
@@ -877,7 +879,7 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
 
   bool first_piece = true;
   Piece cur;
-  if (SINGLE || ps.pieces > 0) {
+  if (SINGLE || (CUT && ps.pieces > 0)) {
     // one piece of an item cut by find_piece (clamped again: a plan entry is not trusted with an access)
     if (T <= 0) return;
     cur.s = ws; cur.seq = seq; cur.T = T;
@@ -918,7 +920,7 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
       // units has nothing before the item's first tile), else 2 wf + 1; later pieces are in slots 2 w'.
       // Cut piece by piece, piece j is in slot 2 (w - (pieces - 1 - j) row blocks).
       int first_slot, step = 1;
-      if (SINGLE || ps.pieces > 0) {
+      if (SINGLE || (CUT && ps.pieces > 0)) {
         step = I / p.Hkv;
         first_slot = 2 * max(0, w - (ps.pieces - 1) * step);
       } else {
@@ -1551,14 +1553,14 @@ static void fill_sched(const AttnParams& p, void* workspace, int kv_chunk, MfmaS
 }
 
 // The streaming kernel's LDS request is above the default limit: raised once per device.
-template <int MAXRB, bool PLANNED, int DH, bool SINGLE>
+template <int MAXRB, bool PLANNED, int DH, int CUT>
 static hipError_t configure_mfma() {
   static std::atomic<unsigned long long> done{0};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 64 && (done.load(std::memory_order_acquire) >> dev & 1ull)) return hipSuccess;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_mfma_kernel<MAXRB, PLANNED, DH, SINGLE>),
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_mfma_kernel<MAXRB, PLANNED, DH, CUT>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)MfTileLds<MAXRB, DH>::BYTES);
   if (e == hipSuccess && dev < 64) done.fetch_or(1ull << dev, std::memory_order_release);
   return e;
@@ -1574,17 +1576,22 @@ hipError_t run_attn_mfma_plan(const AttnParams& p, void* workspace, int kv_chunk
   return hipGetLastError();
 }
 
-template <int MAXRB, bool PLANNED, int DH, bool SINGLE>
-static hipError_t launch_mfma_d(const AttnParams& p, const MfmaSched& sc, hipStream_t st) {
-  hipError_t e = configure_mfma<MAXRB, PLANNED, DH, SINGLE>();
+template <int MAXRB, bool PLANNED, int DH, int CUT>
+static hipError_t launch_mfma_c(const AttnParams& p, const MfmaSched& sc, hipStream_t st) {
+  hipError_t e = configure_mfma<MAXRB, PLANNED, DH, CUT>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_mfma_kernel<MAXRB, PLANNED, DH, SINGLE>), dim3(sc.num_wgs), dim3(MF_BLOCK), (MfTileLds<MAXRB, DH>::BYTES), st, p, sc);
+  hipLaunchKernelGGL((attn_mfma_kernel<MAXRB, PLANNED, DH, CUT>), dim3(sc.num_wgs), dim3(MF_BLOCK), (MfTileLds<MAXRB, DH>::BYTES), st, p, sc);
   return hipGetLastError();
+}
+template <int MAXRB, bool PLANNED, int DH>
+static hipError_t launch_mfma_d(const AttnParams& p, const MfmaSched& sc, hipStream_t st) {
+  if (sc.by_piece == 2) return launch_mfma_c<MAXRB, PLANNED, DH, 2>(p, sc, st);
+  return sc.by_piece ? launch_mfma_c<MAXRB, PLANNED, DH, 1>(p, sc, st) : launch_mfma_c<MAXRB, PLANNED, DH, 0>(p, sc, st);
 }
 template <int MAXRB, bool PLANNED>
 static hipError_t launch_mfma(const AttnParams& p, const MfmaSched& sc, hipStream_t st) {
-  if (p.D == 64) return sc.by_piece == 2 ? launch_mfma_d<MAXRB, PLANNED, 64, true>(p, sc, st) : launch_mfma_d<MAXRB, PLANNED, 64, false>(p, sc, st);
-  if (p.D == 128) return sc.by_piece == 2 ? launch_mfma_d<MAXRB, PLANNED, 128, true>(p, sc, st) : launch_mfma_d<MAXRB, PLANNED, 128, false>(p, sc, st);
+  if (p.D == 64) return launch_mfma_d<MAXRB, PLANNED, 64>(p, sc, st);
+  if (p.D == 128) return launch_mfma_d<MAXRB, PLANNED, 128>(p, sc, st);
   return hipErrorInvalidValue;                  // (attn_mfma_supports keeps other head dims away)
 }
 
