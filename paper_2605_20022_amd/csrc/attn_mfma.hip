@@ -135,6 +135,7 @@ struct MfmaSched {
   float* part_ml;             // [2 * num_wgs][ROWS_WG][4]: running maximum (base 2), row sum, that largest magnitude, unused
   int rt_max;         // row blocks of the largest sequence
   int by_item;        // != 0: the combine entries are indexed by item, else by share
+  int rows_first;     // != 0: the combine kernel's grid runs over the row blocks of an item first
   // Combine entries [num_wgs + 1].
   //   by share  entry w: the split item that ends in the work-group of share w: (first packed row, head | row block << 16,
   //             tile rows, first slot); first < 0: none.  Entry num_wgs: (shares in use, -, -, -)
@@ -1369,7 +1370,10 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
 // The pieces of an item sit in its first slot, then in the first slot (2w) of every later (cut piece by
 // piece: every step-th later) work-group up to the one it ended in.  Sixteen lanes per tile row, a lane owns eight adjacent
 // output columns; PG sixteen-lane groups share a row and take every PG-th piece.
-//   grid (items or shares, ROWS_WG PG / 16)
+//   grid (items or shares, ROWS_WG PG / 16), with rows_first the other way round: an item's row blocks then lie on different
+//   XCDs.  In a grid of 256 items they lie 256 blocks apart, on the same compute unit: with eight long items of some 40 pieces among 248
+//   short ones 12.4 us, the other way round 7.2 (head dim 64 15.2 and 7.1).  With fewer items it makes no difference, but for
+//   eight in all (3.8 us as it is, 4.4 the other way round), and more of them are worse off (360 along the line 5.1 and 6.6).
 // A block that finds nothing to merge costs as much as its launch, and the kernel follows another one on
 // the stream: with few items (entries by item) the grid holds one group of blocks per item that can
 // exist instead of one per share (8 items in a 512-share launch: call 17.9 -> 15.9 us; 24 items of 128 rows: 35.4 -> 33.3).
@@ -1381,12 +1385,14 @@ __global__ __launch_bounds__(256) void attn_mfma_combine_kernel(AttnParams p, Mf
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15;
   const int pg = PG == 1 ? 0 : lane >> 4;                      // piece group
-  const int4* ep4 = sc_.entries + blockIdx.x;
+  const bool rows_first = PG == 1 && sc_.rows_first;
+  const int entry = rows_first ? blockIdx.y : blockIdx.x, row_block = rows_first ? blockIdx.x : blockIdx.y;
+  const int4* ep4 = sc_.entries + entry;
   const int* ep = reinterpret_cast<const int*>(ep4);
   int row0, head, rt, rows_here, first_slot, wl, step = 1;     // step: shares from a piece to the next
   if (sc_.by_item) {
-    const int sh = blockIdx.x / sc_.rt_max, seq = sh / p.Hkv;
-    rt = blockIdx.x - sh * sc_.rt_max; head = sh - seq * p.Hkv;
+    const int sh = entry / sc_.rt_max, seq = sh / p.Hkv;
+    rt = entry - sh * sc_.rt_max; head = sh - seq * p.Hkv;
     first_slot = sload(ep, 0); wl = sload(ep, 1); step = max(1, sload(ep, 2));
     const int r0 = sload(p.row_indptr, seq), r1 = sload(p.row_indptr, seq + 1);          // (clamped as load_seq does)
     row0 = clampi(r0, 0, p.total_rows);
@@ -1394,14 +1400,14 @@ __global__ __launch_bounds__(256) void attn_mfma_combine_kernel(AttnParams p, Mf
     rows_here = min(ROWS_WG, n * p.G - rt * ROWS_WG);          // <= 0: the sequence has no such row block, nobody wrote the entry
     if (rows_here <= 0 || first_slot < 0 || wl >= sc_.num_wgs) return;
   } else {
-    wl = blockIdx.x;                                           // the share in which the item ended
+    wl = entry;                                                // the share in which the item ended
     const int shares = sload(reinterpret_cast<const int*>(sc_.entries + sc_.num_wgs), 0);     // entries beyond are nobody's
     row0 = sload(ep, 0); const int head_rt = sload(ep, 1); rows_here = sload(ep, 2); first_slot = sload(ep, 3);
     if (wl >= shares || row0 < 0) return;
     head = head_rt & 0xffff; rt = head_rt >> 16;
     if (rows_here > ROWS_WG || first_slot < 0 || head >= p.Hkv) return;
   }
-  const int trow = PG == 1 ? blockIdx.y * 16 + wave * 4 + (lane >> 4) : blockIdx.y * 4 + wave;
+  const int trow = PG == 1 ? row_block * 16 + wave * 4 + (lane >> 4) : row_block * 4 + wave;
   const int wf = first_slot >> 1;
   if (wf >= wl) return;
   if (trow >= rows_here || l16 >= MF_D / 8) return;           // (head dim 64: half of the lanes have no column)
@@ -1538,6 +1544,7 @@ static void fill_sched(const AttnParams& p, void* workspace, int kv_chunk, MfmaS
   sc.reuse = (long long)p.max_new_rows * p.G > rows_wg ? 1 : 0;
   sc.rt_max = (int)(((long long)p.max_new_rows * p.G + rows_wg - 1) / rows_wg);
   sc.by_item = (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs ? 1 : 0;
+  sc.rows_first = (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs / 2 ? 1 : 0;
   sc.by_piece = sc.by_item && p.B <= 64 && sc.fixed_share == 0 ? 1 : 0;
   if (sc.by_piece && (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs / 2) sc.by_piece = 2;
   // Pieces of one tile only where an item has at most eight (one pass of the combine kernel): 1 x 300 keys 11.8 -> 10.7 us;
@@ -1605,7 +1612,8 @@ hipError_t run_attn_mfma(const AttnParams& p, void* workspace, int kv_chunk, boo
 
 template <int MAXRB, int PG>
 static void launch_combine(const AttnParams& p, const MfmaSched& sc, int items, hipStream_t st) {
-  const dim3 grid(sc.by_item ? items : sc.num_wgs, 32 * MAXRB * PG / 16);
+  const int row_blocks = 32 * MAXRB * PG / 16;
+  const dim3 grid = PG == 1 && sc.rows_first ? dim3(row_blocks, items) : dim3(sc.by_item ? items : sc.num_wgs, row_blocks);
   if (p.D == 64) hipLaunchKernelGGL((attn_mfma_combine_kernel<MAXRB, 64, PG>), grid, dim3(256), 0, st, p, sc);
   else hipLaunchKernelGGL((attn_mfma_combine_kernel<MAXRB, 128, PG>), grid, dim3(256), 0, st, p, sc);
 }
