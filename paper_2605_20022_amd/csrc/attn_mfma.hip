@@ -129,7 +129,7 @@ struct MfmaSched {
   int reuse;          // != 0: some sequence has several row blocks, i.e. its K/V tiles are read by several items
   int min_share;      // automatic shares are never smaller than this many tiles
   int fixed_share;    // > 0: tiles per work-group asked for by the caller
-  int by_piece;       // 1: items may be cut one by one (find_piece), at most 64 sequences and num_wgs items; 2: they always are
+  int by_piece;       // 1: items may be cut one by one (find_piece), at most 64 sequences and num_wgs items; 2: they always are (fill_sched)
   int min_piece;      // ... into pieces of at least this many tiles
   unsigned short* part_acc;   // [2 * num_wgs][ROWS_WG][D] fp16: the un-normalised output row divided by its largest magnitude
   float* part_ml;             // [2 * num_wgs][ROWS_WG][4]: running maximum (base 2), row sum, that largest magnitude, unused
@@ -413,7 +413,7 @@ __device__ __forceinline__ bool find_share(const AttnParams& p, const MfmaSched&
 // with 36 rows 75 -> 69.8; 16 of 512..4096 keys: equal.  The line is better where s comes out longer than its shares (400 items
 // for 512 work-groups are whole items here, 4/5 of one there): of more than num_wgs / 2 items, pieces are cut only if
 // s is at most MF_PIECE_SLACK tiles above a share (64-row items of 1000..3000 keys, 320 of them: s is 8 above, 62.7 -> 66.6).
-// Up to num_wgs / 2 items (the host's bound) they always are, at most 2 s0 long, and the streaming kernel is the variant
+// Up to num_wgs / 2 items (the host's bound; fill_sched has the exception) they always are, at most 2 s0 long, and the streaming kernel is the variant
 // without the line: no walk over items and no second piece, a third of the instructions and no spilled scalars
 // (16 of 512..4096 keys 39.7 -> 37.9, 1 of 2048 14.6 -> 13.2, 4 of 32768 112.7 -> 109.4).
 // Pieces are numbered (sequence, head, piece, row block): the row blocks that read the same tiles are neighbours.
@@ -434,7 +434,10 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
   if (tiles_all == 0) { ps.W_eff = 0; if (bad && threadIdx.x < 64) flag_status(p.status, bad); return true; }
   const int s0 = max(sc_.min_piece, (tiles_all + sc_.num_wgs - 1) / sc_.num_wgs);
   const int line = max(sc_.min_share, (tiles_all + mf_start_cost(MAXRB) * items_all + sc_.num_wgs - 1) / sc_.num_wgs);
-  const int longest = max(line + MF_PIECE_SLACK, sc_.min_piece);   // size up to which pieces are cut (!SINGLE)
+  // size up to which pieces are cut (!SINGLE); up to num_wgs / 2 items: a quarter above a share, head dim 64, where a work-group alone on
+  // its compute unit gains less, a sixteenth (fill_sched)
+  const int slack = 2 * items_all <= sc_.num_wgs ? max(MF_PIECE_SLACK, line / (p.D == 64 ? 16 : 4)) : MF_PIECE_SLACK;
+  const int longest = max(line + slack, sc_.min_piece);
   auto pieces_at = [&](int c) { return wave_total(I * (int)((unsigned)(T + c - 1) / (unsigned)c)); };
   int size = 0;
   // One piece per compute unit where that takes at most MF_ALONE tiles each: pieces half as long on both work-groups of a CU
@@ -1546,7 +1549,15 @@ static void fill_sched(const AttnParams& p, void* workspace, int kv_chunk, MfmaS
   sc.by_item = (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs ? 1 : 0;
   sc.rows_first = (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs / 2 ? 1 : 0;
   sc.by_piece = sc.by_item && p.B <= 64 && sc.fixed_share == 0 ? 1 : 0;
-  if (sc.by_piece && (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs / 2) sc.by_piece = 2;
+  const long long items_max = (long long)p.B * p.Hkv * sc.rt_max;
+  if (sc.by_piece && items_max <= sc.num_wgs / 2) sc.by_piece = 2;
+  // With close to num_wgs / 2 items and one piece per work-group, an item has hardly more than one piece or two: where lengths differ, the
+  // longest piece is far above the average, which long prefixes show.  The device decides there.  us a call, always pieces / the
+  // device decides / always the line: 32 sequences of 4000..32000 keys, 16 rows 417 / 387 / 388 (head dim 64: 238 / 219 / 216),
+  // 31 of 4000 and one of 16000 112 / 107 / 109 (75 / 62 / 60), 30 of 4096..16384 226 / 211 / 213; 32 of 8192 178 / 180 / 190
+  // (97 / 102 / 106).  Up to 64 tiles, and at head dim 128 with 128 rows, pieces lose little: 31 of 1000 and one of 4000
+  // 38.5 / - / 39.8 (26.2 / 30.0 / 29.4).  29 sequences (232 items) 368 / 362 / 357, but (60.0 / 63.6 / 60.8) of 1024..8192.
+  if (sc.by_piece == 2 && (rows_wg == 64 || p.D == 64) && 32 * items_max >= 15ll * sc.num_wgs && p.max_kv_len > 64 * MF_TK) sc.by_piece = 1;
   // Pieces of one tile only where an item has at most eight (one pass of the combine kernel): 1 x 300 keys 11.8 -> 10.7 us;
   // 1 x 2048 keys, 33 tiles: 14.6 us in twos, 16.0 one by one, 15.6 in threes.
   sc.min_piece = p.max_kv_len <= 7 * MF_TK && p.max_new_rows <= MF_TK ? 1 : 2;

@@ -239,6 +239,31 @@ def test_one_sequence_much_longer_than_the_others(fd, lens, Hkv, n, D):
     assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
 
 
+@pytest.mark.parametrize("D,lens,Hkv,n,what", [
+    (64, [2000, 2000, 2000, 4200], 64, 4, "256 items, the line"),
+    (64, [2000, 4200, 2000, 2000], 64, 65, "128-row items, the line"),
+    (64, [4200] * 4, 64, 4, "pieces"),
+    (128, [2000, 4200, 2000, 2000], 64, 4, "the line"),
+    (128, [4097, 4000, 4000, 3900], 60, 4, "240 items, pieces"),
+    (128, [4096, 100, 100, 100], 60, 4, "64 tiles: always pieces"),
+])
+def test_long_batches_of_nearly_one_item_per_compute_unit(fd, D, lens, Hkv, n, what):
+    """From 15/16 as many items as half of the work-groups on, prefixes above 4096 keys: the device decides."""
+    w = _wl("near", "bf16", len(lens), Hkv, Hkv, D, 16, (max(lens), max(lens)), (n, n), 0, seed=310 + n)
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array(lens, dtype=np.int32)                 # (the page lists are long enough for all of them)
+    call = AttnCall(fd, inp)
+    out, lse = call.run()
+    ref, ref_lse = oracle_attention(inp)
+    assert_attn_close(out, ref, "bf16", f"near {what} D={D}")
+    assert np.abs(lse - ref_lse).max() <= 2e-2
+    fd.fd_verify_draft_plan(call.args)
+    call.args.flags |= fd.FD_ATTN_PLANNED
+    call.out.fill_(float("nan"))
+    out2, lse2 = call.run()
+    assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
+
+
 @pytest.mark.parametrize("n, kv, page", [
     (17, (0, 1), 16),        # 68 rows: the last wave has none, empty and one-key prefixes
     (32, (63, 65), 16),      # 128 rows, one key either side of a tile
