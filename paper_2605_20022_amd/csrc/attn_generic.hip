@@ -44,7 +44,7 @@ __device__ __forceinline__ float quarters_max(float v) {
 
 int attn_generic_rows_per_wg() { return GEN_ROWS; }
 
-// NDB: head dim in blocks of 16, rounded up to 2, 4, 6 or 8 (the columns beyond D are zero in LDS).
+// NDB: head dim in blocks of 16, rounded up to 2, 4, 6 or 8 (the columns beyond D are zero in LDS and in Q).
 // Column of the output block g16 (0 .. NDB - 1) that matrix row m stands for: blocks are taken four
 // at a time (the rest, two, together), column = 64 (g16 / 4) + W m + g16 % 4 with W the group's
 // width, so that a lane's V operands of a group are adjacent in LDS and its outputs adjacent in memory.
@@ -99,9 +99,8 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
   };
 
   // ---- tile loads: thread tid takes 16-byte vectors tid + 256 i of the tile's K and V -------------
-  // No load is conditional: rows past the end repeat the last row, columns past D the first ones.  The
-  // scores of such rows are masked (their probability is zero) and such columns meet zeros of Q or are
-  // not stored.
+  // No load is conditional: rows past the end read the last row, columns past D the first ones, and both enter LDS as zeros.
+  // (The scores of such rows are masked and Q is zero in such columns, but zero times an infinity would not be zero.)
   constexpr bool EXACT = GEN_KEYS * TPR % GEN_BLOCK == 0;
   int ld_row[NLD], ld_col[NLD];
 #pragma unroll
@@ -151,11 +150,21 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
       *reinterpret_cast<u32x4*>(dst) = a; *reinterpret_cast<u32x4*>(dst + 4) = b;
     }
   };
-  auto store_tile = [&](int buf) {
+  auto store_tile = [&](int t, int buf) {
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
       put(&lds[buf][0][ld_row[i] * STR + ld_col[i]], rk[i]);
       put(&lds[buf][1][ld_row[i] * STR + ld_col[i]], rv[i]);
+    }
+    const int rows = t >= cached_tiles ? s.n - (t - cached_tiles) * GEN_KEYS : c1 - c0 - t * GEN_KEYS;     // that exist
+    if (rows < GEN_KEYS || D < DP) {               // (over what was just written: selecting the values before costs every tile 3 %)
+      const u32x4 zero = {0, 0, 0, 0};
+#pragma unroll
+      for (int i = 0; i < NLD; ++i)
+        if (ld_row[i] >= rows || ld_col[i] >= D) {
+          put(&lds[buf][0][ld_row[i] * STR + ld_col[i]], zero);
+          put(&lds[buf][1][ld_row[i] * STR + ld_col[i]], zero);
+        }
     }
   };
 
@@ -181,7 +190,7 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
   }
   load_tile(0);
   fetch_pages(1);
-  store_tile(0);
+  store_tile(0, 0);
   __syncthreads();
 
   float m_run = -INFINITY, l_lane = 0.f;
@@ -286,7 +295,7 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
       if (KS == 1) block(std::integral_constant<int, 2>{}, 0);
       else if (base + 16 * ks < end) block(std::integral_constant<int, 1>{}, ks);
     }
-    if (t + 1 < nt) store_tile((t + 1) & 1);
+    if (t + 1 < nt) store_tile(t + 1, (t + 1) & 1);
     __syncthreads();                               // tile t consumed, tile t + 1 visible
   }
 
@@ -330,7 +339,7 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
 #pragma unroll
         for (int c = 0; c < W; ++c) {
           const int d = 64 * gr + W * (4 * kq + i) + c;
-          if (d < D) Elem<T>::store(op + d, o[4 * gr + c][i] * inv);
+          if (d < D) Elem<T>::store(op + d, l_run > 0.f ? o[4 * gr + c][i] * inv : 0.f);        // (as the combine kernel does)
         }
     }
     if (p.lse && kq == 0) p.lse[orow] = m_run + logf(l_run);
@@ -387,15 +396,16 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnParams p) {
     float Mb = M;
 #pragma unroll
     for (int u = 0; u < NB; ++u) Mb = fmaxf(Mb, ml[u][0]);
-    if (Mb == -INFINITY) continue;
-    const float r = expf(M - Mb);                  // M = -inf: 0
+    const float Ms = Mb == -INFINITY ? 0.f : Mb;   // (no branch on it: the loads of the sums would move behind it)
+    const float r = expf(M - Ms);                  // M = -inf: 0
     num *= r; den *= r; M = Mb;
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
-      const float w = expf(ml[u][0] - M);
+      const float w = expf(ml[u][0] - Ms);
+      const bool none = ml[u][0] == -INFINITY;     // surplus, or a chunk in which no key has any weight: adds nothing, whatever its sums hold
 #pragma unroll
-      for (int e = 0; e < 4; ++e) num[e] = fmaf(w, a[u][e], num[e]);
-      den = fmaf(w, ml[u][1], den);
+      for (int e = 0; e < 4; ++e) num[e] = fmaf(w, none ? 0.f : a[u][e], num[e]);
+      den = fmaf(w, none ? 0.f : ml[u][1], den);
     }
   }
   T* op = reinterpret_cast<T*>(p.out) + slot0 * p.D + d;

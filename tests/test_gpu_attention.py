@@ -76,6 +76,35 @@ def test_full_precision_kernel_edges(fd, dtype, G, rows, D):
     _check(fd, inp, dtype, f"edges {dtype} D={D} G={G} rows={rows} ps={ps} chunk", flags=FORCE_GENERIC, kv_chunk=64)
 
 
+@pytest.mark.parametrize("D", [8, 40, 72, 104, 128])                        # head dims that are padded, and one that is not
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("chunk", [0, 64])
+def test_full_precision_kernel_infinities(fd, chunk, dtype, D):
+    """What pads a tile, a head dim or the combine kernel's last batch of chunks has no weight, and leaves infinities alone."""
+    w = _wl("inf", dtype, 4, 4, 2, D, 16, (300, 300), (0, 0), 5, seed=75 + D)      # mask rows: every row sees every key
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array([33, 64, 290, 300], dtype=np.int32)            # (the page lists are long enough; chunks of 64: 1, 1, 5, 5)
+    up, down = (np.float32("inf"), -np.float32("inf")) if dtype == "f32" else (np.uint16(0x7F80), np.uint16(0xFF80))
+    last = lambda i, off=1: (int(inp["page_indices"][inp["page_indptr"][i] + (inp["kv_len"][i] - off) // 16]), int(inp["kv_len"][i] - off) % 16)  # noqa: E731
+    positive = np.float32(0.5) if dtype == "f32" else np.uint16(0x3F00)
+    inp["q"][:, :, 0] = positive
+    for i in (0, 2):                                                        # the last cached value: +inf in one column
+        page, slot = last(i)
+        inp["v_cache"][page, 0, slot, 3] = up
+    r1 = int(inp["row_indptr"][2]) - 1                                      # sequence 1: the last new value
+    inp["v_new"][r1, 1, 5] = down
+    page, slot = last(3, 20)                                                # sequence 3: a key of -inf in its first column has no weight
+    inp["k_cache"][page, :, slot, 0] = down
+    call = AttnCall(fd, inp, flags=FORCE_GENERIC, kv_chunk=chunk)
+    out, lse = call.run()
+    ref, ref_lse = oracle_attention(inp)
+    assert np.isposinf(ref).any() and np.isneginf(ref).any() and not np.isnan(ref).any()
+    assert np.array_equal(np.isposinf(out), np.isposinf(ref)) and np.array_equal(np.isneginf(out), np.isneginf(ref))
+    finite = np.isfinite(ref)
+    assert_attn_close(out[finite], ref[finite], dtype, f"infinities {dtype} D={D} chunk={chunk}")
+    assert np.abs(lse - ref_lse).max() <= (1e-5 if dtype == "f32" else 2e-2)
+
+
 @pytest.mark.parametrize("case", [
     dict(B=3, G=4, Hkv=2, ps=16, kv=(1, 500), kr=(1, 8), m=8),
     dict(B=2, G=4, Hkv=1, ps=16, kv=(64, 64), kr=(4, 4), m=4),             # exactly one full tile
