@@ -89,7 +89,9 @@ fd_status plan_attn(const fd_attn_args* a, AttnPlan* plan) {
   const int tile_rows = plan->use_mfma ? fd::attn_mfma_rows_per_wg((int)(rows > 128 ? 128 : rows)) : fd::attn_generic_rows_per_wg();
   plan->row_tiles = (int)((rows + tile_rows - 1) / tile_rows);
   if (plan->row_tiles < 1) plan->row_tiles = 1;
-  if ((long long)plan->row_tiles * a->num_kv_heads > 65535)
+  // (the fp32 kernel takes 64 rows at a time; what calls it accepts is counted in sixteens)
+  const long long row_groups = plan->use_mfma ? plan->row_tiles : (rows + 15) / 16;
+  if (row_groups * a->num_kv_heads > 65535)
     return fail(FD_ERR_UNSUPPORTED, "max_new_rows * heads too large for one launch");
   if (plan->use_mfma) {
     // the persistent kernel counts (sequence, head, row block, 64-key tile) units in 32 bits

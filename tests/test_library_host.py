@@ -73,6 +73,19 @@ def test_attention_workspace_query_and_validation():
     assert e.value.code == 1 and "NULL" in str(e.value)
 
 
+def test_most_rows_of_one_launch():
+    """max_new_rows x heads is bounded: 65535 groups of sixteen (fp32 kernel), 64 or 128 tile rows."""
+    f32 = dict(dtype=fd.FD_F32, num_q_heads=8, num_kv_heads=8, total_rows=1, max_kv_len=64)
+    assert fd.fd_verify_draft_attn_workspace(_args(max_new_rows=131056, **f32)) > 0                # 8 x 8191
+    assert fd.fd_verify_draft_attn_workspace(_args(max_new_rows=131057, **f32)) == 0               # 8 x 8192
+    with pytest.raises(fd.FlexDraftError) as e:
+        fd._check(fd.load().fd_verify_draft_attn(C.byref(_args(max_new_rows=131057, **f32)), None))
+    assert e.value.code == 2
+    bf16 = dict(batch=1, num_q_heads=8, num_kv_heads=8, total_rows=1, max_kv_len=64)
+    assert fd.fd_verify_draft_attn_workspace(_args(max_new_rows=8191 * 128, **bf16)) > 0
+    assert fd.fd_verify_draft_attn_workspace(_args(max_new_rows=8191 * 128 + 1, **bf16)) == 0
+
+
 def test_plan_entry_point_validates_on_the_host():
     """fd_verify_draft_plan takes the same argument struct; a planned attention call needs the length of
     the page list (the plan's page ids are checked against it)."""
