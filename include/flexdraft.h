@@ -145,7 +145,9 @@ typedef struct fd_attn_args {
 } fd_attn_args;
 
 /* Bytes of workspace fd_verify_draft_attn needs for these arguments (reads only the
- * host-side scalar fields).  Pure host function; returns 0 on invalid arguments. */
+ * host-side scalar fields).  Pure host function; returns 0 on invalid arguments.
+ * With kv_chunk 0 the fp32 kernel also runs in less, with longer chunks, down to what
+ * chunks of at least 512 keys need. */
 FD_API size_t fd_verify_draft_attn_workspace(const fd_attn_args *args);
 
 /* Hybrid-mask verify+draft attention (Sec. 4.1).  Asynchronous on hip_stream.

@@ -60,11 +60,19 @@ constexpr double GEN_PARTIAL_BYTES = 32.0 * (1 << 20);
 struct AttnPlan {
   bool use_mfma;
   int chunk, max_chunks, row_tiles;
-  size_t acc_bytes, ml_bytes, total_bytes;
+  size_t acc_bytes, total_bytes;
 };
 
-// Host-only checks of the scalar fields and the launch-shape plan.
-fd_status plan_attn(const fd_attn_args* a, AttnPlan* plan) {
+// Bytes of the fp32 kernel's split partials: the output rows (acc), then their maxima and sums.
+size_t partial_bytes(const fd_attn_args* a, long long chunks, size_t* acc) {
+  const size_t slots = (size_t)chunks * (size_t)(a->total_rows > 0 ? a->total_rows : 1) * a->num_q_heads;
+  const size_t acc_bytes = (slots * a->head_dim * sizeof(float) + 255) / 256 * 256;
+  if (acc) *acc = acc_bytes;
+  return acc_bytes + (slots * 2 * sizeof(float) + 255) / 256 * 256;
+}
+
+// Host-only checks of the scalar fields and the launch-shape plan.  have: the bytes of workspace there are (a query: no bound).
+fd_status plan_attn(const fd_attn_args* a, AttnPlan* plan, size_t have = SIZE_MAX) {
   if (!a) return fail(FD_ERR_INVALID_ARG, "args is NULL");
   if (a->batch < 0 || a->total_rows < 0 || a->max_kv_len < 0 || a->max_new_rows < 0 || a->num_pages < 0)
     return fail(FD_ERR_INVALID_ARG, "negative size (batch %d, total_rows %d, max_kv_len %d, max_new_rows %d, num_pages %d)",
@@ -106,7 +114,8 @@ fd_status plan_attn(const fd_attn_args* a, AttnPlan* plan) {
     // matrix instructions take 64 rows at a time, which leaves four times fewer work-groups, so the chunks
     // are made shorter, down to 128 keys (4 x 512..2048 keys, 64 rows: 38 us; 64-key chunks 49, 256-key 38, 512-key 60:
     // a 64-row partial weighs as much as 33 keys), as long as the split partials stay below GEN_PARTIAL_BYTES
-    // (a call that fitted fd_verify_draft_attn_static with the coarse cut still does).
+    // (a call that fitted fd_verify_draft_attn_static with the coarse cut still does) and fit the workspace (one of the
+    // coarse cut's size still does).
     const long long seqs = a->batch > 0 ? a->batch : 1;
     auto chunk_for = [&](long long pairs, long long groups, long long least) {
       long long want = (groups + pairs - 1) / pairs;
@@ -118,7 +127,11 @@ fd_status plan_attn(const fd_attn_args* a, AttnPlan* plan) {
     const long long coarse = chunk_for(seqs * a->num_kv_heads * ((rows + 15) / 16 > 0 ? (rows + 15) / 16 : 1), 2048, 512);
     long long c = chunk_for(seqs * a->num_kv_heads * plan->row_tiles, 1024, 128);
     const double per_chunk = (double)(a->total_rows > 0 ? a->total_rows : 1) * a->num_q_heads * (a->head_dim + 2) * sizeof(float);
-    while (c < coarse && ((long long)a->max_kv_len + c - 1) / c * per_chunk > GEN_PARTIAL_BYTES) c += tile_keys;
+    while (c < coarse) {
+      const long long chunks = a->max_kv_len > 0 ? ((long long)a->max_kv_len + c - 1) / c : 1;
+      if (chunks * per_chunk <= GEN_PARTIAL_BYTES && (plan->use_mfma || partial_bytes(a, chunks, nullptr) <= have)) break;
+      c += tile_keys;
+    }
     if (c > coarse) c = coarse;
     chunk = (int)c;
   }
@@ -130,14 +143,11 @@ fd_status plan_attn(const fd_attn_args* a, AttnPlan* plan) {
   if (plan->use_mfma) {
     // persistent kernel: partial storage depends on the launch size only, not on the lengths
     plan->max_chunks = 1;
-    plan->acc_bytes = plan->ml_bytes = 0;
+    plan->acc_bytes = 0;
     plan->total_bytes = fd::attn_mfma_workspace(fd::attn_mfma_num_wgs(), tile_rows, nullptr, nullptr, nullptr);
     return FD_OK;
   }
-  size_t slots = (size_t)plan->max_chunks * (size_t)(a->total_rows > 0 ? a->total_rows : 1) * a->num_q_heads;
-  plan->acc_bytes = (slots * a->head_dim * sizeof(float) + 255) / 256 * 256;
-  plan->ml_bytes = (slots * 2 * sizeof(float) + 255) / 256 * 256;
-  plan->total_bytes = plan->acc_bytes + plan->ml_bytes;
+  plan->total_bytes = partial_bytes(a, plan->max_chunks, &plan->acc_bytes);
   return FD_OK;
 }
 
@@ -183,7 +193,7 @@ size_t fd_verify_draft_attn_workspace(const fd_attn_args* a) {
 enum { DO_PLAN = 1, DO_ATTN = 2 };
 static fd_status attn_call(const fd_attn_args* a, void* workspace, size_t workspace_bytes, void* hip_stream, int what) {
   AttnPlan plan;
-  fd_status st = plan_attn(a, &plan);
+  fd_status st = plan_attn(a, &plan, workspace_bytes);
   if (st != FD_OK) return st;
   g_err[0] = 0;
   if (a->batch == 0 || a->total_rows == 0) return FD_OK;          // nothing to compute

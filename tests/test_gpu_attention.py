@@ -76,6 +76,32 @@ def test_full_precision_kernel_edges(fd, dtype, G, rows, D):
     _check(fd, inp, dtype, f"edges {dtype} D={D} G={G} rows={rows} ps={ps} chunk", flags=FORCE_GENERIC, kv_chunk=64)
 
 
+@pytest.mark.parametrize("B,kv,n", [(4, (512, 2048), 16), (1, (5000, 5000), 3), (2, (600, 700), 20)])
+def test_full_precision_kernel_in_a_small_workspace(fd, B, kv, n):
+    """Less workspace than the query's answer: longer chunks, down to what chunks of 512 keys need; below that, refused."""
+    w = _wl("small_ws", "f32", B, 8, 2, 128, 16, kv, (n, n), 0, seed=78)
+    inp = W.make_attention_inputs(w)
+    call = AttnCall(fd, inp)
+    R = int(inp["row_indptr"][-1])
+    up256 = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    need = lambda chunk: sum(up256(-(-int(inp["kv_len"].max()) // chunk) * R * 8 * e * 4) for e in (128, 2))  # noqa: E731
+    full = fd.fd_verify_draft_attn_workspace(call.args)
+    least = need(512)
+    assert least < full
+    for have in (full, full - 1, (full + least) // 2, least):
+        call.workspace.fill_(255)
+        call.args.workspace_bytes = have
+        call.out.fill_(float("nan"))
+        out, _ = call.run()
+        ref, _ = oracle_attention(inp)
+        assert_attn_close(out, ref, "f32", f"workspace of {have} of {full} bytes")
+        assert bool((call.workspace[have:] == 255).all())
+    call.args.workspace_bytes = least - 1
+    with pytest.raises(fd.FlexDraftError) as e:
+        fd.fd_verify_draft_attn(call.args)
+    assert e.value.code == 3
+
+
 @pytest.mark.parametrize("D", [8, 40, 72, 104, 128])                        # head dims that are padded, and one that is not
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("chunk", [0, 64])
