@@ -28,6 +28,7 @@ __device__ __forceinline__ void fetch8(const bf16_t* p, Vec8<bf16_t>& r) {
 __device__ __forceinline__ void fetch8(const float* p, Vec8<float>& r) {
   typedef f32x4 __attribute__((aligned(4))) f32x4_any;
   r.a = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
+  __builtin_amdgcn_sched_barrier(0);
   r.b = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p) + 1);
 }
 // near the end of a row, or in a row of fewer than eight logits: one by one, the last one repeated
@@ -69,11 +70,14 @@ template <typename T, int N, bool SHORT> struct RowShare {
     for (int u = 0; u < N; ++u) {
       if (SHORT) fetch8_short(row, at(u), end, r[u]); else fetch8(row + from(u), r[u]);
     }
+    // (without the two barriers the halves of a vector of floats go out in reverse, the last one when all the others have landed:
+    // selection over 40 rows of 151936 floats 13.5 us a call, now 12.6)
+    if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
   }
-  // Before a second pass over the vectors: keeps the compiler from holding the first pass's floats (twice the registers).
+  // Before a second pass over the vectors: keeps the compiler from holding the first pass's widened floats (twice the registers).
   __device__ __forceinline__ void again() {
 #pragma unroll
-    for (int u = 0; u < N; ++u) hold8(r[u]);
+    for (int u = 0; u < N; ++u) if (sizeof(T) == 2) hold8(r[u]);
   }
   __device__ __forceinline__ float max() const {
     float m = -INFINITY;
@@ -103,6 +107,13 @@ template <typename T, int N, bool SHORT> struct RowShare {
     for (int u = 0; u < N; ++u) {
       float x[8], t = 0.f;
       widen8(r[u], x);
+      if (!SHORT && sizeof(T) == 4) {              // (floats: a test per element costs less than a branch per vector, bf16 the other way round)
+        const int skip = at(u) - from(u);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t += i >= skip ? f(x[i]) : 0.f;
+        tot += t;
+        continue;
+      }
 #pragma unroll
       for (int i = 0; i < 8; ++i) t += f(x[i]);
       if (at(u) + 8 > end) {                       // few lanes of a share's last vector, and all beyond
