@@ -493,6 +493,33 @@ def test_planned_call_with_a_foreign_plan_stays_in_bounds(fd):
     assert_attn_close(out, ref, "bf16", "after a foreign plan")
 
 
+@pytest.mark.parametrize("B,Hkv,n,kv,chunk,other_B,other_kv", [
+    (4, 2, 8, (100, 900), 64, 7, (300, 2000)),       # along the line: a chunk size
+    (65, 2, 8, (10, 300), 0, 70, (100, 900)),        # ... more than 64 sequences
+    (40, 8, 8, (50, 300), 0, 45, (300, 700)),        # the device's choice: pieces, the other plan along the line
+    (45, 8, 8, (300, 700), 0, 40, (50, 300)),        # ... the other way round
+    (4, 2, 30, (100, 900), 0, 7, (300, 2000)),       # 128 rows, piece by piece
+    (65, 2, 30, (10, 300), 0, 70, (100, 900)),       # ... along the line
+])
+def test_foreign_plan_in_every_variant_stays_in_bounds(fd, B, Hkv, n, kv, chunk, other_B, other_kv):
+    """As above, for the kernels that walk the line and those of 128 rows."""
+    wl = lambda B, kv, seed: _wl("stale", "bf16", B, 4 * Hkv, Hkv, 128, 16, kv, (2, n), 2, seed=seed)  # noqa: E731
+    call = AttnCall(fd, W.make_attention_inputs(wl(B, kv, 54)), kv_chunk=chunk)
+    other = AttnCall(fd, W.make_attention_inputs(wl(other_B, other_kv, 55)), kv_chunk=chunk)
+    assert call.workspace.numel() == other.workspace.numel()
+    other.workspace.zero_()
+    fd.fd_verify_draft_plan(other.args)
+    call.workspace.copy_(other.workspace)
+    call.args.flags |= fd.FD_ATTN_PLANNED
+    fd.fd_verify_draft_attn(call.args)
+    torch.cuda.synchronize()
+    call.status.zero_()
+    call.args.flags &= ~fd.FD_ATTN_PLANNED
+    out, _ = call.run()
+    ref, _ = oracle_attention(call.inp)
+    assert_attn_close(out, ref, "bf16", "after a foreign plan")
+
+
 def test_mfma_strided_cache_layout(fd):
     """Token-major cache ([page][slot][head][D]) addressed through the stride arguments."""
     w = _wl("nhd", "bf16", 3, 8, 2, 128, 16, (10, 400), (2, 6), 6, seed=31)
@@ -507,6 +534,22 @@ def test_mfma_strided_cache_layout(fd):
     a.cache_stride_page, a.cache_stride_head, a.cache_stride_token = (call.d["k_cache"].stride(i) for i in range(3))
     out, _ = call.run()
     assert_attn_close(out, ref, "bf16", "strided cache")
+
+
+@pytest.mark.parametrize("B,n,D", [(3, 30, 128), (70, 30, 128), (3, 30, 64)])       # piece by piece, along the line
+def test_128_row_tiles_strided_cache_layout(fd, B, n, D):
+    """The same layout through the 128-row kernels, whose lane offsets come from the token pitch."""
+    w = _wl("nhd128", "bf16", B, 8, 2, D, 16, (10, 400), (n - 6, n - 6), 6, seed=32)
+    inp = W.make_attention_inputs(w)
+    ref, _ = oracle_attention(inp)
+    call = AttnCall(fd, inp)
+    for name in ("k_cache", "v_cache"):
+        call.d[name] = call.d[name].permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+    a = call.args
+    a.k_cache = call.d["k_cache"].data_ptr(); a.v_cache = call.d["v_cache"].data_ptr()
+    a.cache_stride_page, a.cache_stride_head, a.cache_stride_token = (call.d["k_cache"].stride(i) for i in range(3))
+    out, _ = call.run()
+    assert_attn_close(out, ref, "bf16", f"strided cache, {B} sequences of {n} rows, D={D}")
 
 
 def test_mask_semantics_on_gpu(fd):
