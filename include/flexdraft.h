@@ -67,7 +67,7 @@ typedef enum fd_dtype { FD_F32 = 0, FD_BF16 = 1 } fd_dtype;
 #define FD_DEV_PAGE_RANGE     4u  /* page id outside [0, num_pages) or page list too short   */
 
 /* fd_attn_args.flags */
-#define FD_ATTN_FORCE_GENERIC 1   /* use the scalar fp32-accumulate kernel even for bf16     */
+#define FD_ATTN_FORCE_GENERIC 1   /* use the full-precision (fp32) kernel even for bf16      */
 #define FD_ATTN_PLANNED       2   /* the workspace holds fd_verify_draft_plan's plan for these
                                    * arguments: fd_verify_draft_attn starts from it           */
 
@@ -158,9 +158,9 @@ FD_API fd_status fd_verify_draft_attn(const fd_attn_args *args, void *hip_stream
  * Planning for fd_verify_draft_attn, separated out because it depends on the lengths only and the
  * same lengths meet every layer of the model in one decoding step (Sec. 4.1: one forward pass
  * verifies and drafts; Sec. 4.3).  The bf16 kernel for head_dim 128 or 64 cuts the batch's key tiles into
- * equal shares for its persistent work-groups (or, with few items, each item into equal pieces); the plan is,
- * per work-group, where its share
- * starts (sequence, offset, the page ids of its first two tiles).  Without a plan every work-group
+ * equal shares for its persistent work-groups (or, with few items, each item into equal pieces); the
+ * plan is, per work-group, where its share starts (sequence, offset, the page ids of its first two
+ * tiles).  Without a plan every work-group
  * of fd_verify_draft_attn finds its share itself, by a scan over the batch, before it can request
  * its first tile; with args->flags & FD_ATTN_PLANNED it starts from the plan this call left in
  * args->workspace, and leaves it intact for the next call.

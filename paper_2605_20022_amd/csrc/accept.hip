@@ -274,9 +274,9 @@ __device__ __forceinline__ float exp_neg(float y) {
 // Sampling, pass 1: per (row, segment) the maximum of x / T and sum exp(x / T - max), for the
 // target and the draft logits.  Both segments are requested up front and held in registers (one
 // memory latency per work-group), the maximum is found first and the sum taken relative to it: the
-// maximum's own term is exactly 1 and every other term's rounding error (|y| 2^-23 of itself,
-// y = x / T - max <= 0) is weighted by its small size, so the plain hardware exp2 is accurate
-// enough for a normaliser that is compared at 1e-5.
+// maximum's own term is 1 up to the rounding of the scaled maximum (scale and subtraction are one FMA)
+// and every other term's rounding error (|y| 2^-23 of itself, y = x / T - max <= 0) is weighted by its
+// small size, so the plain hardware exp2 is accurate enough for a normaliser that is compared at 1e-5.
 //   grid (segments, rows); part [rows][segments][4] = (max_t, sum_t, max_d, sum_d)
 //   NR = rounds of ACC_BLOCK * 8 logits that cover a segment (registers held: 8 NR for bf16)
 template <typename T, int NR, bool SHORT>

@@ -112,8 +112,8 @@ fd_status plan_attn(const fd_attn_args* a, AttnPlan* plan, size_t have = SIZE_MA
   if (chunk == 0) {
     // fp32 kernel: the coarse cut covers 256 CUs with sixteen-row tiles at chunks of at least 512 keys; the
     // matrix instructions take 64 rows at a time, which leaves four times fewer work-groups, so the chunks
-    // are made shorter, down to 128 keys (4 x 512..2048 keys, 64 rows: 38 us; 64-key chunks 49, 256-key 38, 512-key 60:
-    // a 64-row partial weighs as much as 33 keys), as long as the split partials stay below GEN_PARTIAL_BYTES
+    // are made shorter, down to 128 keys (4 x 512..2048 keys, 64 rows, with the kernel the chunk was chosen with: 38 us; 64-key
+    // chunks 49, 256-key 38, 512-key 60; 35 us today: a 64-row partial weighs as much as 33 keys), as long as the split partials stay below GEN_PARTIAL_BYTES
     // (a call that fitted fd_verify_draft_attn_static with the coarse cut still does) and fit the workspace (one of the
     // coarse cut's size still does).
     const long long seqs = a->batch > 0 ? a->batch : 1;
@@ -225,8 +225,8 @@ static fd_status attn_call(const fd_attn_args* a, void* workspace, size_t worksp
   p.total_rows = a->total_rows; p.max_kv_len = a->max_kv_len; p.max_new_rows = a->max_new_rows;
   p.num_pages = a->num_pages; p.page_entries = a->page_indices_len; p.chunk = plan.chunk; p.max_chunks = plan.max_chunks; p.row_tiles = plan.row_tiles;
   {
-    // with 2^(s-1) < d <= 2^s the magic ceil(2^(31+s) / d) fits 32 bits and is off by e < d / d <= 1, i.e.
-    // magic d - 2^(31+s) < d <= 2^s: n / d = floor(n magic / 2^(31+s)) for every n < 2^31
+    // with 2^(s-1) < d <= 2^s the magic ceil(2^(31+s) / d) fits 32 bits; e = magic d - 2^(31+s) < d <= 2^s, hence
+    // n e < 2^(31+s) for every n < 2^31 and floor(n magic / 2^(31+s)) = n / d
     const unsigned long long d = (unsigned)a->page_size;
     int sh = 0;
     while ((1ull << sh) < d) ++sh;

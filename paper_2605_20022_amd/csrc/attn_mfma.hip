@@ -3,12 +3,14 @@
 // Work decomposition.  An *item* is one (sequence, KV head, block of up to ROWS_WG tile
 // rows); a tile row is (new row, query head of the group), so K and V are read from HBM once
 // for all rows and all G heads of the KV head.  An item consists of ceil(L/64) tiles of 64
-// cached keys followed by the tile(s) of the sequence's own new rows.  All tiles of all
-// items, in (sequence, head, row block) order, form one line of work that is cut into equal
-// shares, one per persistent work-group (two work-groups per CU), so that every CU streams
-// the same number of bytes whatever the length mix of the batch.  A share is walked as a
-// sequence of *pieces* (runs of tiles inside one item).  A piece that covers a whole item is
-// normalised and stored; an item cut by a share boundary leaves one split partial (base-2
+// cached keys followed by the tile(s) of the sequence's own new rows.  The work is cut in one of two ways:
+//   along the line   all tiles of all items, in (sequence, head, row block) order, form one line that is cut into
+//                    equal shares, one per persistent work-group (two work-groups per CU), so that every CU streams
+//                    the same number of bytes whatever the length mix of the batch (find_share)
+//   piece by piece   every item is cut into equal pieces and a work-group takes exactly one: calls of few items
+//                    (find_piece; fill_sched has the rule)
+// A share of the line is walked as a sequence of *pieces* (runs of tiles inside one item).  A piece that covers a whole item is
+// normalised and stored; an item cut into several leaves one split partial (base-2
 // running max, sum, un-normalised O as fp16 rows scaled by their largest entry) per work-group
 // that touched it, and the work-group in which it ends leaves an entry for the combine kernel below.
 //
@@ -413,8 +415,8 @@ __device__ __forceinline__ bool find_share(const AttnParams& p, const MfmaSched&
 // with 36 rows 75 -> 69.8; 16 of 512..4096 keys: equal.  The line is better where s comes out longer than its shares (400 items
 // for 512 work-groups are whole items here, 4/5 of one there): of more than num_wgs / 2 items, pieces are cut only if
 // s is at most MF_PIECE_SLACK tiles above a share (64-row items of 1000..3000 keys, 320 of them: s is 8 above, 62.7 -> 66.6).
-// Up to num_wgs / 2 items (the host's bound; fill_sched has the exception) they always are, at most 2 s0 long, and the streaming kernel is the variant
-// without the line: no walk over items and no second piece, a third of the instructions and no spilled scalars
+// Up to num_wgs / 2 items (the host's bound; fill_sched has the exception) they always are, at most 2 s0 long, and the
+// streaming kernel is the variant without the line: no walk over items and no second piece, a third of the instructions and no spilled scalars
 // (16 of 512..4096 keys 39.7 -> 37.9, 1 of 2048 14.6 -> 13.2, 4 of 32768 112.7 -> 109.4).
 // Pieces are numbered (sequence, head, piece, row block): the row blocks that read the same tiles are neighbours.
 // Every wave works this out by itself (lane i holds sequence i): no LDS, no barrier.
@@ -1093,10 +1095,11 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
     };
     // DIRECT: while tile t is multiplied out of one LDS buffer, tile t+1 flies into the other.  A wave takes both 32-key blocks
     // of the tile under one softmax step: the sixteen MFMAs of S on two chains, and the exponentials of the second
-    // block between the P V MFMAs of the first.  The registers that staged tiles hold LDS fragments instead.  Against staging through registers, block by block (us a call): 2 sequences of 272 rows of 4
-    // heads 76.1 -> 71.4, 8 of 36 rows 68.1 -> 65.9, 4 of 32 rows over 32768 keys 109.4 -> 107.4.  Bound by issue: of 72 us
-    // at the first size the MFMAs alone take 23, the softmax 13 on top (an MFMA in flight keeps the vector pipe of its
-    // SIMD busy for most of its time), waiting for tiles 10; the LDS reads hide behind the MFMAs.
+    // block between the P V MFMAs of the first.  The registers that staged tiles hold LDS fragments instead.  Against staging
+    // through registers, block by block (us a call): 2 sequences of 272 rows of 4 heads 76.1 -> 71.4, 8 of 36 rows
+    // 68.1 -> 65.9, 4 of 32 rows over 32768 keys 109.4 -> 107.4.  Bound by issue: of 72 us at the first size the MFMAs
+    // alone take 23, the softmax 13 on top (an MFMA in flight keeps the vector pipe of its SIMD busy for most of its
+    // time), waiting for tiles 10; the LDS reads hide behind the MFMAs.
     auto iteration_direct = [&](int t, int buf) {
       const int tau = tile0 + t;
       // Waves in their MFMA phases go before waves in their softmax (with the turns of the other variant: 2 sequences of 272 rows
