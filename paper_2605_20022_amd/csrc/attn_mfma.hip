@@ -141,9 +141,8 @@ struct MfmaSched {
   // Combine entries [num_wgs + 1].
   //   by share  entry w: the split item that ends in the work-group of share w: (first packed row, head | row block << 16,
   //             tile rows, first slot); first < 0: none.  Entry num_wgs: (shares in use, -, -, -)
-  //   by item   entry (sequence * Hkv + head) * rt_max + row block: (first slot, share it ended in, shares from one of its
-  //             pieces to the next, -); first < 0: the item was not split.  Written by the work-group that holds the
-  //             item's last tile.
+  //   by item   entry (sequence * Hkv + head) * rt_max + row block: (first slot, share it ended in, -, -); first < 0: the
+  //             item was not split.  Written by the work-group that holds the item's last tile.
   int4* entries;
   struct PlanEntry* plan;     // [num_wgs]: written by the planning kernel, read by a planned streaming kernel
 };
@@ -418,7 +417,7 @@ __device__ __forceinline__ bool find_share(const AttnParams& p, const MfmaSched&
 // Up to num_wgs / 2 items (the host's bound; fill_sched has the exception) they always are, at most 2 s0 long, and the
 // streaming kernel is the variant without the line: no walk over items and no second piece, a third of the instructions and no spilled scalars
 // (16 of 512..4096 keys 39.7 -> 37.9, 1 of 2048 14.6 -> 13.2, 4 of 32768 112.7 -> 109.4).
-// Pieces are numbered (sequence, head, piece, row block): the row blocks that read the same tiles are neighbours.
+// An item's pieces have consecutive numbers (in lists: head, length class, sequence, row block, piece; else sequence, head, row block, piece).
 // Every wave works this out by itself (lane i holds sequence i): no LDS, no barrier.
 // Returns false if the call is to be cut along the line; has_piece: this work-group has one.
 struct PieceShare { int w, seq, W_eff, pieces, head, rt, tile0, nt; };
@@ -462,19 +461,35 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
   }
   if (!SINGLE && size > longest) return false;
   if (bad && threadIdx.x < 64) flag_status(p.status, bad);
-  const int S = (T + size - 1) / size, n = I * S;
-  const int hi = wave_incl_scan(n), lo = hi - n;
-  ps.W_eff = __builtin_amdgcn_readlane(hi, 63);
-  // Which piece a work-group takes: neighbours on one XCD, as on the line, unless that leaves an XCD more than a quarter above the
-  // average.  One work-group holds one piece however short it is, so where one sequence is much longer than the
-  // others half of the XCDs had nothing but its pieces and the other half next to nothing to do; in turn, every
-  // compute unit gets some of both.  us a call, in runs / in turn: 31 sequences of 256 keys and one of 32768, 16 rows 56.0 / 48.6 (line:
-  // 50), 24 of 1000 and eight of 16384 129.8 / 110, 28 of 300 and four of 8192 49.0 / 43.5.  Even batches stay in runs (one sequence of
-  // 2048 keys: 11.5 / 12.5, the combine kernel finds a head's partial rows on its own XCD), and so do calls with several row blocks, which
-  // read the same tiles.
-  const int chunk = (ps.W_eff + sc_.xcds - 1) / sc_.xcds;
-  ps.w = pw / sc_.xcds < chunk ? (pw % sc_.xcds) * chunk + pw / sc_.xcds : ps.W_eff;
-  if (!sc_.reuse && 4ll * tiles_all < 3ll * ps.W_eff * size) {     // (many pieces are far shorter than the longest)
+  const int RT = I / p.Hkv, S = (T + size - 1) / size, per = RT * S;
+  ps.W_eff = wave_total(I * S);
+  // Which piece a work-group takes: neighbours on one XCD, as on the line.  Every work-group holds one piece however short it is, so
+  // lists of equally many pieces are not lists of equally many tiles, and where lengths differ:
+  //   KV heads a multiple of the XCDs   an XCD takes the pieces of its heads, a head's row blocks and sequences in one list: the lists
+  //     are alike.  In a list the longest pieces come first (those of more than 15/16 of the longest, of more than 7/8, the others),
+  //     since the first work-group of a compute unit has its first tile 3 us before the second, and the second ones take the
+  //     rest from its end, so that the longest share their compute unit with the shortest.  us a call, runs over (sequence, head, piece, row
+  //     block) / lists: 2 sequences of 272 rows (pieces of 22 and 28 tiles) 68.3 / 63.9; 16 of 512..4096 keys, 16 rows 37.4 / 36.5;
+  //     24 of 512..4096, 32 rows 58.2 / 56.0; 8 of 36 rows in four blocks 59.0 / 57.5; 15 of 1000 and one of 131072, 16 rows 118 / 111.
+  //   else   runs, unless they leave an XCD more than a quarter above the average (one sequence much longer than the others: half
+  //     of the XCDs had nothing but its pieces): then in turn, every compute unit gets some of both.
+  // Even batches stay in runs (24 sequences of 2048 keys, 32 rows 50.2, in lists 51.3).
+  const bool lists = p.Hkv % sc_.xcds == 0 && 16ll * tiles_all < 15ll * ps.W_eff * size;
+  const int n = lists ? per : I * S;               // this lane's pieces in a list, or in all; lo: those before them
+  int lo, P = ps.W_eff;
+  if (lists) {
+    const int longest_here = S > 0 ? (T + S - 1) / S : 0;
+    const int shift = 16 * longest_here > 15 * size ? 0 : 8 * longest_here > 7 * size ? 10 : 20;          // three sums in one (fill_sched: at most 1023 pieces)
+    const int sums = wave_incl_scan(n << shift), all = __builtin_amdgcn_readlane(sums, 63);
+    const int n0 = all & 1023, n1 = all >> 10 & 1023;
+    P = n0 + n1 + (all >> 20);
+    lo = (shift == 0 ? 0 : shift == 10 ? n0 : n0 + n1) + (sums >> shift & 1023) - n;
+  } else lo = wave_incl_scan(n) - n;
+  const int hi = lo + n;
+  const int xcd = pw % sc_.xcds, place = pw / sc_.xcds, half = sc_.num_wgs / sc_.xcds / FD_WGS_PER_CU;
+  const int chunk = (ps.W_eff + sc_.xcds - 1) / sc_.xcds;                 // (lists: P pieces for each head of the XCD)
+  ps.w = place >= chunk ? ps.W_eff : xcd * chunk + (lists && place >= half ? chunk - 1 - (place - half) : place);
+  if (!lists && !sc_.reuse && 4ll * tiles_all < 3ll * ps.W_eff * size) {           // (many pieces are far shorter than the longest)
     const float mean = S > 0 ? (float)T / (float)S : 0.f;          // tiles of a piece of this lane's sequence
     const float before = (float)(wave_incl_scan(T * I) - T * I);   // tiles before the sequence
     float most = 0.f, upto = 0.f;
@@ -489,17 +504,19 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
     if (most * (float)sc_.xcds > 1.25f * (float)tiles_all) ps.w = pw;
   }
   if (ps.w >= ps.W_eff) return true;
-  const int at = __ffsll((long long)__ballot(lo <= ps.w && ps.w < hi)) - 1;
+  ps.head = lists ? ps.w / P : 0;
+  const int q = ps.w - ps.head * P;
+  const int at = __ffsll((long long)__ballot(lo <= q && q < hi)) - 1;
   if (at < 0) return true;                                         // cannot happen
   auto from = [&](int v) { return __builtin_amdgcn_readlane(v, at); };
   ws.L = from(s.L); ws.row0 = from(s.row0); ws.n = from(s.n); ws.k = from(s.k);
   ws.v = from(s.v); ws.nb = from(s.nb); ws.page0 = from(s.page0); ws.npages = from(s.npages);
-  const int Ts = from(T), Ss = from(S), RT = from(I) / p.Hkv;
-  const int local = ps.w - from(lo);
+  const int Ts = from(T), Ss = from(S), per_s = from(per);
+  int local = q - from(lo);
+  if (!lists) { ps.head = local / per_s; local -= ps.head * per_s; }
   ps.seq = at; ps.pieces = Ss;
-  ps.head = local / (RT * Ss);
-  const int r = local - ps.head * (RT * Ss), j = r / RT;
-  ps.rt = r - j * RT;
+  ps.rt = local / Ss;
+  const int j = local - ps.rt * Ss;
   // piece j: tiles [floor(j T / S), floor((j + 1) T / S)), in 32 bits: T = a S + b
   const int a = Ts / Ss, b = Ts - a * Ss;
   ps.tile0 = j * a + (j * b) / Ss;
@@ -924,16 +941,15 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
       // Its first piece sits in the work-group wf that owns the item's first tile, in slot 2 wf
       // if nothing of wf's share precedes the item (a share that begins among the item's start-up
       // units has nothing before the item's first tile), else 2 wf + 1; later pieces are in slots 2 w'.
-      // Cut piece by piece, piece j is in slot 2 (w - (pieces - 1 - j) row blocks).
-      int first_slot, step = 1;
+      // Cut piece by piece, piece j is in slot 2 (w - (pieces - 1 - j)).
+      int first_slot;
       if (SINGLE || (CUT && ps.pieces > 0)) {
-        step = I / p.Hkv;
-        first_slot = 2 * max(0, w - (ps.pieces - 1) * step);
+        first_slot = 2 * max(0, w - (min(ps.pieces, sc_.num_wgs) - 1));
       } else {
         const int wf = wg_of_unit(cur.item_u + MF_START_COST);
         first_slot = 2 * wf + (share_start(wf) >= cur.item_u ? 0 : 1);
       }
-      if (sc_.by_item) sc_.entries[item_id] = make_int4(first_slot, w, step, 0);
+      if (sc_.by_item) sc_.entries[item_id] = make_int4(first_slot, w, 0, 0);
       else sc_.entries[w] = make_int4(cur.s.row0, cur.head | (cur.rt << 16), min(ROWS_WG, cur.s.n * p.G - cur.rt * ROWS_WG), first_slot);
     }
     const int RB = ln.RB, KQ = ln.KQ, rb = ln.rb, kq = ln.kq, trow = ln.trow, nn = ln.nn, hq = ln.hq;
@@ -1373,8 +1389,8 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
 // ---------------------------------------------------------------------------------------
 // Merge the split partials of every item that was cut by a share boundary:
 //   M = max m;  out = sum 2^{m - M} acc / sum 2^{m - M} l;  lse = (M + log2 sum) ln 2.
-// The pieces of an item sit in its first slot, then in the first slot (2w) of every later (cut piece by
-// piece: every step-th later) work-group up to the one it ended in.  Sixteen lanes per tile row, a lane owns eight adjacent
+// The pieces of an item sit in its first slot, then in the first slot (2w) of every later
+// work-group up to the one it ended in.  Sixteen lanes per tile row, a lane owns eight adjacent
 // output columns; PG sixteen-lane groups share a row and take every PG-th piece.
 //   grid (items or shares, ROWS_WG PG / 16), with rows_first the other way round: an item's row blocks then lie on different
 //   XCDs.  In a grid of 256 items they lie 256 blocks apart, on the same compute unit: with eight long items of some 40 pieces among 248
@@ -1395,11 +1411,11 @@ __global__ __launch_bounds__(256) void attn_mfma_combine_kernel(AttnParams p, Mf
   const int entry = rows_first ? blockIdx.y : blockIdx.x, row_block = rows_first ? blockIdx.x : blockIdx.y;
   const int4* ep4 = sc_.entries + entry;
   const int* ep = reinterpret_cast<const int*>(ep4);
-  int row0, head, rt, rows_here, first_slot, wl, step = 1;     // step: shares from a piece to the next
+  int row0, head, rt, rows_here, first_slot, wl;
   if (sc_.by_item) {
     const int sh = entry / sc_.rt_max, seq = sh / p.Hkv;
     rt = entry - sh * sc_.rt_max; head = sh - seq * p.Hkv;
-    first_slot = sload(ep, 0); wl = sload(ep, 1); step = max(1, sload(ep, 2));
+    first_slot = sload(ep, 0); wl = sload(ep, 1);
     const int r0 = sload(p.row_indptr, seq), r1 = sload(p.row_indptr, seq + 1);          // (clamped as load_seq does)
     row0 = clampi(r0, 0, p.total_rows);
     const int n = min(clampi(r1 - r0, 0, p.max_new_rows), p.total_rows - row0);
@@ -1420,13 +1436,13 @@ __global__ __launch_bounds__(256) void attn_mfma_combine_kernel(AttnParams p, Mf
   const int T_row = rt * ROWS_WG + trow;
   const int nn = T_row / p.G, hq = head * p.G + T_row % p.G;
   if (row0 + nn >= p.total_rows) return;
-  const int np = (step == 1 ? wl - wf : (wl - wf) / step) + 1;     // pieces: slot first_slot, then 2 (wf + step) .. 2 wl
+  const int np = wl - wf + 1;                      // pieces: slot first_slot, then 2 (wf + 1) .. 2 wl
   auto ml_of = [&](int pi) -> const f32x4* {               // (max, sum, scale, -)
-    const long long slot = pi == 0 ? first_slot : 2 * (wf + pi * step);
+    const long long slot = pi == 0 ? first_slot : 2 * (wf + pi);
     return reinterpret_cast<const f32x4*>(sc_.part_ml + (slot * ROWS_WG + trow) * 4);
   };
   auto acc_of = [&](int pi) -> const u32x4* {               // eight fp16 columns of the scaled row
-    const long long slot = pi == 0 ? first_slot : 2 * (wf + pi * step);
+    const long long slot = pi == 0 ? first_slot : 2 * (wf + pi);
     return reinterpret_cast<const u32x4*>(sc_.part_acc + (slot * ROWS_WG + trow) * MF_D) + l16;
   };
   float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -1551,7 +1567,7 @@ static void fill_sched(const AttnParams& p, void* workspace, int kv_chunk, MfmaS
   sc.rt_max = (int)(((long long)p.max_new_rows * p.G + rows_wg - 1) / rows_wg);
   sc.by_item = (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs ? 1 : 0;
   sc.rows_first = (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs / 2 ? 1 : 0;
-  sc.by_piece = sc.by_item && p.B <= 64 && sc.fixed_share == 0 ? 1 : 0;
+  sc.by_piece = sc.by_item && p.B <= 64 && sc.fixed_share == 0 && sc.num_wgs < 1024 ? 1 : 0;      // (find_piece counts pieces in ten bits)
   const long long items_max = (long long)p.B * p.Hkv * sc.rt_max;
   if (sc.by_piece && items_max <= sc.num_wgs / 2) sc.by_piece = 2;
   // With close to num_wgs / 2 items and one piece per work-group, an item has hardly more than one piece or two: where lengths differ, the

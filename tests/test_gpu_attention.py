@@ -294,6 +294,31 @@ def test_one_sequence_much_longer_than_the_others(fd, lens, Hkv, n, D):
     assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
 
 
+@pytest.mark.parametrize("lens,Hkv,n,D", [
+    ([2208, 2346, 3219, 636, 1028, 3462, 1900, 700], 8, 4, 128),       # all three length classes, second work-groups from the list's end
+    ([700, 3000, 64, 0, 1300], 8, 4, 64),
+    ([1500, 640], 8, 100, 128),        # four row blocks, the last one with 16 rows
+    ([1500, 640], 16, 33, 128),        # two heads per XCD, a last row block of four rows
+    ([900, 0, 0, 100], 8, 40, 64),     # sequences without a prefix
+    ([600, 200], 24, 4, 128),          # three heads per XCD, fewer pieces than places
+])
+def test_lists_of_pieces_per_head(fd, lens, Hkv, n, D):
+    """KV heads a multiple of eight and pieces of different lengths: planned and self-planning calls agree bit for bit."""
+    w = _wl("lists", "bf16", len(lens), 4 * Hkv, Hkv, D, 16, (max(lens), max(lens)), (n - 2, n), 0, seed=340 + n)
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array(lens, dtype=np.int32)                 # (the page lists are long enough for all of them)
+    call = AttnCall(fd, inp)
+    out, lse = call.run()
+    ref, ref_lse = oracle_attention(inp)
+    assert_attn_close(out, ref, "bf16", f"lists {lens} Hkv={Hkv} n={n} D={D}")
+    assert np.abs(lse - ref_lse).max() <= 2e-2
+    fd.fd_verify_draft_plan(call.args)
+    call.args.flags |= fd.FD_ATTN_PLANNED
+    call.out.fill_(float("nan"))
+    out2, lse2 = call.run()
+    assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
+
+
 @pytest.mark.parametrize("D,lens,Hkv,n,what", [
     (64, [2000, 2000, 2000, 4200], 64, 4, "256 items, the line"),
     (64, [2000, 4200, 2000, 2000], 64, 65, "128-row items, the line"),
