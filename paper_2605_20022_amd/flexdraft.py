@@ -106,13 +106,20 @@ def _check(code: int):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> C.c_void_p:
+# The handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object for it, 2.7 us of
+# a call's 6 to 10; the handle alone is 0.3 us (thirteen calls of a decoding step: 115 -> 77 us on the host).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _dtype_code(t: torch.Tensor) -> int:

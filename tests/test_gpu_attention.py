@@ -704,3 +704,13 @@ def test_argument_errors_and_device_status(fd):
     empty = AttnCall(fd, subset_inputs(inp, []))
     fd.fd_verify_draft_attn(empty.args)
     torch.cuda.synchronize()
+
+
+def test_calls_go_to_the_current_stream(fd):
+    """Without a stream argument a call goes to torch's current stream of the current device, whichever that is."""
+    side = torch.cuda.Stream()
+    assert fd._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert fd._stream(None) == side.cuda_stream
+    assert fd._stream(side) == side.cuda_stream
+    assert fd._stream(None) == torch.cuda.current_stream().cuda_stream != side.cuda_stream
