@@ -127,7 +127,8 @@ struct MfmaSched {
   int page_shift;
   int group_shift;    // log2(query heads per KV head), -1 if that is not a power of two
   int num_wgs;        // persistent work-groups launched
-  int xcds;           // work-group x runs on XCD x % xcds (1: no such structure is assumed)
+  int xcds;           // work-group x runs on XCD x % xcds (a power of two; 1: no such structure is assumed)
+  int xcd_shift;      // log2(xcds)
   int reuse;          // != 0: some sequence has several row blocks, i.e. its K/V tiles are read by several items
   int min_share;      // automatic shares are never smaller than this many tiles
   int fixed_share;    // > 0: tiles per work-group asked for by the caller
@@ -136,6 +137,7 @@ struct MfmaSched {
   unsigned short* part_acc;   // [2 * num_wgs][ROWS_WG][D] fp16: the un-normalised output row divided by its largest magnitude
   float* part_ml;             // [2 * num_wgs][ROWS_WG][4]: running maximum (base 2), row sum, that largest magnitude, unused
   int rt_max;         // row blocks of the largest sequence
+  int alone;          // 1: whatever the lengths, pieces of at most MF_ALONE tiles on num_wgs / 2 work-groups hold every item
   int by_item;        // != 0: the combine entries are indexed by item, else by share
   int rows_first;     // != 0: the combine kernel's grid runs over the row blocks of an item first
   // Combine entries [num_wgs + 1].
@@ -224,12 +226,21 @@ __device__ __forceinline__ unsigned lds_offset(const void* p) {
   return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
 }
 
-// Tiles of one item of this sequence, and how many items (heads x row blocks) it has.
+// Tiles of one item of this sequence, its row blocks, and how many items (heads x row blocks) it has.
+__device__ __forceinline__ int seq_row_blocks(const AttnParams& p, const SeqInfo& s, int rows_wg) {
+  return s.n <= 0 ? 0 : (int)((unsigned)(s.n * p.G + rows_wg - 1) / (unsigned)rows_wg);
+}
 __device__ __forceinline__ void seq_shape(const AttnParams& p, const SeqInfo& s, int rows_wg, int& tiles, int& items) {
   if (s.n <= 0) { tiles = 0; items = 0; return; }
   tiles = (s.L + MF_TK - 1) / MF_TK + (s.n + MF_TK - 1) / MF_TK;
-  items = p.Hkv * ((s.n * p.G + rows_wg - 1) / rows_wg);
+  items = p.Hkv * seq_row_blocks(p, s, rows_wg);
 }
+
+// x / d with inv = inverse(d), for 0 <= x, x / d < 1024 and d <= 1024: (x + 1/2) inv is within 2^-12 of (x + 1/2) / d (two roundings of at most 2^-23
+// of it), which is at least 2^-11 away from every whole number.  An integer division is some 35 dependent instructions, and what
+// precedes a call's first tile, or its combine kernel's loads, consists of little else.
+__device__ __forceinline__ float inverse(int d) { return __builtin_amdgcn_rcpf((float)d); }
+__device__ __forceinline__ int small_div(int x, float inv) { return (int)(((float)x + 0.5f) * inv); }
 
 // Work units of one item with `tiles` tiles.  The line of work is cut into shares of equal
 // *time*, not of equal tile count: beginning an item (new query rows, new page list, the merge
@@ -433,13 +444,14 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
   }
   const int tiles_all = wave_total(T * I), items_all = wave_total(I);
   if (tiles_all == 0) { ps.W_eff = 0; if (bad && threadIdx.x < 64) flag_status(p.status, bad); return true; }
-  const int s0 = max(sc_.min_piece, (tiles_all + sc_.num_wgs - 1) / sc_.num_wgs);
+  const int s0 = max(sc_.min_piece, (int)((unsigned)(tiles_all + sc_.num_wgs - 1) / (unsigned)sc_.num_wgs));
   const int line = max(sc_.min_share, (tiles_all + mf_start_cost(MAXRB) * items_all + sc_.num_wgs - 1) / sc_.num_wgs);
   // size up to which pieces are cut (!SINGLE); up to num_wgs / 2 items: a quarter above a share, head dim 64, where a work-group alone on
   // its compute unit gains less, a sixteenth (fill_sched)
   const int slack = 2 * items_all <= sc_.num_wgs ? max(MF_PIECE_SLACK, line / (p.D == 64 ? 16 : 4)) : MF_PIECE_SLACK;
   const int longest = max(line + slack, sc_.min_piece);
-  auto pieces_at = [&](int c) { return wave_total(I * (int)((unsigned)(T + c - 1) / (unsigned)c)); };
+  auto cuts = [&](int c) { return (int)((unsigned)(T + c - 1) / (unsigned)c); };
+  auto pieces_at = [&](int c) { return wave_total(I * cuts(c)); };
   int size = 0;
   // One piece per compute unit where that takes at most MF_ALONE tiles each: pieces half as long on both work-groups of a CU
   // begin, store and are merged twice as often.  us a call, two per CU -> one: 128 rows, 24 items of 34 tiles 18.3 -> 17.4 (a step
@@ -450,8 +462,8 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
     // The smallest of the sizes s0 + i step that fits the launch: the larger, the fewer pieces.  Six sums over the sequences at
     // most; every size tried against every sequence took a call that plans for itself 7 us at 64 sequences (48 sequences of
     // 1000..3000 keys, cut along the line in the end: 88.7 -> 83.3 us; 64 of 900..1000 in pieces: 58.0 -> 52.6).
-    const int step = s0 / 63 + 1;
-    int lo = 0, hi = SINGLE ? (s0 + step - 1) / step : min(63, (longest - s0) / step);      // (2 s0 fits while items <= num_wgs / 2)
+    const int step = s0 < 63 ? 1 : s0 / 63 + 1;
+    int lo = 0, hi = SINGLE ? (step == 1 ? s0 : (s0 + step - 1) / step) : min(63, (longest - s0) / step);      // (2 s0 fits while items <= num_wgs / 2)
     if (pieces_at(s0 + hi * step) > sc_.num_wgs) return false;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
@@ -461,7 +473,7 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
   }
   if (!SINGLE && size > longest) return false;
   if (bad && threadIdx.x < 64) flag_status(p.status, bad);
-  const int RT = I / p.Hkv, S = (T + size - 1) / size, per = RT * S;
+  const int RT = seq_row_blocks(p, s, ROWS_WG), S = cuts(size), per = RT * S;
   ps.W_eff = wave_total(I * S);
   // Which piece a work-group takes: neighbours on one XCD, as on the line.  Every work-group holds one piece however short it is, so
   // lists of equally many pieces are not lists of equally many tiles, and where lengths differ:
@@ -474,7 +486,7 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
   //   else   runs, unless they leave an XCD more than a quarter above the average (one sequence much longer than the others: half
   //     of the XCDs had nothing but its pieces): then in turn, every compute unit gets some of both.
   // Even batches stay in runs (24 sequences of 2048 keys, 32 rows 50.2, in lists 51.3).
-  const bool lists = p.Hkv % sc_.xcds == 0 && 16ll * tiles_all < 15ll * ps.W_eff * size;
+  const bool lists = (p.Hkv & (sc_.xcds - 1)) == 0 && 16ll * tiles_all < 15ll * ps.W_eff * size;
   const int n = lists ? per : I * S;               // this lane's pieces in a list, or in all; lo: those before them
   int lo, P = ps.W_eff;
   if (lists) {
@@ -486,8 +498,8 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
     lo = (shift == 0 ? 0 : shift == 10 ? n0 : n0 + n1) + (sums >> shift & 1023) - n;
   } else lo = wave_incl_scan(n) - n;
   const int hi = lo + n;
-  const int xcd = pw % sc_.xcds, place = pw / sc_.xcds, half = sc_.num_wgs / sc_.xcds / FD_WGS_PER_CU;
-  const int chunk = (ps.W_eff + sc_.xcds - 1) / sc_.xcds;                 // (lists: P pieces for each head of the XCD)
+  const int xcd = pw & (sc_.xcds - 1), place = pw >> sc_.xcd_shift, half = (sc_.num_wgs >> sc_.xcd_shift) / FD_WGS_PER_CU;
+  const int chunk = (ps.W_eff + sc_.xcds - 1) >> sc_.xcd_shift;                 // (lists: P pieces for each head of the XCD)
   ps.w = place >= chunk ? ps.W_eff : xcd * chunk + (lists && place >= half ? chunk - 1 - (place - half) : place);
   if (!lists && !sc_.reuse && 4ll * tiles_all < 3ll * ps.W_eff * size) {           // (many pieces are far shorter than the longest)
     const float mean = S > 0 ? (float)T / (float)S : 0.f;          // tiles of a piece of this lane's sequence
@@ -504,7 +516,7 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
     if (most * (float)sc_.xcds > 1.25f * (float)tiles_all) ps.w = pw;
   }
   if (ps.w >= ps.W_eff) return true;
-  ps.head = lists ? ps.w / P : 0;
+  ps.head = lists ? small_div(ps.w, inverse(P)) : 0;
   const int q = ps.w - ps.head * P;
   const int at = __ffsll((long long)__ballot(lo <= q && q < hi)) - 1;
   if (at < 0) return true;                                         // cannot happen
@@ -513,14 +525,15 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
   ws.v = from(s.v); ws.nb = from(s.nb); ws.page0 = from(s.page0); ws.npages = from(s.npages);
   const int Ts = from(T), Ss = from(S), per_s = from(per);
   int local = q - from(lo);
-  if (!lists) { ps.head = local / per_s; local -= ps.head * per_s; }
+  if (!lists) { ps.head = small_div(local, inverse(per_s)); local -= ps.head * per_s; }
   ps.seq = at; ps.pieces = Ss;
-  ps.rt = local / Ss;
+  const float inv_s = inverse(Ss);
+  ps.rt = small_div(local, inv_s);
   const int j = local - ps.rt * Ss;
   // piece j: tiles [floor(j T / S), floor((j + 1) T / S)), in 32 bits: T = a S + b
-  const int a = Ts / Ss, b = Ts - a * Ss;
-  ps.tile0 = j * a + (j * b) / Ss;
-  ps.nt = (j + 1) * a + ((j + 1) * b) / Ss - ps.tile0;
+  const int a = (int)((unsigned)Ts / (unsigned)Ss), b = Ts - a * Ss;
+  ps.tile0 = j * a + small_div(j * b, inv_s);
+  ps.nt = (j + 1) * a + small_div((j + 1) * b, inv_s) - ps.tile0;
   has_piece = true;
   return true;
 }
@@ -906,15 +919,15 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
     // one piece of an item cut by find_piece (clamped again: a plan entry is not trusted with an access)
     if (T <= 0) return;
     cur.s = ws; cur.seq = seq; cur.T = T;
-    cur.head = clampi(ps.head, 0, p.Hkv - 1); cur.rt = clampi(ps.rt, 0, I / p.Hkv - 1);
+    cur.head = clampi(ps.head, 0, p.Hkv - 1); cur.rt = clampi(ps.rt, 0, seq_row_blocks(p, ws, ROWS_WG) - 1);
     cur.tile0 = clampi(ps.tile0, 0, T - 1); cur.nt = clampi(ps.nt, 1, T - cur.tile0);
     cur.n_ct_all = (ws.L + MF_TK - 1) / MF_TK;
     cur.kh = Kc + (long long)cur.head * p.sh; cur.vh = Vc + (long long)cur.head * p.sh;
     cur.pi = p.page_indices + ws.page0;
     g = g1;                                       // nothing after it
   } else if (!next_piece(cur)) return;
-  Lane ln = make_lane(cur);
   if (!PLANNED) start_ids(cur, nid0, nid1);       // (a plan entry brings the first piece's page ids with it)
+  Lane ln = make_lane(cur);
   start_loads(cur, ln, nid0, nid1, !FD_DEFER_T1);
 #if FD_DEFER_T1
   // Every work-group starts at the same moment: with two tiles each in the first burst (33 MB) the memory
@@ -1407,14 +1420,17 @@ __global__ __launch_bounds__(256) void attn_mfma_combine_kernel(AttnParams p, Mf
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15;
   const int pg = PG == 1 ? 0 : lane >> 4;                      // piece group
+  // by item: (head and row block, sequence, row block of sixteen), or with rows_first the last one first
   const bool rows_first = PG == 1 && sc_.rows_first;
-  const int entry = rows_first ? blockIdx.y : blockIdx.x, row_block = rows_first ? blockIdx.x : blockIdx.y;
+  const int bx = rows_first ? blockIdx.y : blockIdx.x, seq = rows_first ? blockIdx.z : blockIdx.y;
+  const int row_block = rows_first ? blockIdx.x : sc_.by_item ? blockIdx.z : blockIdx.y;
+  const int entry = sc_.by_item ? seq * p.Hkv * sc_.rt_max + bx : bx;
   const int4* ep4 = sc_.entries + entry;
   const int* ep = reinterpret_cast<const int*>(ep4);
   int row0, head, rt, rows_here, first_slot, wl;
   if (sc_.by_item) {
-    const int sh = entry / sc_.rt_max, seq = sh / p.Hkv;
-    rt = entry - sh * sc_.rt_max; head = sh - seq * p.Hkv;
+    head = sc_.rt_max == 1 ? bx : bx / sc_.rt_max;
+    rt = bx - head * sc_.rt_max;
     first_slot = sload(ep, 0); wl = sload(ep, 1);
     const int r0 = sload(p.row_indptr, seq), r1 = sload(p.row_indptr, seq + 1);          // (clamped as load_seq does)
     row0 = clampi(r0, 0, p.total_rows);
@@ -1434,7 +1450,7 @@ __global__ __launch_bounds__(256) void attn_mfma_combine_kernel(AttnParams p, Mf
   if (wf >= wl) return;
   if (trow >= rows_here || l16 >= MF_D / 8) return;           // (head dim 64: half of the lanes have no column)
   const int T_row = rt * ROWS_WG + trow;
-  const int nn = T_row / p.G, hq = head * p.G + T_row % p.G;
+  const int nn = sc_.group_shift >= 0 ? T_row >> sc_.group_shift : T_row / p.G, hq = head * p.G + (T_row - nn * p.G);
   if (row0 + nn >= p.total_rows) return;
   const int np = wl - wf + 1;                      // pieces: slot first_slot, then 2 (wf + 1) .. 2 wl
   auto ml_of = [&](int pi) -> const f32x4* {               // (max, sum, scale, -)
@@ -1560,6 +1576,9 @@ static void fill_sched(const AttnParams& p, void* workspace, int kv_chunk, MfmaS
   for (int b = 0; b < 16; ++b) if ((1 << b) == p.G) sc.group_shift = b;
   sc.num_wgs = attn_mfma_num_wgs();
   sc.xcds = sc.num_wgs % FD_XCDS == 0 ? FD_XCDS : 1;
+  static_assert((FD_XCDS & (FD_XCDS - 1)) == 0, "XCDs are counted by shifts");
+  sc.xcd_shift = 0;
+  while ((1 << sc.xcd_shift) < sc.xcds) ++sc.xcd_shift;
   sc.min_share = 2;
   sc.fixed_share = kv_chunk > 0 ? (kv_chunk + MF_TK - 1) / MF_TK : 0;
   rows_wg = attn_mfma_rows_per_wg(p.max_new_rows * p.G > 128 ? 128 : p.max_new_rows * p.G);
@@ -1580,6 +1599,9 @@ static void fill_sched(const AttnParams& p, void* workspace, int kv_chunk, MfmaS
   // Pieces of one tile only where an item has at most eight (one pass of the combine kernel): 1 x 300 keys 11.8 -> 10.7 us;
   // 1 x 2048 keys, 33 tiles: 14.6 us in twos, 16.0 one by one, 15.6 in threes.
   sc.min_piece = p.max_kv_len <= 7 * MF_TK && p.max_new_rows <= MF_TK ? 1 : 2;
+  // (the smallest size that find_piece tries is at most MF_ALONE: num_wgs / 2 pieces of five tiles are 2.5 num_wgs tiles)
+  const long long tiles_max = ((long long)p.max_kv_len + MF_TK - 1) / MF_TK + (p.max_new_rows + MF_TK - 1) / MF_TK;
+  sc.alone = sc.by_piece == 2 && items_max * ((tiles_max + MF_ALONE - 1) / MF_ALONE) <= sc.num_wgs / 2 ? 1 : 0;
   size_t off_ml, off_en, off_pl;
   attn_mfma_workspace(sc.num_wgs, rows_wg, &off_ml, &off_en, &off_pl);
   char* base = reinterpret_cast<char*>(workspace);
@@ -1588,6 +1610,9 @@ static void fill_sched(const AttnParams& p, void* workspace, int kv_chunk, MfmaS
   sc.entries = reinterpret_cast<int4*>(base + off_en);
   sc.plan = reinterpret_cast<PlanEntry*>(base + off_pl);
 }
+
+// Work-groups that can have a share (1 x 2048 keys, 16 rows, 11.4 -> 11.2 us a planned call; 4 x 500..1000 12.3 -> 12.0).
+static int launch_wgs(const MfmaSched& sc) { return sc.alone ? sc.num_wgs / FD_WGS_PER_CU : sc.num_wgs; }
 
 // The streaming kernel's LDS request is above the default limit: raised once per device.
 template <int MAXRB, bool PLANNED, int DH, int CUT>
@@ -1608,8 +1633,8 @@ static hipError_t configure_mfma() {
 hipError_t run_attn_mfma_plan(const AttnParams& p, void* workspace, int kv_chunk, hipStream_t st) {
   MfmaSched sc; int rows_wg;
   fill_sched(p, workspace, kv_chunk, sc, rows_wg);
-  if (rows_wg == 64) hipLaunchKernelGGL(attn_mfma_plan_kernel<2>, dim3(sc.num_wgs), dim3(MF_BLOCK), 0, st, p, sc);
-  else hipLaunchKernelGGL(attn_mfma_plan_kernel<4>, dim3(sc.num_wgs), dim3(MF_BLOCK), 0, st, p, sc);
+  if (rows_wg == 64) hipLaunchKernelGGL(attn_mfma_plan_kernel<2>, dim3(launch_wgs(sc)), dim3(MF_BLOCK), 0, st, p, sc);
+  else hipLaunchKernelGGL(attn_mfma_plan_kernel<4>, dim3(launch_wgs(sc)), dim3(MF_BLOCK), 0, st, p, sc);
   return hipGetLastError();
 }
 
@@ -1617,7 +1642,7 @@ template <int MAXRB, bool PLANNED, int DH, int CUT>
 static hipError_t launch_mfma_c(const AttnParams& p, const MfmaSched& sc, hipStream_t st) {
   hipError_t e = configure_mfma<MAXRB, PLANNED, DH, CUT>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_mfma_kernel<MAXRB, PLANNED, DH, CUT>), dim3(sc.num_wgs), dim3(MF_BLOCK), (MfTileLds<MAXRB, DH>::BYTES), st, p, sc);
+  hipLaunchKernelGGL((attn_mfma_kernel<MAXRB, PLANNED, DH, CUT>), dim3(launch_wgs(sc)), dim3(MF_BLOCK), (MfTileLds<MAXRB, DH>::BYTES), st, p, sc);
   return hipGetLastError();
 }
 template <int MAXRB, bool PLANNED, int DH>
@@ -1641,9 +1666,10 @@ hipError_t run_attn_mfma(const AttnParams& p, void* workspace, int kv_chunk, boo
 }
 
 template <int MAXRB, int PG>
-static void launch_combine(const AttnParams& p, const MfmaSched& sc, int items, hipStream_t st) {
+static void launch_combine(const AttnParams& p, const MfmaSched& sc, hipStream_t st) {
   const int row_blocks = 32 * MAXRB * PG / 16;
-  const dim3 grid = PG == 1 && sc.rows_first ? dim3(row_blocks, items) : dim3(sc.by_item ? items : sc.num_wgs, row_blocks);
+  const int per_seq = p.Hkv * sc.rt_max;
+  const dim3 grid = PG == 1 && sc.rows_first ? dim3(row_blocks, per_seq, p.B) : sc.by_item ? dim3(per_seq, p.B, row_blocks) : dim3(sc.num_wgs, row_blocks);
   if (p.D == 64) hipLaunchKernelGGL((attn_mfma_combine_kernel<MAXRB, 64, PG>), grid, dim3(256), 0, st, p, sc);
   else hipLaunchKernelGGL((attn_mfma_combine_kernel<MAXRB, 128, PG>), grid, dim3(256), 0, st, p, sc);
 }
@@ -1656,8 +1682,8 @@ hipError_t run_attn_mfma_combine(const AttnParams& p, void* workspace, hipStream
   // four lane groups per row while that gives at most 1024 blocks: 8 items of 64 rows, 18 pieces: call 15.9 -> 14.7 us;
   // 24 of 128 rows: 33.3 -> 33.0; 32 of 128 rows, 17 pieces: equal; 128 of 64 rows, 5 pieces: 38.9 -> 40.3
   const bool spread = sc.by_item && items * rows_wg <= 4096;
-  if (rows_wg == 64) spread ? launch_combine<2, 4>(p, sc, items, st) : launch_combine<2, 1>(p, sc, items, st);
-  else spread ? launch_combine<4, 4>(p, sc, items, st) : launch_combine<4, 1>(p, sc, items, st);
+  if (rows_wg == 64) spread ? launch_combine<2, 4>(p, sc, st) : launch_combine<2, 1>(p, sc, st);
+  else spread ? launch_combine<4, 4>(p, sc, st) : launch_combine<4, 1>(p, sc, st);
   return hipGetLastError();
 }
 

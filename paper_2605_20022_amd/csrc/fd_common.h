@@ -124,10 +124,11 @@ __device__ __forceinline__ SeqInfo load_seq_t(const AttnParams& p, int i, uint32
   }
   s.page0 = pg0 < 0 ? 0 : pg0;
   s.npages = pg1 - s.page0 < 0 ? 0 : pg1 - s.page0;
-  int need = (s.L + p.page_size - 1) / p.page_size;
-  if (list_bad || need > s.npages) {      // page list shorter than kv_len claims
+  // ceil(L / page_size) > npages, without the division
+  if (list_bad || s.L > (long long)s.npages * p.page_size) {      // page list shorter than kv_len claims
     bad |= FD_DEV_PAGE_RANGE;
-    s.L = s.npages * p.page_size < s.L ? s.npages * p.page_size : s.L;
+    const long long cap = (long long)s.npages * p.page_size;
+    s.L = cap < s.L ? (int)cap : s.L;
   }
   if (SCALAR && bad) flag_status(p.status, bad);
   if (bad_out) *bad_out = bad;
@@ -145,7 +146,7 @@ __device__ __forceinline__ void clamp_seq(const AttnParams& p, SeqInfo& s) {
   s.n = clampi(s.n, 0, p.max_new_rows < p.total_rows - s.row0 ? p.max_new_rows : p.total_rows - s.row0);
   s.k = clampi(s.k, 0, s.n);
   s.v = clampi(s.v, 0, s.k);
-  if (s.nb < 1 || (s.n - s.k) % s.nb) s.nb = 1;
+  if (s.nb < 1 || (s.nb != 1 && (s.n - s.k) % s.nb)) s.nb = 1;
   s.page0 = clampi(s.page0, 0, p.page_entries);
   s.npages = clampi(s.npages, 0, p.page_entries - s.page0);
   const long long cap = (long long)s.npages * p.page_size;
@@ -159,8 +160,11 @@ struct RowWindow { int vr, lo, hi; };
 __device__ __forceinline__ RowWindow row_window(int r, const SeqInfo& s) {
   RowWindow w;
   if (r < s.k) { w.vr = r + 1; w.lo = 0; w.hi = 0; return w; }
-  const int mb = (s.n - s.k) / s.nb;                // >= 1 whenever a mask row exists
-  const int b = (r - s.k) / (mb > 0 ? mb : 1);
+  int mb = s.n - s.k, b = 0;                        // rows of a block (>= 1 whenever a mask row exists), and which block r is in
+  if (s.nb != 1) {
+    mb = mb / s.nb;
+    b = (r - s.k) / (mb > 0 ? mb : 1);
+  }
   w.vr = s.v + b < s.k ? s.v + b : s.k;
   w.lo = s.k + b * mb;
   w.hi = w.lo + mb;

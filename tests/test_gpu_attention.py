@@ -301,6 +301,9 @@ def test_one_sequence_much_longer_than_the_others(fd, lens, Hkv, n, D):
     ([1500, 640], 16, 33, 128),        # two heads per XCD, a last row block of four rows
     ([900, 0, 0, 100], 8, 40, 64),     # sequences without a prefix
     ([600, 200], 24, 4, 128),          # three heads per XCD, fewer pieces than places
+    ([2496, 2496, 2496, 2400], 8, 4, 128),     # 256 pieces of five tiles at most: the largest call on half of the work-groups
+    ([2496, 100, 2496, 2400], 8, 32, 128),     # ... with 128 rows
+    ([2497, 2497, 2497, 2400], 8, 4, 64),      # one tile more: all work-groups
 ])
 def test_lists_of_pieces_per_head(fd, lens, Hkv, n, D):
     """KV heads a multiple of eight and pieces of different lengths: planned and self-planning calls agree bit for bit."""
