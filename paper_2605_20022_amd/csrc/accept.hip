@@ -386,11 +386,27 @@ __global__ __launch_bounds__(ACC_BLOCK) void accept_sample_weights_kernel(
       xd_d = Elem<T>::load(draft + (long long)(r0 + j) * row_stride + d);
       u_d = u_accept[r0 + j];
     }
+    // a lane's first HELD segments are requested together and kept (4 pairs of rows 13.7 -> 12.7 us a call)
+    constexpr int HELD = 4;
+    typedef __attribute__((ext_vector_type(4))) double f64x4;
+    f64x4 st[HELD];
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) st[u] = *reinterpret_cast<const f64x4*>(pr + min(gl + u * SG, nseg - 1) * 4);
     double mt = -INFINITY, md = -INFINITY;
-    for (int sg = gl; sg < nseg; sg += SG) { mt = fmax(mt, pr[sg * 4]); md = fmax(md, pr[sg * 4 + 2]); }
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {               // (the last segment repeated: no matter for a maximum)
+      mt = fmax(mt, st[u][0]); md = fmax(md, st[u][2]);
+      if (gl + u * SG >= nseg) st[u][1] = st[u][3] = 0.0;
+    }
+    for (int sg = gl + HELD * SG; sg < nseg; sg += SG) { mt = fmax(mt, pr[sg * 4]); md = fmax(md, pr[sg * 4 + 2]); }
     mt = row_max(mt); md = row_max(md);
     double zt = 0.0, zd = 0.0;
-    for (int sg = gl; sg < nseg; sg += SG) {
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+      if (st[u][1] > 0.0) zt += st[u][1] * (double)exp_neg((float)(st[u][0] - mt));
+      if (st[u][3] > 0.0) zd += st[u][3] * (double)exp_neg((float)(st[u][2] - md));
+    }
+    for (int sg = gl + HELD * SG; sg < nseg; sg += SG) {
       const double m0 = pr[sg * 4], s0 = pr[sg * 4 + 1], m1 = pr[sg * 4 + 2], s1 = pr[sg * 4 + 3];
       if (s0 > 0.0) zt += s0 * (double)exp_neg((float)(m0 - mt));     // maxima are floats held in doubles: the difference is exact
       if (s1 > 0.0) zd += s1 * (double)exp_neg((float)(m1 - md));
@@ -618,6 +634,7 @@ __global__ __launch_bounds__(ACC_BLOCK) void draft_stats_partial_kernel(
 // ---------------------------------------------------------------------------------------
 constexpr int DS_GROUP = 16;
 constexpr int DS_ROWS = ACC_BLOCK / DS_GROUP;
+constexpr int DS_HELD = 4;
 
 __global__ __launch_bounds__(ACC_BLOCK) void draft_select_epilogue_kernel(
     const float* __restrict__ part_val, const int* __restrict__ part_idx, const double* __restrict__ part_sum,
@@ -633,14 +650,32 @@ __global__ __launch_bounds__(ACC_BLOCK) void draft_select_epilogue_kernel(
   for (int j0 = 0; j0 < k; j0 += DS_ROWS) {                  // k is uniform over the group
     const int j = min(j0 + grp, k - 1);                      // surplus lane groups repeat the last row, unwritten
     const long long base = (long long)(r0 + j) * nseg;
+    // A lane's first DS_HELD segments (all of them up to 655360 logits a row) are requested together: their maxima first, the rest
+    // when the row's maximum is known, was two latencies of memory (8 rows 8.4 -> 7.1 us a call, 480 rows 28.2 -> 27.8).
+    float v[DS_HELD]; int ix[DS_HELD]; double sm[DS_HELD];
+#pragma unroll
+    for (int u = 0; u < DS_HELD; ++u) {
+      const int s = min(gl + u * DS_GROUP, nseg - 1);
+      v[u] = part_val[base + s]; ix[u] = part_idx[base + s]; sm[u] = part_sum[base + s];
+    }
     float m = -INFINITY;
-    for (int s = gl; s < nseg; s += DS_GROUP) m = fmaxf(m, part_val[base + s]);
+#pragma unroll
+    for (int u = 0; u < DS_HELD; ++u) {
+      if (gl + u * DS_GROUP >= nseg) v[u] = -INFINITY;
+      m = fmaxf(m, v[u]);
+    }
+    for (int s = gl + DS_HELD * DS_GROUP; s < nseg; s += DS_GROUP) m = fmaxf(m, part_val[base + s]);
     m = row_max(m);
     int bi = 0x7fffffff; double z = 0.0;
-    for (int s = gl; s < nseg; s += DS_GROUP) {
-      const float v = part_val[base + s];
-      if (v == m) bi = min(bi, part_idx[base + s]);
-      if (v > -INFINITY) z += part_sum[base + s] * (double)exp_neg((v - m) * inv_t);
+#pragma unroll
+    for (int u = 0; u < DS_HELD; ++u) {
+      if (v[u] == m && gl + u * DS_GROUP < nseg) bi = min(bi, ix[u]);
+      if (v[u] > -INFINITY) z += sm[u] * (double)exp_neg((v[u] - m) * inv_t);
+    }
+    for (int s = gl + DS_HELD * DS_GROUP; s < nseg; s += DS_GROUP) {
+      const float w = part_val[base + s];
+      if (w == m) bi = min(bi, part_idx[base + s]);
+      if (w > -INFINITY) z += part_sum[base + s] * (double)exp_neg((w - m) * inv_t);
     }
     bi = row_min(bi);
     z = row_sum(z);
