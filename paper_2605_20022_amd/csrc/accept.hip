@@ -6,6 +6,7 @@
 // per sequence merges the segment results and walks the verify rows.
 #include "fd_common.h"
 #include <float.h>
+#include <type_traits>
 
 namespace fd {
 
@@ -191,23 +192,22 @@ __device__ __forceinline__ void amax_merge(float& v, int& i, float ov, int oi) {
 // ---------------------------------------------------------------------------------------
 // Greedy, pass 1: arg-max of one vocabulary segment of one row.
 //   grid (segments, rows); part_val/part_idx [rows][segments]
-// A segment is at most ACC_BLOCK * 8 * ARG_ROUNDS logits, so a lane holds all of its share in
+// A segment is at most ACC_BLOCK * 8 * NR logits (NR <= ARG_ROUNDS rounds), so a lane holds all of its share in
 // registers.  First the segment's maximum (one max per logit), then only the lanes whose own
 // maximum equals it look for the lowest index holding that value: comparing (value, index)
 // pairs logit by logit would cost several times the instructions and bound the kernel by
 // arithmetic rather than by the stream.
 // ---------------------------------------------------------------------------------------
 constexpr int ARG_ROUNDS = 5;
-constexpr int ARG_SEG_MAX = ACC_BLOCK * 8 * ARG_ROUNDS;
 
-template <typename T, bool SHORT>
+template <typename T, int NR, bool SHORT>
 __global__ __launch_bounds__(ACC_BLOCK) void argmax_partial_kernel(
     const T* __restrict__ logits, long long row_stride, int vocab, int seg_len,
     float* __restrict__ part_val, int* __restrict__ part_idx) {
   const int seg = blockIdx.x, row = blockIdx.y, nseg = gridDim.x;
   const T* rp = logits + (long long)row * row_stride;
   const int e0 = seg * seg_len;
-  RowShare<T, ARG_ROUNDS, SHORT> sh(e0, min(vocab, e0 + min(seg_len, ARG_SEG_MAX)));
+  RowShare<T, NR, SHORT> sh(e0, min(vocab, e0 + min(seg_len, NR * ACC_BLOCK * 8)));
   __shared__ float sv[ACC_BLOCK / FD_WAVE]; __shared__ int si[ACC_BLOCK / FD_WAVE];
   sh.request(rp);
   const float m = sh.max();
@@ -582,14 +582,14 @@ __global__ __launch_bounds__(ACC_BLOCK) void accept_sample_pick_kernel(
 // what its probability needs, in one pass with the segment held in registers.
 //   grid (segments, rows); part_val/part_idx/part_sum [rows][segments]
 // ---------------------------------------------------------------------------------------
-template <typename T, bool SHORT>
+template <typename T, int NR, bool SHORT>
 __global__ __launch_bounds__(ACC_BLOCK) void draft_stats_partial_kernel(
     const T* __restrict__ logits, long long row_stride, int vocab, int seg_len, float inv_t,
     float* __restrict__ part_val, int* __restrict__ part_idx, double* __restrict__ part_sum) {
   const int seg = blockIdx.x, row = blockIdx.y, nseg = gridDim.x;
   const T* rp = logits + (long long)row * row_stride;
   const int e0 = seg * seg_len;
-  RowShare<T, ARG_ROUNDS, SHORT> sh(e0, min(vocab, e0 + min(seg_len, ARG_SEG_MAX)));
+  RowShare<T, NR, SHORT> sh(e0, min(vocab, e0 + min(seg_len, NR * ACC_BLOCK * 8)));
   __shared__ float sv[ACC_BLOCK / FD_WAVE]; __shared__ int si[ACC_BLOCK / FD_WAVE];
   __shared__ double sd[ACC_BLOCK / FD_WAVE];
   sh.request(rp);
@@ -754,6 +754,21 @@ static inline int seg_len_for(int vocab, int nseg) {
   return (l + 7) / 8 * 8;
 }
 
+// The kernel variant for segments of seg_len logits: as many rounds of ACC_BLOCK * 8 logits as cover a segment (<= ARG_ROUNDS); rows of fewer
+// than eight logits have one of their own.  A round beyond the segment's end costs the arithmetic of one that is not (always
+// five rounds / as many as needed, us a call, bf16 rows of 151936: selection over 8 rows 7.1 / 5.9, over 64 11.2 / 9.1; greedy acceptance of 8
+// rows 6.0 / 5.5, of 32 rows of floats 9.4 / 8.5; from 128 rows on five are needed).
+template <typename F> static void with_rounds(int seg_len, int vocab, F&& launch) {
+  if (vocab < 8) { launch(std::integral_constant<int, 1>{}, std::true_type{}); return; }
+  switch ((seg_len + ACC_BLOCK * 8 - 1) / (ACC_BLOCK * 8)) {
+    case 1: launch(std::integral_constant<int, 1>{}, std::false_type{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}, std::false_type{}); break;
+    case 3: launch(std::integral_constant<int, 3>{}, std::false_type{}); break;
+    case 4: launch(std::integral_constant<int, 4>{}, std::false_type{}); break;
+    default: launch(std::integral_constant<int, ARG_ROUNDS>{}, std::false_type{}); break;
+  }
+}
+
 // Sampling workspace layout (all blocks 256-byte aligned), shared by the size query and the launcher.
 struct SampleLayout {
   size_t part, row_stats, chunk_res, chunk_p, decision, total;
@@ -791,8 +806,10 @@ static hipError_t launch_greedy(const T* logits, long long row_stride, int vocab
   float* pv = reinterpret_cast<float*>(ws);
   int* pi = reinterpret_cast<int*>(pv + (size_t)(total_rows > 0 ? total_rows : 1) * nseg);
   if (total_rows > 0)
-    hipLaunchKernelGGL((vocab < 8 ? argmax_partial_kernel<T, true> : argmax_partial_kernel<T, false>), dim3(nseg, total_rows), dim3(ACC_BLOCK), 0, st,
-                       logits, row_stride, vocab, sl, pv, pi);
+    with_rounds(sl, vocab, [&](auto nr, auto is_short) {
+      hipLaunchKernelGGL((argmax_partial_kernel<T, decltype(nr)::value, decltype(is_short)::value>), dim3(nseg, total_rows), dim3(ACC_BLOCK), 0, st,
+                         logits, row_stride, vocab, sl, pv, pi);
+    });
   if (batch > 0)
     hipLaunchKernelGGL(accept_greedy_epilogue_kernel, dim3(batch), dim3(ACC_BLOCK), 0, st,
                        pv, pi, nseg, row_indptr, toks, total_rows, max_rows, accept_len, bonus, row_argmax);
@@ -815,18 +832,10 @@ static hipError_t launch_sample(const T* target, const T* draft, long long row_s
   int* decision = reinterpret_cast<int*>(base + lay.decision);
   float inv_t = 1.0f / temperature;
   if (total_rows > 0)
-    switch ((sl + ACC_BLOCK * 8 - 1) / (ACC_BLOCK * 8)) {        // rounds that cover a segment (<= ARG_ROUNDS)
-#define FD_STATS_CASE(NR)                                                                                          \
-      case NR: hipLaunchKernelGGL((softmax_stats_partial_kernel<T, NR, false>), dim3(nseg, total_rows), dim3(ACC_BLOCK), 0, st, \
-                                  target, draft, row_stride, vocab, sl, inv_t, part); break;
-      case 1:
-        hipLaunchKernelGGL((vocab < 8 ? softmax_stats_partial_kernel<T, 1, true> : softmax_stats_partial_kernel<T, 1, false>), dim3(nseg, total_rows),
-                           dim3(ACC_BLOCK), 0, st, target, draft, row_stride, vocab, sl, inv_t, part); break;
-      FD_STATS_CASE(2) FD_STATS_CASE(3) FD_STATS_CASE(4)
-      default: hipLaunchKernelGGL((softmax_stats_partial_kernel<T, ARG_ROUNDS, false>), dim3(nseg, total_rows), dim3(ACC_BLOCK), 0, st,
-                                  target, draft, row_stride, vocab, sl, inv_t, part); break;
-#undef FD_STATS_CASE
-    }
+    with_rounds(sl, vocab, [&](auto nr, auto is_short) {
+      hipLaunchKernelGGL((softmax_stats_partial_kernel<T, decltype(nr)::value, decltype(is_short)::value>), dim3(nseg, total_rows), dim3(ACC_BLOCK), 0, st,
+                         target, draft, row_stride, vocab, sl, inv_t, part);
+    });
   if (batch > 0) {
     int groups = (nchunks + (ACC_BLOCK / FD_WAVE) - 1) / (ACC_BLOCK / FD_WAVE);
     int want = (1024 + batch - 1) / batch;
@@ -860,8 +869,10 @@ static hipError_t launch_draft_select(const T* logits, long long row_stride, int
   double* pd = reinterpret_cast<double*>(base + align256(slots * sizeof(float)) + align256(slots * sizeof(int)));
   const float inv_t = 1.0f / temperature;
   if (total_rows > 0)
-    hipLaunchKernelGGL((vocab < 8 ? draft_stats_partial_kernel<T, true> : draft_stats_partial_kernel<T, false>), dim3(nseg, total_rows), dim3(ACC_BLOCK), 0, st,
-                       logits, row_stride, vocab, sl, inv_t, pv, pi, pd);
+    with_rounds(sl, vocab, [&](auto nr, auto is_short) {
+      hipLaunchKernelGGL((draft_stats_partial_kernel<T, decltype(nr)::value, decltype(is_short)::value>), dim3(nseg, total_rows), dim3(ACC_BLOCK), 0, st,
+                         logits, row_stride, vocab, sl, inv_t, pv, pi, pd);
+    });
   if (batch > 0)
     hipLaunchKernelGGL(draft_select_epilogue_kernel, dim3(batch), dim3(ACC_BLOCK), 0, st, pv, pi, pd, nseg, inv_t,
                        threshold, row_indptr, total_rows, max_rows, tokens, confidence, keep_len);

@@ -90,6 +90,33 @@ def test_row_shares_end_anywhere(fd, dtype, V):
     compare_sampling(acc, bon, o_acc, o_bon, info, indptr, *ref[:2], toks, ua, ur, 0.8)
 
 
+@pytest.mark.parametrize("V", [1500, 4000, 9001, 16001, 20001])          # segments of one, two, three, four and five rounds
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_many_rows_take_longer_segments(fd, dtype, V):
+    """1100 rows: two segments a row at most, as many rounds of 2048 logits as a segment has."""
+    rng = np.random.default_rng(V + 1)
+    ks = np.tile([11, 0, 16, 17], 25)
+    indptr = np.concatenate([[0], np.cumsum(ks)]).astype(np.int32)
+    R = int(indptr[-1])
+    vals = (rng.standard_normal((R, V)) * 2).astype(np.float32)
+    vals[::5, V - 1] = 11.0                                  # the row's last logit
+    vals[1::5, V // 2 - 1] = 11.0                            # about where the second segment begins
+    logits = W.f32_to_bf16_bits(vals) if dtype == "bf16" else vals
+    _, _, am = oc.accept_greedy(logits, indptr, np.zeros(R, dtype=np.int64))
+    toks = rng.integers(0, V, size=R)
+    agree = rng.random(R - 1) < 0.8
+    toks[1:][agree] = am[:-1][agree]
+    _greedy_case(fd, logits, indptr, toks.astype(np.int32))
+    _draft_select_case(fd, logits, indptr, 0.9, 0.2)
+    dv = (vals + 0.6 * rng.standard_normal(vals.shape)).astype(np.float32)
+    draft = W.f32_to_bf16_bits(dv) if dtype == "bf16" else dv
+    tk = rng.integers(0, V, size=R).astype(np.int32)
+    ua, ur = rng.random(R, dtype=np.float32), rng.random(R, dtype=np.float32)
+    o_acc, o_bon, info = oc.accept_sample(logits, draft, indptr, tk, ua, ur, 0.9)
+    acc, bon = run_sample(fd, logits, draft, indptr, tk, ua, ur, 0.9)
+    compare_sampling(acc, bon, o_acc, o_bon, info, indptr, logits, draft, tk, ua, ur, 0.9)
+
+
 def test_cfg3_greedy_vocab_151936(fd):
     w, a = W.CONFIGS["cfg3"]
     lens = W.make_lengths(w)
