@@ -139,7 +139,6 @@ struct MfmaSched {
   int rt_max;         // row blocks of the largest sequence
   int alone;          // 1: whatever the lengths, pieces of at most MF_ALONE tiles on num_wgs / 2 work-groups hold every item
   int by_item;        // != 0: the combine entries are indexed by item, else by share
-  int rows_first;     // != 0: the combine kernel's grid runs over the row blocks of an item first
   // Combine entries [num_wgs + 1].
   //   by share  entry w: the split item that ends in the work-group of share w: (first packed row, head | row block << 16,
   //             tile rows, first slot); first < 0: none.  Entry num_wgs: (shares in use, -, -, -)
@@ -1405,10 +1404,12 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
 // The pieces of an item sit in its first slot, then in the first slot (2w) of every later
 // work-group up to the one it ended in.  Sixteen lanes per tile row, a lane owns eight adjacent
 // output columns; PG sixteen-lane groups share a row and take every PG-th piece.
-//   grid (items or shares, ROWS_WG PG / 16), with rows_first the other way round: an item's row blocks then lie on different
-//   XCDs.  In a grid of 256 items they lie 256 blocks apart, on the same compute unit: with eight long items of some 40 pieces among 248
-//   short ones 12.4 us, the other way round 7.2 (head dim 64 15.2 and 7.1).  With fewer items it makes no difference, but for
-//   eight in all (3.8 us as it is, 4.4 the other way round), and more of them are worse off (360 along the line 5.1 and 6.6).
+//   grid by item (KV heads, row blocks of 16 / PG rows, sequences), by share (shares, row blocks).  By item a head's blocks run on the
+//   XCD of the head, whose L2 holds the partials where the pieces are cut in lists per head or one sequence is all there is, and the
+//   next call's stores find them there; the row blocks of an item follow one another and go to different compute units.
+//   us a call, items first / now: 1 sequence of 2048 keys and 72 rows 18.2 / 16.5 (streaming kernel 14.4 / 13.2, this one 5.0 / 4.4), 16 of
+//   512..4096 at head dim 64 22.8 / 21.8, 4 of 500..1000 12.05 / 11.8; eight long items of some 40 pieces among 248 short ones equal
+//   (their row blocks 256 blocks apart, on one compute unit: 5 us more).
 // A block that finds nothing to merge costs as much as its launch, and the kernel follows another one on
 // the stream: with few items (entries by item) the grid holds one group of blocks per item that can
 // exist instead of one per share (8 items in a 512-share launch: call 17.9 -> 15.9 us; 24 items of 128 rows: 35.4 -> 33.3).
@@ -1420,17 +1421,14 @@ __global__ __launch_bounds__(256) void attn_mfma_combine_kernel(AttnParams p, Mf
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15;
   const int pg = PG == 1 ? 0 : lane >> 4;                      // piece group
-  // by item: (head and row block, sequence, row block of sixteen), or with rows_first the last one first
-  const bool rows_first = PG == 1 && sc_.rows_first;
-  const int bx = rows_first ? blockIdx.y : blockIdx.x, seq = rows_first ? blockIdx.z : blockIdx.y;
-  const int row_block = rows_first ? blockIdx.x : sc_.by_item ? blockIdx.z : blockIdx.y;
-  const int entry = sc_.by_item ? seq * p.Hkv * sc_.rt_max + bx : bx;
+  constexpr int ROW_BLOCKS = ROWS_WG * PG / 16;
+  const int seq = blockIdx.z, row_block = blockIdx.y % ROW_BLOCKS;            // (by item)
+  const int entry = sc_.by_item ? (seq * p.Hkv + blockIdx.x) * sc_.rt_max + blockIdx.y / ROW_BLOCKS : blockIdx.x;
   const int4* ep4 = sc_.entries + entry;
   const int* ep = reinterpret_cast<const int*>(ep4);
   int row0, head, rt, rows_here, first_slot, wl;
   if (sc_.by_item) {
-    head = sc_.rt_max == 1 ? bx : bx / sc_.rt_max;
-    rt = bx - head * sc_.rt_max;
+    head = blockIdx.x; rt = blockIdx.y / ROW_BLOCKS;
     first_slot = sload(ep, 0); wl = sload(ep, 1);
     const int r0 = sload(p.row_indptr, seq), r1 = sload(p.row_indptr, seq + 1);          // (clamped as load_seq does)
     row0 = clampi(r0, 0, p.total_rows);
@@ -1585,7 +1583,6 @@ static void fill_sched(const AttnParams& p, void* workspace, int kv_chunk, MfmaS
   sc.reuse = (long long)p.max_new_rows * p.G > rows_wg ? 1 : 0;
   sc.rt_max = (int)(((long long)p.max_new_rows * p.G + rows_wg - 1) / rows_wg);
   sc.by_item = (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs ? 1 : 0;
-  sc.rows_first = (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs / 2 ? 1 : 0;
   sc.by_piece = sc.by_item && p.B <= 64 && sc.fixed_share == 0 && sc.num_wgs < 1024 ? 1 : 0;      // (find_piece counts pieces in ten bits)
   const long long items_max = (long long)p.B * p.Hkv * sc.rt_max;
   if (sc.by_piece && items_max <= sc.num_wgs / 2) sc.by_piece = 2;
@@ -1668,8 +1665,7 @@ hipError_t run_attn_mfma(const AttnParams& p, void* workspace, int kv_chunk, boo
 template <int MAXRB, int PG>
 static void launch_combine(const AttnParams& p, const MfmaSched& sc, hipStream_t st) {
   const int row_blocks = 32 * MAXRB * PG / 16;
-  const int per_seq = p.Hkv * sc.rt_max;
-  const dim3 grid = PG == 1 && sc.rows_first ? dim3(row_blocks, per_seq, p.B) : sc.by_item ? dim3(per_seq, p.B, row_blocks) : dim3(sc.num_wgs, row_blocks);
+  const dim3 grid = sc.by_item ? dim3(p.Hkv, sc.rt_max * row_blocks, p.B) : dim3(sc.num_wgs, row_blocks);
   if (p.D == 64) hipLaunchKernelGGL((attn_mfma_combine_kernel<MAXRB, 64, PG>), grid, dim3(256), 0, st, p, sc);
   else hipLaunchKernelGGL((attn_mfma_combine_kernel<MAXRB, 128, PG>), grid, dim3(256), 0, st, p, sc);
 }
