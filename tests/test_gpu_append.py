@@ -66,6 +66,37 @@ def test_append_matches_oracle(fd, dtype, D, ps):
     assert np.array_equal(as_bits(call2.d["k_cache"]), kc)
 
 
+@pytest.mark.parametrize("dtype,Hkv,D,ps", [("bf16", 8, 128, 3), ("f32", 5, 96, 16), ("bf16", 3, 8, 2)])
+def test_append_takes_rows_in_fours(fd, dtype, Hkv, D, ps):
+    """1 .. 13 committed rows (below, at and past a batch of four), pages ending inside a batch, and one page id outside the
+    pool: that page's rows are skipped and reported, the others written."""
+    w = W.AttnWorkload("fours", dtype, 13, Hkv, Hkv, D, ps, (0, 40), (13, 13), 0, 1.0, seed=83, spare_page_frac=0.2)
+    inp = _with_room(W.make_attention_inputs(w), 13)
+    acc = np.arange(13, dtype=np.int32)
+    as_bits = (lambda t: t.view(torch.int16).cpu().numpy().view(np.uint16)) if dtype == "bf16" else (lambda t: t.cpu().numpy())
+    call = AttnCall(fd, inp)
+    new_len = torch.full((13,), -5, dtype=torch.int32, device="cuda")
+    fd.fd_append_kv(call.args, call.d["k_cache"], call.d["v_cache"], torch.from_numpy(acc).cuda(), new_len)
+    torch.cuda.synchronize()
+    ref = oa.append_accepted_kv(inp["k_cache"], inp["v_cache"], inp["k_new"], inp["v_new"], inp["page_indptr"], inp["page_indices"],
+                                inp["kv_len"], inp["row_indptr"], inp["verify_len"], acc, page_size=ps)
+    assert int(call.status.item()) == 0
+    assert np.array_equal(as_bits(call.d["k_cache"]), ref[0]) and np.array_equal(as_bits(call.d["v_cache"]), ref[1])
+    assert np.array_equal(new_len.cpu().numpy(), ref[2])
+    # sequence 12: the page of its sixth committed row is not in the pool
+    call = AttnCall(fd, inp)
+    lp = (int(inp["kv_len"][12]) + 5) // ps
+    call.d["page_indices"][int(inp["page_indptr"][12]) + lp] = 10 ** 6
+    fd.fd_append_kv(call.args, call.d["k_cache"], call.d["v_cache"], torch.from_numpy(acc).cuda(), new_len)
+    torch.cuda.synchronize()
+    assert int(call.status.item()) & 4
+    page = int(inp["page_indices"][int(inp["page_indptr"][12]) + lp])
+    want_k, want_v = ref[0].copy(), ref[1].copy()
+    want_k[page], want_v[page] = inp["k_cache"][page], inp["v_cache"][page]
+    assert np.array_equal(as_bits(call.d["k_cache"]), want_k) and np.array_equal(as_bits(call.d["v_cache"]), want_v)
+    assert np.array_equal(new_len.cpu().numpy(), ref[2])
+
+
 def test_append_reports_bad_device_data(fd):
     w = W.AttnWorkload("appbad", "bf16", 3, 8, 2, 128, 16, (10, 40), (2, 4), 2, 1.0, seed=82)
     inp = W.make_attention_inputs(w)                    # no spare room: kv 10..40 may fill its last page
