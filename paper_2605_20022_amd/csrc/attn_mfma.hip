@@ -1630,8 +1630,9 @@ static hipError_t configure_mfma() {
 hipError_t run_attn_mfma_plan(const AttnParams& p, void* workspace, int kv_chunk, hipStream_t st) {
   MfmaSched sc; int rows_wg;
   fill_sched(p, workspace, kv_chunk, sc, rows_wg);
-  if (rows_wg == 64) hipLaunchKernelGGL(attn_mfma_plan_kernel<2>, dim3(launch_wgs(sc)), dim3(MF_BLOCK), 0, st, p, sc);
-  else hipLaunchKernelGGL(attn_mfma_plan_kernel<4>, dim3(launch_wgs(sc)), dim3(MF_BLOCK), 0, st, p, sc);
+  const dim3 block(sc.by_piece == 2 ? FD_WAVE : MF_BLOCK);         // (a wave finds its piece by itself, a share of the line takes the work-group; 4.4 -> 3.9 us)
+  if (rows_wg == 64) hipLaunchKernelGGL(attn_mfma_plan_kernel<2>, dim3(launch_wgs(sc)), block, 0, st, p, sc);
+  else hipLaunchKernelGGL(attn_mfma_plan_kernel<4>, dim3(launch_wgs(sc)), block, 0, st, p, sc);
   return hipGetLastError();
 }
 
