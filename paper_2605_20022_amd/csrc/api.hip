@@ -233,6 +233,12 @@ static fd_status attn_call(const fd_attn_args* a, void* workspace, size_t worksp
     const unsigned long long magic = ((1ull << (31 + sh)) + d - 1) / d;
     p.page_magic = (unsigned)magic; p.page_magic_shift = sh > 0 ? sh - 1 : 0;
   }
+  // Full-precision kernel: with more than two chunks per compute unit, if all were as long as the longest may be, the device cuts equal pieces (even_pieces says
+  // why from there on); not where 32 tile rows or fewer leave the products aside (4 of 512..2048 keys, 16 rows 24.0 us, in pieces 25.4).
+  const int cus = fd::attn_mfma_num_wgs() / 2;
+  const long long most_chunks = (long long)(a->batch > 0 ? a->batch : 1) * a->num_kv_heads * plan.row_tiles * plan.max_chunks;
+  p.even_cus = !plan.use_mfma && a->kv_chunk == 0 && a->batch <= FD_WAVE && (long long)a->max_new_rows * p.G > 32 && most_chunks > 2 * cus && most_chunks <= 8 * cus &&
+               plan.max_chunks > 2 && plan.max_chunks < 512 && plan.chunk <= 8192 && a->max_new_rows <= 8192 ? cus : 0;      // (quotients that small_div takes)
   p.sm_scale = a->sm_scale > 0.f ? a->sm_scale : 1.0f / sqrtf((float)a->head_dim);
   p.k_cache = a->k_cache; p.v_cache = a->v_cache;
   p.sp = a->cache_stride_page; p.sh = a->cache_stride_head; p.st = a->cache_stride_token;

@@ -42,13 +42,51 @@ __device__ __forceinline__ float quarters_max(float v) {
   return fmaxf(__builtin_bit_cast(float, (unsigned)b[0]), __builtin_bit_cast(float, (unsigned)b[1]));
 }
 
+// Where the longest lengths allow more work-groups of one chunk each than the chip holds at once (AttnParams::even_cus, set on the host),
+// the device deals out the tiles (32 keys; those of the prefix, then those of the new rows) itself: every sequence is cut into equal
+// pieces, at most as many as it has chunks of p.chunk keys, and the pieces are the first work-groups of the launch.
+// A compute unit takes its tiles one after the other whether one work-group holds them or two (some 2.9 us a tile of 64 rows), so a call
+// takes as long as the compute unit with the most of them: rounds of pieces, times tiles of a piece and the one that its partial weighs.  The
+// piece size is the one of four, p.chunk to 7/4 of it, for which that is least.  In a grid over (chunk, head, sequence) the chunks that
+// shorter sequences don't have leave some compute units with three work-groups and others with one.
+// us a call, fp32, 8 KV heads, 64 tile rows, head dim 128, chunks of 128 keys / pieces: 3 sequences of 2992..3583 keys
+// 59.7 / 45.6, 5 of 1036..1997 50.3 / 39.5, 5 of 512..4096 68.4 / 58.8, 16 of 512..2048 105.9 / 85.5, 16 of 2048 125.4 / 106.8, 9 of 1024 55.0 / 44.2;
+// 8 of 500..2000 at head dim 64 34.7 / 30.5, bf16 at head dim 96 49.2 / 40.9; one KV head, 8 of 1000..4000, 512 tile rows 106.3 / 81.4.
+// Up to two work-groups per compute unit the grid is kept: they all start at once, and where lengths differ
+// little (4 of 1400..2000 keys) finding the pieces costs more than it gives, 35.6 / 36.4.
+// Every wave works this out by itself, lane i for sequence i.
+struct EvenPieces { SeqInfo s; uint32_t bad; int T, S, items; };           // of this lane: tiles, pieces of an item, items (heads x row tiles)
+__device__ __forceinline__ EvenPieces even_pieces(const AttnParams& p) {
+  EvenPieces e;
+  const int lane = threadIdx.x & 63;
+  e.s = SeqInfo{}; e.bad = 0; e.T = e.S = e.items = 0;
+  const int c0 = p.chunk / GEN_KEYS;
+  int most = 0;
+  if (lane < p.B) {
+    e.s = load_seq_t<false>(p, lane, &e.bad);
+    e.T = (e.s.L + GEN_KEYS - 1) / GEN_KEYS + (e.s.n + GEN_KEYS - 1) / GEN_KEYS;
+    e.items = p.Hkv * ((e.s.n * p.G + GEN_ROWS - 1) / GEN_ROWS);
+    most = max(1, small_div((e.s.L + GEN_KEYS - 1) / GEN_KEYS + c0 - 1, inverse(c0)));
+  }
+  const float inv_cus = inverse(p.even_cus);
+  int least = 0x7fffffff;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = c0 + (q * c0 + 3) / 4;
+    const int S = min(most, small_div(e.T + c - 1, inverse(c)));
+    const int cost = small_div(wave_total(e.items * S) + p.even_cus - 1, inv_cus) * (c + 1);
+    if (cost < least) { least = cost; e.S = S; }
+  }
+  return e;
+}
+
 int attn_generic_rows_per_wg() { return GEN_ROWS; }
 
 // NDB: head dim in blocks of 16, rounded up to 2, 4, 6 or 8 (the columns beyond D are zero in LDS and in Q).
 // Column of the output block g16 (0 .. NDB - 1) that matrix row m stands for: blocks are taken four
 // at a time (the rest, two, together), column = 64 (g16 / 4) + W m + g16 % 4 with W the group's
 // width, so that a lane's V operands of a group are adjacent in LDS and its outputs adjacent in memory.
-template <typename T, int NDB>
+template <typename T, int NDB, bool EVEN>
 __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p) {
   constexpr int DP = 16 * NDB;                     // padded head dim
   // LDS row pitch: a multiple of 16 bytes that is odd in units of 16, so that the 16 rows one
@@ -60,14 +98,43 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
   constexpr int NG = (NDB + 3) / 4;                // column groups
   __shared__ __attribute__((aligned(16))) float lds[2][2][GEN_KEYS * STR];   // [buffer][K, V]
 
-  // Consecutive work-group ids go to different XCDs; rotating the chunk index by head and
-  // sequence keeps any one XCD from collecting only the long (or only the short) chunks.
-  const int chunk_id = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x;
-  const int g = blockIdx.y % p.Hkv, rt = blockIdx.y / p.Hkv;
-  const SeqInfo s = load_seq(p, blockIdx.z);
-  const int nchunks = max(1, (s.L + p.chunk - 1) / p.chunk);
+  int chunk_id, nchunks, g, rt, tile0, tile1;      // tiles of the sequence: those of its prefix, then those of its new rows
+  SeqInfo s;
+  if (EVEN) {
+    // pieces are numbered (sequence, row tile, head, piece)
+    const EvenPieces e = even_pieces(p);
+    const int w = blockIdx.x;
+    if (w == 0 && threadIdx.x < 64 && e.bad) flag_status(p.status, e.bad);
+    const int hi = wave_incl_scan(e.items * e.S), lo = hi - e.items * e.S;
+    const int at = __ffsll((long long)__ballot(lo <= w && w < hi)) - 1;
+    if (at < 0) return;
+    auto from = [&](int v) { return __builtin_amdgcn_readlane(v, at); };
+    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    s.L = from(e.s.L); s.row0 = from(e.s.row0); s.n = from(e.s.n); s.k = from(e.s.k);
+    s.v = from(e.s.v); s.nb = from(e.s.nb); s.page0 = from(e.s.page0); s.npages = from(e.s.npages);
+    const int tiles = from(e.T);
+    nchunks = from(e.S);
+    const float inv = inverse(nchunks);
+    const int local = w - from(lo), unit = uniform(small_div(local, inv));
+    chunk_id = uniform(local - unit * nchunks);
+    rt = uniform((int)((unsigned)unit / (unsigned)p.Hkv));
+    g = uniform(unit - rt * p.Hkv);
+    const int a = small_div(tiles, inv), b = tiles - a * nchunks;         // (j T / S, with T = a S + b)
+    tile0 = uniform(chunk_id * a + small_div(chunk_id * b, inv));
+    tile1 = uniform((chunk_id + 1) * a + small_div((chunk_id + 1) * b, inv));
+  } else {
+    // Consecutive work-group ids go to different XCDs; rotating the chunk index by head and
+    // sequence keeps any one XCD from collecting only the long (or only the short) chunks.
+    chunk_id = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x;
+    g = blockIdx.y % p.Hkv; rt = blockIdx.y / p.Hkv;
+    s = load_seq(p, blockIdx.z);
+    nchunks = max(1, (s.L + p.chunk - 1) / p.chunk);
+    if (chunk_id >= nchunks) return;
+    tile0 = chunk_id * (p.chunk / GEN_KEYS);
+    tile1 = chunk_id == nchunks - 1 ? (s.L + GEN_KEYS - 1) / GEN_KEYS + (s.n + GEN_KEYS - 1) / GEN_KEYS : tile0 + p.chunk / GEN_KEYS;
+  }
   const int rows_total = s.n * p.G;
-  if (chunk_id >= nchunks || rt * GEN_ROWS >= rows_total) return;
+  if (rt * GEN_ROWS >= rows_total) return;
   const int D = p.D, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l15 = lane & 15, kq = lane >> 4;
   const T* Kc = reinterpret_cast<const T*>(p.k_cache) + (long long)g * p.sh;
@@ -87,11 +154,10 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
   const int my_nn = my_T / p.G, my_hq = g * p.G + my_T % p.G;
   const RowWindow win = row_window(row_valid ? my_nn : 0, s);
 
-  const int c0 = chunk_id * p.chunk;
-  const int c1 = min(s.L, c0 + p.chunk);
-  const int cached_tiles = c1 > c0 ? (c1 - c0 + GEN_KEYS - 1) / GEN_KEYS : 0;
-  const int new_tiles = chunk_id == nchunks - 1 ? (s.n + GEN_KEYS - 1) / GEN_KEYS : 0;
-  const int nt = cached_tiles + new_tiles;
+  const int prefix_tiles = (s.L + GEN_KEYS - 1) / GEN_KEYS;
+  const int c0 = tile0 * GEN_KEYS, c1 = min(s.L, tile1 * GEN_KEYS);
+  const int nt = tile1 - tile0, cached_tiles = max(0, min(prefix_tiles, tile1) - tile0);
+  const int new0 = EVEN ? max(0, tile0 - prefix_tiles) * GEN_KEYS : 0;            // first new key of this work-group's new tiles (chunks: the last has them all)
 
   // key / page_size by a multiplication (AttnParams::page_magic): exact for keys below 2^31
   auto page_of = [&](int key) {
@@ -124,7 +190,7 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
     if (t >= cached_tiles) {
 #pragma unroll
       for (int i = 0; i < NLD; ++i) {
-        const int key = min((t - cached_tiles) * GEN_KEYS + ld_row[i], s.n - 1);
+        const int key = min(new0 + (t - cached_tiles) * GEN_KEYS + ld_row[i], s.n - 1);
         const long long off = (long long)(s.row0 + key) * p.Hkv * D + (ld_col[i] < D ? ld_col[i] : 0);
         rk[i] = *reinterpret_cast<const u32x4*>(Kn + off); rv[i] = *reinterpret_cast<const u32x4*>(Vn + off);
       }
@@ -156,7 +222,7 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
       put(&lds[buf][0][ld_row[i] * STR + ld_col[i]], rk[i]);
       put(&lds[buf][1][ld_row[i] * STR + ld_col[i]], rv[i]);
     }
-    const int rows = t >= cached_tiles ? s.n - (t - cached_tiles) * GEN_KEYS : c1 - c0 - t * GEN_KEYS;     // that exist
+    const int rows = t >= cached_tiles ? s.n - new0 - (t - cached_tiles) * GEN_KEYS : c1 - c0 - t * GEN_KEYS;     // that exist
     if (rows < GEN_KEYS || D < DP) {               // (over what was just written: selecting the values before costs every tile 3 %)
       const u32x4 zero = {0, 0, 0, 0};
 #pragma unroll
@@ -201,7 +267,7 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
   for (int t = 0; t < nt; ++t) {
     if (t + 1 < nt) { load_tile(t + 1); fetch_pages(t + 2); }
     const bool is_new = t >= cached_tiles;
-    const int base = is_new ? (t - cached_tiles) * GEN_KEYS : c0 + t * GEN_KEYS;
+    const int base = is_new ? new0 + (t - cached_tiles) * GEN_KEYS : c0 + t * GEN_KEYS;
     const int end = is_new ? s.n : c1;                                  // keys at or beyond are invisible
     const bool masked = is_new || base + GEN_KEYS > end;
     const float* Ks = lds[t & 1][0];
@@ -209,9 +275,14 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
     auto block = [&](auto nkb_c, int kb0) {        // NKB 16-key blocks from kb0 on
       constexpr int NKB = decltype(nkb_c)::value;
       // K fragments are requested one 16-column step ahead of the matrix instructions that take them
-      f32x4 sc[NKB][2];                            // two accumulation chains per key block
+      // accumulation chains per key block; four with pieces, whose sums over keys are up to 7/4 as long as those of chunks: the error
+      // against 64 bits is then no larger (2-norm, mean of eight calls: chunks 3.36e-7, pieces 3.21e-7, with two chains 3.58e-7; time equal)
+      constexpr int CHAINS = EVEN ? 4 : 2;
+      f32x4 sc[NKB][CHAINS];
 #pragma unroll
-      for (int b = 0; b < NKB; ++b) sc[b][0] = sc[b][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int b = 0; b < NKB; ++b)
+#pragma unroll
+        for (int e = 0; e < CHAINS; ++e) sc[b][e] = f32x4{0.f, 0.f, 0.f, 0.f};
       const float* kp = Ks + (16 * kb0 + l15) * STR + 4 * kq;
       f32x4 kf[2][NKB];
 #pragma unroll
@@ -227,7 +298,7 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
         for (int e = 0; e < 4; ++e)
 #pragma unroll
           for (int b = 0; b < NKB; ++b)
-            sc[b][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j & 1][b][e], q[j][e], sc[b][e & 1], 0, 0, 0);
+            sc[b][e % CHAINS] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j & 1][b][e], q[j][e], sc[b][e % CHAINS], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
       // V fragments likewise, one key step (8 matrix instructions at head dim 128) ahead; the first before the softmax
@@ -250,7 +321,11 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
 #pragma unroll
       for (int b = 0; b < NKB; ++b)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[b][i] = (sc[b][0][i] + sc[b][1][i]) * p.sm_scale;
+        for (int i = 0; i < 4; ++i) {
+          float sum = sc[b][0][i] + sc[b][1][i];
+          if (CHAINS == 4) sum += sc[b][CHAINS - 2][i] + sc[b][CHAINS - 1][i];
+          x[b][i] = sum * p.sm_scale;
+        }
       if (masked) {
         RowWindow wv = win;
         if (!is_new) { wv.vr = end; wv.lo = 0; wv.hi = 0; }             // a prefix tile: the keys below the end
@@ -370,14 +445,15 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
 // 32 lanes per (row, head), a lane owns four columns; grid (ceil(Hq / 8), max_new_rows, B).  The
 // chunks are taken four at a time, their loads issued together, with a running maximum.
 // ---------------------------------------------------------------------------------------
-template <typename T>
+template <typename T, bool EVEN>
 __global__ __launch_bounds__(256) void attn_combine_kernel(AttnParams p) {
   const int seq = blockIdx.z, nn = blockIdx.y;
   const SeqInfo s = load_seq(p, seq);
-  if (nn >= s.n || s.L <= p.chunk) return;         // one chunk: the streaming kernel stored the rows itself
+  int nchunks = (s.L + p.chunk - 1) / p.chunk;
+  if (EVEN) nchunks = __builtin_amdgcn_readlane(even_pieces(p).S, seq);
+  if (nn >= s.n || nchunks <= 1) return;           // one chunk: the streaming kernel stored the rows itself
   const int hq = blockIdx.x * 8 + (threadIdx.x >> 5), d = (threadIdx.x & 31) * 4;
   if (hq >= p.Hq || d >= p.D) return;
-  const int nchunks = (s.L + p.chunk - 1) / p.chunk;
   const long long row = s.row0 + nn;
   const long long stride = (long long)p.total_rows * p.Hq;     // partial slots per chunk
   const long long slot0 = row * p.Hq + hq;
@@ -414,25 +490,31 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnParams p) {
   if (p.lse && d == 0) p.lse[slot0] = M + logf(den);
 }
 
-template <typename T>
+template <typename T, bool EVEN>
 static void launch_generic(const AttnParams& p, hipStream_t st) {
-  dim3 grid(p.max_chunks, p.Hkv * p.row_tiles, p.B);
-  if (p.D <= 32) hipLaunchKernelGGL((attn_generic_kernel<T, 2>), grid, dim3(GEN_BLOCK), 0, st, p);
-  else if (p.D <= 64) hipLaunchKernelGGL((attn_generic_kernel<T, 4>), grid, dim3(GEN_BLOCK), 0, st, p);
-  else if (p.D <= 96) hipLaunchKernelGGL((attn_generic_kernel<T, 6>), grid, dim3(GEN_BLOCK), 0, st, p);
-  else hipLaunchKernelGGL((attn_generic_kernel<T, 8>), grid, dim3(GEN_BLOCK), 0, st, p);
+  const dim3 grid = EVEN ? dim3(p.B * p.Hkv * p.row_tiles * p.max_chunks) : dim3(p.max_chunks, p.Hkv * p.row_tiles, p.B);
+  if (p.D <= 32) hipLaunchKernelGGL((attn_generic_kernel<T, 2, EVEN>), grid, dim3(GEN_BLOCK), 0, st, p);
+  else if (p.D <= 64) hipLaunchKernelGGL((attn_generic_kernel<T, 4, EVEN>), grid, dim3(GEN_BLOCK), 0, st, p);
+  else if (p.D <= 96) hipLaunchKernelGGL((attn_generic_kernel<T, 6, EVEN>), grid, dim3(GEN_BLOCK), 0, st, p);
+  else hipLaunchKernelGGL((attn_generic_kernel<T, 8, EVEN>), grid, dim3(GEN_BLOCK), 0, st, p);
 }
 
 hipError_t run_attn_generic(const AttnParams& p, int dtype, hipStream_t st) {
-  if (dtype == FD_BF16) launch_generic<bf16_t>(p, st);
-  else launch_generic<float>(p, st);
+  if (dtype == FD_BF16) p.even_cus > 0 ? launch_generic<bf16_t, true>(p, st) : launch_generic<bf16_t, false>(p, st);
+  else p.even_cus > 0 ? launch_generic<float, true>(p, st) : launch_generic<float, false>(p, st);
   return hipGetLastError();
 }
 
+template <typename T>
+static void launch_generic_combine(const AttnParams& p, hipStream_t st) {
+  const dim3 grid((p.Hq + 7) / 8, p.max_new_rows, p.B);
+  if (p.even_cus > 0) hipLaunchKernelGGL((attn_combine_kernel<T, true>), grid, dim3(256), 0, st, p);
+  else hipLaunchKernelGGL((attn_combine_kernel<T, false>), grid, dim3(256), 0, st, p);
+}
+
 hipError_t run_attn_combine(const AttnParams& p, int dtype, hipStream_t st) {
-  dim3 grid((p.Hq + 7) / 8, p.max_new_rows, p.B);
-  if (dtype == FD_BF16) hipLaunchKernelGGL(attn_combine_kernel<bf16_t>, grid, dim3(256), 0, st, p);
-  else hipLaunchKernelGGL(attn_combine_kernel<float>, grid, dim3(256), 0, st, p);
+  if (dtype == FD_BF16) launch_generic_combine<bf16_t>(p, st);
+  else launch_generic_combine<float>(p, st);
   return hipGetLastError();
 }
 

@@ -235,12 +235,6 @@ __device__ __forceinline__ void seq_shape(const AttnParams& p, const SeqInfo& s,
   items = p.Hkv * seq_row_blocks(p, s, rows_wg);
 }
 
-// x / d with inv = inverse(d), for 0 <= x, x / d < 1024 and d <= 1024: (x + 1/2) inv is within 2^-12 of (x + 1/2) / d (two roundings of at most 2^-23
-// of it), which is at least 2^-11 away from every whole number.  An integer division is some 35 dependent instructions, and what
-// precedes a call's first tile, or its combine kernel's loads, consists of little else.
-__device__ __forceinline__ float inverse(int d) { return __builtin_amdgcn_rcpf((float)d); }
-__device__ __forceinline__ int small_div(int x, float inv) { return (int)(((float)x + 0.5f) * inv); }
-
 // Work units of one item with `tiles` tiles.  The line of work is cut into shares of equal
 // *time*, not of equal tile count: beginning an item (new query rows, new page list, the merge
 // and the stores of the one before) costs about as much as streaming two tiles, so every item is
@@ -254,19 +248,6 @@ __device__ __forceinline__ long long uniform_ll(long long v) {
   unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)((unsigned long long)v >> 32));
   return (long long)(((unsigned long long)hi << 32) | lo);
 }
-
-// Inclusive scan over the wave, all lanes active.  By the register file's own lane shifts: planning consists of little else, and six trips
-// through LDS (__shfl_up) are six latencies of LDS.
-__device__ __forceinline__ int wave_incl_scan(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // from the lane 1, 2, 4, 8 below in the row of sixteen
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // rows 1 and 3: the last lane of the row below
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // rows 2 and 3: lane 31
-  return v;
-}
-__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_incl_scan(v), 63); }
 
 // Where work-group w's share of the line starts.  Every thread of the work-group calls this; the
 // results are uniform.  Tile counts fit 32 bits (the host checks the bound), so no 64-bit division

@@ -49,6 +49,25 @@ __device__ __forceinline__ void flag_status(uint32_t* status, uint32_t bit) {
   if (status) atomicOr(status, bit);
 }
 
+// Inclusive scan over the wave, all lanes active.  By the register file's own lane shifts: planning consists of little else, and six trips
+// through LDS (__shfl_up) are six latencies of LDS.
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // from the lane 1, 2, 4, 8 below in the row of sixteen
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // rows 1 and 3: the last lane of the row below
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // rows 2 and 3: lane 31
+  return v;
+}
+__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_incl_scan(v), 63); }
+
+// x / d with inv = inverse(d), for 0 <= x, x / d < 1024 and d <= 1024: (x + 1/2) inv is within 2^-12 of (x + 1/2) / d (two roundings of at most 2^-23
+// of it), which is at least 2^-11 away from every whole number.  An integer division is some 35 dependent instructions, and what
+// precedes a call's first tile, or its combine kernel's loads, consists of little else.
+__device__ __forceinline__ float inverse(int d) { return __builtin_amdgcn_rcpf((float)d); }
+__device__ __forceinline__ int small_div(int x, float inv) { return (int)(((float)x + 0.5f) * inv); }
+
 // Per-sequence description every attention kernel derives from the device arrays,
 // clamped to the host-declared bounds so that no later access leaves the buffers.
 struct SeqInfo {
@@ -69,6 +88,7 @@ struct AttnParams {
   int chunk;          // cached tokens per work-group
   int max_chunks;     // grid extent over chunks
   int row_tiles;      // grid extent over row tiles
+  int even_cus;       // > 0: compute units that the full-precision kernel deals pieces of equal length to (even_pieces)
   unsigned page_magic; int page_magic_shift;   // key / page_size = mulhi(key, magic) >> shift for page_size >= 2, key < 2^31
   float sm_scale;
   const void* k_cache; const void* v_cache;

@@ -131,6 +131,26 @@ def test_full_precision_kernel_infinities(fd, chunk, dtype, D):
     assert np.abs(lse - ref_lse).max() <= (1e-5 if dtype == "f32" else 2e-2)
 
 
+@pytest.mark.parametrize("lens,Hkv,G,n,D,ps,dtype", [
+    (8 * [1024], 8, 4, 16, 32, 16, "f32"),                         # two chunks of 128 keys per compute unit: the largest call cut by chunks
+    (9 * [1024], 8, 4, 16, 32, 16, "f32"),                         # the smallest in equal pieces
+    ([2048, 700, 1300, 0, 33], 8, 4, 16, 96, 3, "bf16"),           # sequences of one piece, and without a prefix
+    ([2048, 2047, 1, 900, 1025, 160] + 10 * [129], 8, 4, 9, 64, 1, "f32"),     # eight chunks per compute unit: the largest in equal pieces
+    (17 * [2048 - 64], 8, 4, 9, 8, 16, "f32"),                     # more than that
+    ([129, 129, 300, 1, 64, 260, 129, 129, 0, 350, 128, 127], 4, 1, 200, 128, 16, "f32"),     # pieces that begin among seven tiles of new keys
+    ([600] + 63 * [40], 4, 4, 9, 40, 24, "bf16"),                  # a sequence in every lane
+    ([600] + 64 * [40], 4, 4, 9, 40, 24, "bf16"),                  # one more than that
+])
+def test_full_precision_kernel_equal_pieces(fd, lens, Hkv, G, n, D, ps, dtype):
+    """Around the calls from and up to which the device cuts the work into equal pieces."""
+    w = _wl("equal", dtype, len(lens), G * Hkv, Hkv, D, ps, (max(lens), max(lens)), (n - 3, n), 0, seed=70 + n)
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array(lens, dtype=np.int32)                          # (the page lists are long enough for all of them)
+    what = f"equal pieces {lens} Hkv={Hkv} n={n} D={D}"
+    _check(fd, inp, dtype, what, flags=FORCE_GENERIC)
+    _check(fd, inp, dtype, what + ", chunks", flags=FORCE_GENERIC, kv_chunk=128)
+
+
 @pytest.mark.parametrize("case", [
     dict(B=3, G=4, Hkv=2, ps=16, kv=(1, 500), kr=(1, 8), m=8),
     dict(B=2, G=4, Hkv=1, ps=16, kv=(64, 64), kr=(4, 4), m=4),             # exactly one full tile
