@@ -20,8 +20,8 @@
 // split partials (running max, sum, un-normalised output) that the combine kernel merges.
 //
 // Measured (4 sequences of 512..2048, 8 KV heads, 64 tile rows each, head dim 128, fp32; 1.64 GFLOP, 53 MB):
-// 35 us a call, 47 TFLOP/s, against 283 us with scalar products on sixteen-row tiles; 16 such sequences 108 us.
-// What is left: with the tile loads taken out 35 us, with the products taken out 21 us -- 340 work-groups of 128
+// 35 us a call, 47 TFLOP/s, against 283 us with scalar products on sixteen-row tiles; 16 such sequences 85 us.
+// What is left: with the tile loads taken out 35 us, with the products taken out 21 us -- 408 work-groups of 128
 // keys put two on some CUs and one on others, and the split partials (34 KB a work-group) are written and read once.
 #include "fd_common.h"
 
