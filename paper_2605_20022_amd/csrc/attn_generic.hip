@@ -264,6 +264,27 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
 #pragma unroll
   for (int b = 0; b < NDB; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  // A piece may be longer than a chunk, and the rounding of a sum over keys grows with the number of keys that go through one accumulator: a
+  // piece is summed in parts of a chunk each, and a part that has ended waits in registers of its own.
+  // 2-norm error against 64 bits over that of chunks (mean of eight calls), pieces summed in one go / in parts: 16 sequences of 2048 keys
+  // at head dim 128 1.10 / 0.86, 16 of 512..2048 at head dim 32 1.08 / 0.93, one KV head with 512 tile rows at head dim 64 1.08 / 0.88,
+  // 12 of 300..1200 at head dim 8 1.10 / 0.96.  us a call: 16 of 512..2048 85.3 / 85.6, 6 of 4000 88.2 / 89.5, the others within 1 %.
+  const int part_tiles = p.chunk / GEN_KEYS;
+  int part_end = part_tiles;
+  float m_done = -INFINITY, l_done = 0.f;
+  f32x4 o_done[EVEN ? NDB : 1];
+  if (EVEN) {
+#pragma unroll
+    for (int b = 0; b < NDB; ++b) o_done[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto end_part = [&]() {                          // what is done, and the part in o and l_lane, at the reference m_run
+    const float r = expf(m_done - (m_run == -INFINITY ? 0.f : m_run));               // (m_done = -inf: 0)
+    l_done = l_done * r + l_lane;
+#pragma unroll
+    for (int b = 0; b < NDB; ++b) o_done[EVEN ? b : 0] = o_done[EVEN ? b : 0] * r + o[b];
+    m_done = m_run;
+  };
+
   for (int t = 0; t < nt; ++t) {
     if (t + 1 < nt) { load_tile(t + 1); fetch_pages(t + 2); }
     const bool is_new = t >= cached_tiles;
@@ -275,8 +296,8 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
     auto block = [&](auto nkb_c, int kb0) {        // NKB 16-key blocks from kb0 on
       constexpr int NKB = decltype(nkb_c)::value;
       // K fragments are requested one 16-column step ahead of the matrix instructions that take them
-      // accumulation chains per key block; four with pieces, whose sums over keys are up to 7/4 as long as those of chunks: the error
-      // against 64 bits is then no larger (2-norm, mean of eight calls: chunks 3.36e-7, pieces 3.21e-7, with two chains 3.58e-7; time equal)
+      // accumulation chains per key block; four with pieces, where time is equal and the error smaller (9 sequences of 1024 keys, 64 tile
+      // rows, head dim 128: chunks with two chains 3.27e-7, pieces with four 2.71e-7)
       constexpr int CHAINS = EVEN ? 4 : 2;
       f32x4 sc[NKB][CHAINS];
 #pragma unroll
@@ -370,8 +391,21 @@ __global__ __launch_bounds__(GEN_BLOCK, 2) void attn_generic_kernel(AttnParams p
       if (KS == 1) block(std::integral_constant<int, 2>{}, 0);
       else if (base + 16 * ks < end) block(std::integral_constant<int, 1>{}, ks);
     }
+    if (EVEN && t + 1 == part_end && t + 1 < nt) {
+      end_part();
+      l_lane = 0.f;
+#pragma unroll
+      for (int b = 0; b < NDB; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+      part_end += part_tiles;
+    }
     if (t + 1 < nt) store_tile(t + 1, (t + 1) & 1);
     __syncthreads();                               // tile t consumed, tile t + 1 visible
+  }
+  if (EVEN && nt > part_tiles) {
+    end_part();
+    l_lane = l_done;
+#pragma unroll
+    for (int b = 0; b < NDB; ++b) o[b] = o_done[EVEN ? b : 0];
   }
 
   // ---- merge the two waves of a row block (same register layout) through LDS --------------------

@@ -151,6 +151,24 @@ def test_full_precision_kernel_equal_pieces(fd, lens, Hkv, G, n, D, ps, dtype):
     _check(fd, inp, dtype, what + ", chunks", flags=FORCE_GENERIC, kv_chunk=128)
 
 
+@pytest.mark.parametrize("lens,Hkv,G,n,D,chunk", [
+    ([300, 1200, 700, 1100, 900, 450, 640, 820, 1000, 350, 1190, 780], 8, 4, 16, 8, 128),                  # pieces of six tiles, chunks of four
+    ([512, 2048, 1700, 900, 1300, 610, 1999, 1500, 800, 1100, 1850, 700, 1250, 1600, 950, 1400], 8, 4, 16, 32, 256),       # 12 and 8
+    ([1000, 4000, 3000, 2500, 1500, 3500, 2000, 2750], 1, 16, 32, 64, 256),                                # 12 and 8
+    (16 * [2048], 8, 4, 16, 128, 320),                                                                     # 18 and 10
+])
+def test_full_precision_kernel_equal_pieces_round_no_more_than_chunks(fd, lens, Hkv, G, n, D, chunk):
+    """The error against 64 bits of pieces longer than the automatic cut's chunks (`chunk`) is no larger than that of the chunks.
+
+    Both are sums of some 10^5 roundings: the ratio of their 2-norms varies by 1 % from one input to another, hence 1.02."""
+    w = _wl("rounding", "f32", len(lens), G * Hkv, Hkv, D, 16, (max(lens), max(lens)), (n, n), 0, seed=90 + D)
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array(lens, dtype=np.int32)                          # (the page lists are long enough for all of them)
+    ref, _ = oracle_attention(inp)
+    err = [np.linalg.norm(AttnCall(fd, inp, flags=FORCE_GENERIC, kv_chunk=c).run()[0] - ref) for c in (0, chunk)]
+    assert err[0] <= 1.02 * err[1], f"pieces {err[0]:.3e}, chunks {err[1]:.3e}"
+
+
 @pytest.mark.parametrize("case", [
     dict(B=3, G=4, Hkv=2, ps=16, kv=(1, 500), kr=(1, 8), m=8),
     dict(B=2, G=4, Hkv=1, ps=16, kv=(64, 64), kr=(4, 4), m=4),             # exactly one full tile
