@@ -409,6 +409,8 @@ __device__ __forceinline__ bool find_share(const AttnParams& p, const MfmaSched&
 // streaming kernel is the variant without the line: no walk over items and no second piece, a third of the instructions and no spilled scalars
 // (16 of 512..4096 keys 39.7 -> 37.9, 1 of 2048 14.6 -> 13.2, 4 of 32768 112.7 -> 109.4).
 // An item's pieces have consecutive numbers (in lists: head, length class, sequence, row block, piece; else sequence, head, row block, piece).
+// In lists they are taken in that order.  Outside, a head's pieces are taken piece by piece, all of its row blocks at a time: these read the same
+// tiles, and are neighbours on an XCD.
 // Every wave works this out by itself (lane i holds sequence i): no LDS, no barrier.
 // Returns false if the call is to be cut along the line; has_piece: this work-group has one.
 struct PieceShare { int w, seq, W_eff, pieces, head, rt, tile0, nt; };
@@ -505,11 +507,20 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
   ws.v = from(s.v); ws.nb = from(s.nb); ws.page0 = from(s.page0); ws.npages = from(s.npages);
   const int Ts = from(T), Ss = from(S), per_s = from(per);
   int local = q - from(lo);
-  if (!lists) { ps.head = small_div(local, inverse(per_s)); local -= ps.head * per_s; }
   ps.seq = at; ps.pieces = Ss;
   const float inv_s = inverse(Ss);
-  ps.rt = small_div(local, inv_s);
-  const int j = local - ps.rt * Ss;
+  int j;
+  if (lists) {
+    ps.rt = small_div(local, inv_s);
+    j = local - ps.rt * Ss;
+  } else {
+    ps.head = small_div(local, inverse(per_s)); local -= ps.head * per_s;
+    const int RTs = from(RT);
+    // one after the other, an item's pieces left its row blocks on different XCDs: one KV head, 32768 keys, 272 rows 39.2 us a call, so 37.1;
+    // four heads, 8 sequences of 2048..8192 keys and 36 rows 36.3, so 34.5
+    j = small_div(local, inverse(RTs)); ps.rt = local - j * RTs;
+    ps.w += ps.rt * Ss + j - local;
+  }
   // piece j: tiles [floor(j T / S), floor((j + 1) T / S)), in 32 bits: T = a S + b
   const int a = (int)((unsigned)Ts / (unsigned)Ss), b = Ts - a * Ss;
   ps.tile0 = j * a + small_div(j * b, inv_s);

@@ -360,6 +360,52 @@ def test_lists_of_pieces_per_head(fd, lens, Hkv, n, D):
     assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
 
 
+def _planned_pieces(fd, call):
+    """The pieces of a call that is cut piece by piece, as its plan deals them out: (work-group, sequence, head, row block, first tile, tiles).
+
+    The plan is the workspace's last part, 32 words per work-group (two work-groups per compute unit)."""
+    wgs = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    call.workspace.fill_(255)                                      # (sequence -1: no piece)
+    fd.fd_verify_draft_plan(call.args)
+    need = fd.fd_verify_draft_attn_workspace(call.args)
+    plan = call.workspace[need - 128 * wgs:need].cpu().numpy().view(np.int32).reshape(wgs, 32)
+    pieces = [(x, int(e[0]), int(e[25]), int(e[26]), int(e[27]), int(e[28])) for x, e in enumerate(plan) if e[0] >= 0]
+    assert all(plan[x][24] > 0 for x, *_ in pieces)
+    return pieces
+
+
+@pytest.mark.parametrize("lens,Hkv,G,n,D", [
+    ([2048], 4, 4, 72, 128),           # three row blocks, the last one of 32 rows
+    ([4096], 2, 4, 272, 128),          # nine row blocks
+    ([8192], 1, 4, 272, 128),
+    ([4096, 2048, 3000], 3, 4, 100, 64),       # heads that are no power of two, sequences of different lengths
+    ([5000, 900], 4, 8, 36, 128),
+])
+def test_row_blocks_of_the_same_tiles_share_an_xcd(fd, lens, Hkv, G, n, D):
+    """Outside the lists per head: a tile is read on few XCDs (work-group x runs on XCD x % 8), whichever row blocks need it."""
+    w = _wl("share", "bf16", len(lens), G * Hkv, Hkv, D, 16, (max(lens), max(lens)), (n, n), 0, seed=350 + n)
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array(lens, dtype=np.int32)                 # (the page lists are long enough for all of them)
+    call = AttnCall(fd, inp)
+    pieces = _planned_pieces(fd, call)
+    blocks = -(-n * G // 128)
+    tiles = [-(-L // 64) + -(-n // 64) for L in lens]
+    assert sum(p[5] for p in pieces) == Hkv * blocks * sum(tiles)  # every tile of every item once
+    read = {(x % 8, seq, head, t) for x, seq, head, _, t0, nt in pieces for t in range(t0, t0 + nt)}
+    # a run of an XCD begins and ends inside a group of row blocks at most: two groups' tiles of an XCD are read elsewhere as well
+    longest = max(p[5] for p in pieces)
+    assert len(read) <= Hkv * sum(tiles) + 8 * 2 * longest, f"{len(read)} tiles read, {Hkv * sum(tiles)} in all"
+    out, lse = call.run()
+    ref, ref_lse = oracle_attention(inp)
+    assert_attn_close(out, ref, "bf16", f"share {lens} Hkv={Hkv} n={n} D={D}")
+    assert np.abs(lse - ref_lse).max() <= 2e-2
+    fd.fd_verify_draft_plan(call.args)
+    call.args.flags |= fd.FD_ATTN_PLANNED
+    call.out.fill_(float("nan"))
+    out2, lse2 = call.run()
+    assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
+
+
 @pytest.mark.parametrize("D,lens,Hkv,n,what", [
     (64, [2000, 2000, 2000, 4200], 64, 4, "256 items, the line"),
     (64, [2000, 4200, 2000, 2000], 64, 65, "128-row items, the line"),
