@@ -409,8 +409,8 @@ __device__ __forceinline__ bool find_share(const AttnParams& p, const MfmaSched&
 // streaming kernel is the variant without the line: no walk over items and no second piece, a third of the instructions and no spilled scalars
 // (16 of 512..4096 keys 39.7 -> 37.9, 1 of 2048 14.6 -> 13.2, 4 of 32768 112.7 -> 109.4).
 // An item's pieces have consecutive numbers (in lists: head, length class, sequence, row block, piece; else sequence, head, row block, piece).
-// In lists they are taken in that order.  Outside, a head's pieces are taken piece by piece, all of its row blocks at a time: these read the same
-// tiles, and are neighbours on an XCD.
+// They are taken in that order where the KV heads are a multiple of the XCDs: an XCD then has whole heads (all but the first and last of a run).  Else a
+// head's pieces are taken piece by piece, all of its row blocks at a time: these read the same tiles, and are neighbours on an XCD.
 // Every wave works this out by itself (lane i holds sequence i): no LDS, no barrier.
 // Returns false if the call is to be cut along the line; has_piece: this work-group has one.
 struct PieceShare { int w, seq, W_eff, pieces, head, rt, tile0, nt; };
@@ -468,7 +468,8 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
   //   else   runs, unless they leave an XCD more than a quarter above the average (one sequence much longer than the others: half
   //     of the XCDs had nothing but its pieces): then in turn, every compute unit gets some of both.
   // Even batches stay in runs (24 sequences of 2048 keys, 32 rows 50.2, in lists 51.3).
-  const bool lists = (p.Hkv & (sc_.xcds - 1)) == 0 && 16ll * tiles_all < 15ll * ps.W_eff * size;
+  const bool whole_heads = (p.Hkv & (sc_.xcds - 1)) == 0;
+  const bool lists = whole_heads && 16ll * tiles_all < 15ll * ps.W_eff * size;
   const int n = lists ? per : I * S;               // this lane's pieces in a list, or in all; lo: those before them
   int lo, P = ps.W_eff;
   if (lists) {
@@ -508,16 +509,15 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
   const int Ts = from(T), Ss = from(S), per_s = from(per);
   int local = q - from(lo);
   ps.seq = at; ps.pieces = Ss;
+  if (!lists) { ps.head = small_div(local, inverse(per_s)); local -= ps.head * per_s; }
   const float inv_s = inverse(Ss);
   int j;
-  if (lists) {
-    ps.rt = small_div(local, inv_s);
-    j = local - ps.rt * Ss;
+  if (whole_heads) {
+    ps.rt = small_div(local, inv_s); j = local - ps.rt * Ss;
   } else {
-    ps.head = small_div(local, inverse(per_s)); local -= ps.head * per_s;
+    // by item, its row blocks lay on different XCDs: one KV head, 32768 keys, 272 rows 39.2 us a call, so 37.1; four heads, 8 sequences
+    // of 2048..8192 keys and 36 rows 36.3, so 34.5
     const int RTs = from(RT);
-    // one after the other, an item's pieces left its row blocks on different XCDs: one KV head, 32768 keys, 272 rows 39.2 us a call, so 37.1;
-    // four heads, 8 sequences of 2048..8192 keys and 36 rows 36.3, so 34.5
     j = small_div(local, inverse(RTs)); ps.rt = local - j * RTs;
     ps.w += ps.rt * Ss + j - local;
   }
@@ -1396,9 +1396,10 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
 // The pieces of an item sit in its first slot, then in the first slot (2w) of every later
 // work-group up to the one it ended in.  Sixteen lanes per tile row, a lane owns eight adjacent
 // output columns; PG sixteen-lane groups share a row and take every PG-th piece.
-//   grid by item (KV heads, row blocks of 16 / PG rows, sequences), by share (shares, row blocks).  By item a head's blocks run on the
-//   XCD of the head, whose L2 holds the partials where the pieces are cut in lists per head or one sequence is all there is, and the
-//   next call's stores find them there; the row blocks of an item follow one another and go to different compute units.
+//   grid by item (KV heads, row blocks of 16 / PG rows, sequences), by share (shares, row blocks).  By item, with eight KV heads, a head's blocks
+//   run on the XCD of the head: its L2 holds the partials where the pieces are cut in lists per head or one sequence is all there is, and
+//   the next call's stores find them there.  (With 8 m heads the blocks of head h run on XCD h % 8, its pieces on h / m: the same for
+//   two heads of 16.)  The row blocks of an item follow one another and go to different compute units.
 //   us a call, items first / now: 1 sequence of 2048 keys and 72 rows 18.2 / 16.5 (streaming kernel 14.4 / 13.2, this one 5.0 / 4.4), 16 of
 //   512..4096 at head dim 64 22.8 / 21.8, 4 of 500..1000 12.05 / 11.8; eight long items of some 40 pieces among 248 short ones equal
 //   (their row blocks 256 blocks apart, on one compute unit: 5 us more).

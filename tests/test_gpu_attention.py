@@ -382,7 +382,7 @@ def _planned_pieces(fd, call):
     ([5000, 900], 4, 8, 36, 128),
 ])
 def test_row_blocks_of_the_same_tiles_share_an_xcd(fd, lens, Hkv, G, n, D):
-    """Outside the lists per head: a tile is read on few XCDs (work-group x runs on XCD x % 8), whichever row blocks need it."""
+    """KV heads that are no multiple of eight: a tile is read on few XCDs (work-group x runs on XCD x % 8), whichever row blocks need it."""
     w = _wl("share", "bf16", len(lens), G * Hkv, Hkv, D, 16, (max(lens), max(lens)), (n, n), 0, seed=350 + n)
     inp = W.make_attention_inputs(w)
     inp["kv_len"] = np.array(lens, dtype=np.int32)                 # (the page lists are long enough for all of them)
