@@ -235,10 +235,12 @@ static fd_status attn_call(const fd_attn_args* a, void* workspace, size_t worksp
   }
   // Full-precision kernel: with more than two chunks per compute unit, if all were as long as the longest may be, the device cuts equal pieces (even_pieces says
   // why from there on); not where 32 tile rows or fewer leave the products aside (4 of 512..2048 keys, 16 rows 24.0 us, in pieces 25.4).
+  // The automatic cut aims at 1024 chunks, so that where an item has three or more there are at most 511 items and 1533 chunks; the limits on
+  // chunks, their length and the rows are those of the quotients that small_div takes.
   const int cus = fd::attn_mfma_num_wgs() / 2;
   const long long most_chunks = (long long)(a->batch > 0 ? a->batch : 1) * a->num_kv_heads * plan.row_tiles * plan.max_chunks;
-  p.even_cus = !plan.use_mfma && a->kv_chunk == 0 && a->batch <= FD_WAVE && (long long)a->max_new_rows * p.G > 32 && most_chunks > 2 * cus && most_chunks <= 8 * cus &&
-               plan.max_chunks > 2 && plan.max_chunks < 512 && plan.chunk <= 8192 && a->max_new_rows <= 8192 ? cus : 0;      // (quotients that small_div takes)
+  p.even_cus = !plan.use_mfma && a->kv_chunk == 0 && a->batch <= FD_WAVE && (long long)a->max_new_rows * p.G > 32 && most_chunks > 2 * cus &&
+               plan.max_chunks > 2 && plan.max_chunks < 512 && plan.chunk <= 8192 && a->max_new_rows <= 8192 ? cus : 0;
   p.sm_scale = a->sm_scale > 0.f ? a->sm_scale : 1.0f / sqrtf((float)a->head_dim);
   p.k_cache = a->k_cache; p.v_cache = a->v_cache;
   p.sp = a->cache_stride_page; p.sh = a->cache_stride_head; p.st = a->cache_stride_token;

@@ -135,8 +135,10 @@ def test_full_precision_kernel_infinities(fd, chunk, dtype, D):
     (8 * [1024], 8, 4, 16, 32, 16, "f32"),                         # two chunks of 128 keys per compute unit: the largest call cut by chunks
     (9 * [1024], 8, 4, 16, 32, 16, "f32"),                         # the smallest in equal pieces
     ([2048, 700, 1300, 0, 33], 8, 4, 16, 96, 3, "bf16"),           # sequences of one piece, and without a prefix
-    ([2048, 2047, 1, 900, 1025, 160] + 10 * [129], 8, 4, 9, 64, 1, "f32"),     # eight chunks per compute unit: the largest in equal pieces
-    (17 * [2048 - 64], 8, 4, 9, 8, 16, "f32"),                     # more than that
+    ([2048, 2047, 1, 900, 1025, 160] + 10 * [129], 8, 4, 9, 64, 1, "f32"),     # four chunks of 256 keys per compute unit, if all were as long as the longest
+    (17 * [2048 - 64], 8, 4, 9, 8, 16, "f32"),                     # a few more than that
+    ([65408, 3000], 1, 4, 9, 8, 16, "f32"),                        # 511 chunks of 128 keys: the most that are taken as pieces
+    ([65409, 3000], 1, 4, 9, 8, 16, "f32"),                        # 512: chunks
     ([129, 129, 300, 1, 64, 260, 129, 129, 0, 350, 128, 127], 4, 1, 200, 128, 16, "f32"),     # pieces that begin among seven tiles of new keys
     ([600] + 63 * [40], 4, 4, 9, 40, 24, "bf16"),                  # a sequence in every lane
     ([600] + 64 * [40], 4, 4, 9, 40, 24, "bf16"),                  # one more than that
@@ -149,6 +151,32 @@ def test_full_precision_kernel_equal_pieces(fd, lens, Hkv, G, n, D, ps, dtype):
     what = f"equal pieces {lens} Hkv={Hkv} n={n} D={D}"
     _check(fd, inp, dtype, what, flags=FORCE_GENERIC)
     _check(fd, inp, dtype, what + ", chunks", flags=FORCE_GENERIC, kv_chunk=128)
+
+
+@pytest.mark.parametrize("bound", [24576, 24577])                  # chunks of 8192 keys, the longest that are taken as pieces, and of 8256
+def test_full_precision_kernel_equal_pieces_long_chunks(fd, bound):
+    """A call declared for longer sequences than it has: one of three chunks, 56 of a few keys."""
+    lens = [20000] + 56 * [5]
+    w = _wl("long_chunks", "f32", 57, 16, 1, 8, 16, (20000, 20000), (32, 32), 0, seed=79)
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array(lens, dtype=np.int32)                          # (the page lists are long enough for all of them)
+    _check(fd, inp, "f32", f"long chunks, bound {bound}", flags=FORCE_GENERIC, max_kv_len=bound)
+
+
+@pytest.mark.parametrize("n", [8192, 8193])                        # the most rows that are taken as pieces, and one more
+def test_full_precision_kernel_equal_pieces_many_rows(fd, n):
+    """Pieces of 36 tiles, most of them new rows, against chunks (whose last one holds all of these); both within 1e-5 of the definition."""
+    w = _wl("many_rows", "f32", 1, 1, 1, 8, 16, (1024, 1024), (n, n), 0, seed=80)
+    inp = W.make_attention_inputs(w)
+    (out, lse), (ref, ref_lse) = (AttnCall(fd, inp, flags=FORCE_GENERIC, kv_chunk=c).run() for c in (0, 128))
+    assert np.isfinite(out).all() and np.abs(out - ref).max() <= 2e-5 and np.abs(lse - ref_lse).max() <= 2e-5
+    # the first rows and the last ones, which see 1025 keys and all of them, by the definition
+    K, V = (np.concatenate([inp[c][inp["page_indices"]].transpose(0, 2, 1, 3).reshape(1024, 8), inp[x][:, 0]]).astype(np.float64)
+            for c, x in (("k_cache", "k_new"), ("v_cache", "v_new")))
+    for r in (0, 1, 31, 32, n // 2, n - 1):
+        x = K[:1025 + r] @ inp["q"][r, 0].astype(np.float64) / np.sqrt(8.0)
+        e = np.exp(x - x.max())
+        assert np.abs(out[r, 0] - e @ V[:1025 + r] / e.sum()).max() <= 1e-5 and abs(lse[r, 0] - x.max() - np.log(e.sum())) <= 1e-5
 
 
 @pytest.mark.parametrize("lens,Hkv,G,n,D,chunk", [
