@@ -76,7 +76,8 @@ def test_full_precision_kernel_edges(fd, dtype, G, rows, D):
     _check(fd, inp, dtype, f"edges {dtype} D={D} G={G} rows={rows} ps={ps} chunk", flags=FORCE_GENERIC, kv_chunk=64)
 
 
-@pytest.mark.parametrize("B,kv,n", [(4, (512, 2048), 16), (1, (5000, 5000), 3), (2, (600, 700), 20)])
+@pytest.mark.parametrize("B,kv,n", [(4, (512, 2048), 16), (1, (5000, 5000), 3), (2, (600, 700), 20),
+                                    (40, (300, 2048), 9)])        # equal pieces, with chunks of 192 keys and of 256 or 320; chunks of 512
 def test_full_precision_kernel_in_a_small_workspace(fd, B, kv, n):
     """Less workspace than the query's answer: longer chunks, down to what chunks of 512 keys need; below that, refused."""
     w = _wl("small_ws", "f32", B, 8, 2, 128, 16, kv, (n, n), 0, seed=78)
@@ -177,6 +178,73 @@ def test_full_precision_kernel_equal_pieces_many_rows(fd, n):
         x = K[:1025 + r] @ inp["q"][r, 0].astype(np.float64) / np.sqrt(8.0)
         e = np.exp(x - x.max())
         assert np.abs(out[r, 0] - e @ V[:1025 + r] / e.sum()).max() <= 1e-5 and abs(lse[r, 0] - x.max() - np.log(e.sum())) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype,D,m,blocks", [
+    ("f32", 64, 192, [1]),                                         # one mask block
+    ("f32", 96, 96, [16]),                                         # one per verify row
+    ("bf16", 64, 192, [16, 4, 1, 8, 2, 12, 3, 6, 16, 24, 48, 1]),  # of 12 to 192 rows
+    ("f32", 128, 96, [2, 16, 1, 32, 8, 4]),
+])
+def test_full_precision_kernel_equal_pieces_masks(fd, dtype, D, m, blocks):
+    """Verify rows and mask blocks in equal pieces, some of which begin among the mask rows; default and explicit visibility."""
+    lens = [129, 140, 350, 33, 0, 300, 129, 260, 350, 200, 129, 64]
+    w = _wl("masks", dtype, len(lens), 8, 4, D, 16, (350, 350), (16, 16), m, seed=90 + m + D)
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array(lens, dtype=np.int32)                          # (the page lists are long enough for all of them)
+    if blocks != [1]:
+        inp["mask_blocks"] = np.array((12 * blocks)[:12], dtype=np.int32)
+    first_vis = np.random.default_rng(D).integers(0, 17, size=12).astype(np.int32)
+    for vis in (None, first_vis):
+        what = f"masks {dtype} D={D} m={m} blocks={blocks} vis={vis}"
+        _check(fd, inp, dtype, what, mask_vis=vis, flags=FORCE_GENERIC)
+        _check(fd, inp, dtype, what + ", chunks", mask_vis=vis, flags=FORCE_GENERIC, kv_chunk=128)
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 8), ("f32", 128), ("bf16", 40)])
+def test_full_precision_kernel_equal_pieces_infinities(fd, dtype, D):
+    """Infinities in sequences of one and of several pieces, each longer than a chunk or not."""
+    lens = [33, 64, 1000, 300, 1000, 700, 900, 500, 128]
+    w = _wl("inf_pieces", dtype, 9, 16, 8, D, 16, (1000, 1000), (0, 0), 17, seed=95 + D)      # mask rows: every row sees every key
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array(lens, dtype=np.int32)                          # (the page lists are long enough for all of them)
+    up, down = (np.float32("inf"), -np.float32("inf")) if dtype == "f32" else (np.uint16(0x7F80), np.uint16(0xFF80))
+    at = lambda i, key: (int(inp["page_indices"][inp["page_indptr"][i] + key // 16]), key % 16)      # noqa: E731
+    inp["q"][:, :, 0] = np.float32(0.5) if dtype == "f32" else np.uint16(0x3F00)
+    for i, key in ((0, 32), (2, 999), (3, 0), (4, 500)):                    # one cached value of +inf
+        page, slot = at(i, key)
+        inp["v_cache"][page, 0, slot, 3] = up
+    inp["v_new"][int(inp["row_indptr"][6]) - 1, 1, 5] = down                # sequence 5: the last new value
+    for key in (0, 128, 899):                                               # sequence 6: keys without weight
+        page, slot = at(6, key)
+        inp["k_cache"][page, :, slot, 0] = down
+    out, lse = AttnCall(fd, inp, flags=FORCE_GENERIC).run()
+    ref, ref_lse = oracle_attention(inp)
+    assert np.isposinf(ref).any() and np.isneginf(ref).any() and not np.isnan(ref).any()
+    assert np.array_equal(np.isposinf(out), np.isposinf(ref)) and np.array_equal(np.isneginf(out), np.isneginf(ref))
+    finite = np.isfinite(ref)
+    assert_attn_close(out[finite], ref[finite], dtype, f"infinities {dtype} D={D}")
+    assert np.abs(lse - ref_lse).max() <= (1e-5 if dtype == "f32" else 2e-2)
+
+
+def test_full_precision_kernel_equal_pieces_device_status(fd):
+    """Lengths, rows and page lists that are not what the host declared: clamped and reported, the other sequences as they should be."""
+    lens = 12 * [1000]
+    w = _wl("pieces_status", "f32", 12, 32, 8, 32, 16, (1000, 1000), (12, 12), 0, seed=98)
+    inp = W.make_attention_inputs(w)
+    ref, ref_lse = oracle_attention(inp)
+    own = lambda i: slice(int(inp["row_indptr"][i]), int(inp["row_indptr"][i + 1]))      # noqa: E731
+    for name, at, value, bit in (("kv_len", 3, 10 ** 6, 1), ("kv_len", 11, -1, 1), ("verify_len", 5, 13, 2), ("page_indptr", 12, 10 ** 6, 4)):
+        call = AttnCall(fd, inp, flags=FORCE_GENERIC)
+        call.d[name][at] = value
+        fd.fd_verify_draft_attn(call.args)
+        torch.cuda.synchronize()
+        assert int(call.status.item()) & bit, (name, value)
+        out, lse = call.out.cpu().numpy(), call.lse.cpu().numpy()
+        for i in range(12):
+            if i != min(at, 11):
+                assert_attn_close(out[own(i)], ref[own(i)], "f32", f"{name}[{at}] = {value}, sequence {i}")
+                assert np.abs(lse[own(i)] - ref_lse[own(i)]).max() <= 1e-5
 
 
 @pytest.mark.parametrize("lens,Hkv,G,n,D,chunk", [
