@@ -631,7 +631,7 @@ __global__ __launch_bounds__(MF_BLOCK, 2) void attn_mfma_kernel(AttnParams p, Mf
     W_eff = clampi(W_eff, 0, sc_.num_wgs);
     if (pw == 0 && tid == 0 && !sc_.by_item) sc_.entries[sc_.num_wgs] = make_int4(W_eff, 0, 0, 0);       // for the combine kernel
     if (seq < 0 || seq >= p.B || W_eff < 1 || w < 0 || w >= W_eff || g1 <= g0 || Pt > g0 || sh_q == 0) return;
-    clamp_seq(p, ws);
+    clamp_seq<SINGLE>(p, ws);
     if (!CUT || ps.pieces < 0) ps.pieces = 0;
     if (SINGLE && ps.pieces == 0) return;        // (not this call's plan)
   } else {

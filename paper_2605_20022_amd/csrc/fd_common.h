@@ -159,14 +159,17 @@ __device__ __forceinline__ SeqInfo load_seq(const AttnParams& p, int i) { return
 
 // The same bounds applied to a description that came from somewhere else than the device arrays
 // (a plan entry): whatever it holds, nothing derived from it leaves the caller's buffers.  The
-// length of page_indices must be known (page_entries > 0).
+// length of page_indices must be known (page_entries > 0).  BRANCH: no division where there is one mask block.  Not in kernels whose scalars
+// spill: behind the branch the compiler spills 312 of them in the 64-row variant along the line, without it 162 (65 sequences of 115..460
+// keys and 14 rows of 2 heads, planned, 34.3 us a call, so 30.4).
+template <bool BRANCH>
 __device__ __forceinline__ void clamp_seq(const AttnParams& p, SeqInfo& s) {
   s.L = clampi(s.L, 0, p.max_kv_len);
   s.row0 = clampi(s.row0, 0, p.total_rows);
   s.n = clampi(s.n, 0, p.max_new_rows < p.total_rows - s.row0 ? p.max_new_rows : p.total_rows - s.row0);
   s.k = clampi(s.k, 0, s.n);
   s.v = clampi(s.v, 0, s.k);
-  if (s.nb < 1 || (s.nb != 1 && (s.n - s.k) % s.nb)) s.nb = 1;
+  if (s.nb < 1 || (!(BRANCH && s.nb == 1) && (s.n - s.k) % s.nb)) s.nb = 1;
   s.page0 = clampi(s.page0, 0, p.page_entries);
   s.npages = clampi(s.npages, 0, p.page_entries - s.page0);
   const long long cap = (long long)s.npages * p.page_size;
