@@ -97,6 +97,25 @@ def test_new_length_is_stored_past_a_barrier(kernels):
         assert copies and max(copies) < barrier[0]
 
 
+def test_combine_kernel_requests_a_batch_at_once(kernels):
+    """Twelve pieces of a row, or six where four lane groups share it: two vector loads each, and no wait for one of them before the last is requested."""
+    seen = 0
+    for name, code in kernels.items():
+        m = re.search(r"attn_mfma_combine_kernelILi[24]ELi\d+ELi([14])E", name)
+        if not m:
+            continue
+        seen += 1
+        run = longest = 0
+        for ins in code:
+            if ins.startswith("global_load"):
+                run += 1
+                longest = max(longest, run)
+            elif ins.startswith("s_waitcnt") and ("vmcnt" in ins or ins.split()[1] == "0"):
+                run = 0
+        assert longest >= (24 if m[1] == "1" else 12), (name, longest)
+    assert seen == 8                                         # 64 and 128 rows, head dims 64 and 128, one lane group a row and four
+
+
 def test_planned_kernels_along_the_line_spill_few_scalars(code_objects):
     """Each spilled scalar is a vector instruction where it is stored or used.  A branch before the walk over items doubled them (312 in the 64-row
     variant, 221 in the 128-row one: planned calls 2 to 16 % slower); without it there are 145 to 164."""
