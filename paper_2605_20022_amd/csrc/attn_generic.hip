@@ -20,7 +20,7 @@
 // split partials (running max, sum, un-normalised output) that the combine kernel merges.
 //
 // Measured (4 sequences of 512..2048, 8 KV heads, 64 tile rows each, head dim 128, fp32; 1.64 GFLOP, 53 MB):
-// 35 us a call, 47 TFLOP/s, against 283 us with scalar products on sixteen-row tiles; 16 such sequences 85 us.
+// 35 us a call, 47 TFLOP/s, against 283 us with scalar products on sixteen-row tiles; 16 such sequences 86 us.
 // What is left: with the tile loads taken out 35 us, with the products taken out 21 us -- 408 work-groups of 128
 // keys put two on some CUs and one on others, and the split partials (34 KB a work-group) are written and read once.
 #include "fd_common.h"
@@ -47,11 +47,15 @@ __device__ __forceinline__ float quarters_max(float v) {
 // pieces, at most as many as it has chunks of p.chunk keys, and the pieces are the first work-groups of the launch.
 // A compute unit takes its tiles one after the other whether one work-group holds them or two (some 2.9 us a tile of 64 rows), so a call
 // takes as long as the compute unit with the most of them: rounds of pieces, times tiles of a piece and the one that its partial weighs.  The
-// piece size is the one of four, p.chunk to 7/4 of it, for which that is least.  In a grid over (chunk, head, sequence) the chunks that
-// shorter sequences don't have leave some compute units with three work-groups and others with one.
-// us a call, fp32, 8 KV heads, 64 tile rows, head dim 128, chunks of 128 keys / pieces: 3 sequences of 2992..3583 keys
-// 59.7 / 45.6, 5 of 1036..1997 50.3 / 39.5, 5 of 512..4096 68.4 / 58.8, 16 of 512..2048 105.9 / 85.5, 16 of 2048 125.4 / 106.8, 9 of 1024 55.0 / 44.2;
-// 8 of 500..2000 at head dim 64 34.7 / 30.5, bf16 at head dim 96 49.2 / 40.9; one KV head, 8 of 1000..4000, 512 tile rows 106.3 / 81.4.
+// piece size is the one of four, p.chunk to 7/4 of it, for which that product is least.  (A sequence has as many pieces as its prefix has chunks at most, so
+// that new rows that are many against the prefix make its pieces longer than the size: 385 keys and 256 new rows with chunks of 128 keys are
+// four pieces of up to six tiles.  The product counts them as the size.)  In a grid over (chunk, head, sequence) the chunks that shorter
+// sequences don't have leave some compute units with three work-groups and others with one, and equal lengths end in a round of few.
+// us a call, fp32, 8 KV heads, 64 tile rows, head dim 128, chunks / pieces (keys of a chunk of the automatic cut, of a piece at most):
+// 3 sequences of 2992..3583 keys 59.2 / 45.7 (128, 160), 9 of 1024 55.1 / 44.9 (128, 160), 5 of 1036..1997 49.9 / 40.8 (128, 128), 5 of 512..4096
+// 68.8 / 59.2 (192, 256), 16 of 512..2048 105.3 / 85.8 (320, 416), 16 of 2048 125.5 / 107.5 (320, 576); 8 of 500..2000 at head dim 64 34.9 / 31.4,
+// bf16 at head dim 96 49.3 / 41.0 (128, 192); one KV head, 8 of 1000..4000, 512 tile rows 106.5 / 82.1 (320, 416).  6 of 4000 in three rounds instead
+// of four 89.2 / 90.0 (192, 256).  Declared for longer sequences than there are: 16 of 60..100 with a bound of 2048 35.0 / 27.6.
 // Up to two work-groups per compute unit the grid is kept: they all start at once, and where lengths differ
 // little (4 of 1400..2000 keys) finding the pieces costs more than it gives, 35.6 / 36.4.
 // Every wave works this out by itself, lane i for sequence i.

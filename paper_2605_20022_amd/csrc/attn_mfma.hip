@@ -462,9 +462,11 @@ __device__ __forceinline__ bool find_piece(const AttnParams& p, const MfmaSched&
   //   KV heads a multiple of the XCDs   an XCD takes the pieces of its heads, a head's row blocks and sequences in one list: the lists
   //     are alike.  In a list the longest pieces come first (those of more than 15/16 of the longest, of more than 7/8, the others),
   //     since the first work-group of a compute unit has its first tile 3 us before the second, and the second ones take the
-  //     rest from its end, so that the longest share their compute unit with the shortest.  us a call, runs over (sequence, head, piece, row
-  //     block) / lists: 2 sequences of 272 rows (pieces of 22 and 28 tiles) 68.3 / 63.9; 16 of 512..4096 keys, 16 rows 37.4 / 36.5;
-  //     24 of 512..4096, 32 rows 58.2 / 56.0; 8 of 36 rows in four blocks 59.0 / 57.5; 15 of 1000 and one of 131072, 16 rows 118 / 111.
+  //     rest from its end, so that the longest share their compute unit with the shortest.  us a call, runs over (sequence,
+  //     head, piece, row block) / lists: 2 sequences of 272 rows (pieces of 22 and 28 tiles) 67.3 / 63.5; 16 of 512..4096 keys, 16 rows 37.4 / 36.1;
+  //     24 of 512..4096, 32 rows 58.2 / 56.0; 15 of 1000 and one of 131072, 16 rows 118 / 111.  Row blocks of few rows count like full ones, and two
+  //     full ones may share a compute unit: 8 sequences of 36 rows (blocks of 128 and 16) 56.5 / 56.4, 7 of 3418..6836 keys and 6..20 rows of eight
+  //     heads 43.5 / 44.9 with some lengths, 50.0 / 47.8 with others.
   //   else   runs, unless they leave an XCD more than a quarter above the average (one sequence much longer than the others: half
   //     of the XCDs had nothing but its pieces): then in turn, every compute unit gets some of both.
   // Even batches stay in runs (24 sequences of 2048 keys, 32 rows 50.2, in lists 51.3).
@@ -1628,7 +1630,9 @@ static hipError_t configure_mfma() {
 hipError_t run_attn_mfma_plan(const AttnParams& p, void* workspace, int kv_chunk, hipStream_t st) {
   MfmaSched sc; int rows_wg;
   fill_sched(p, workspace, kv_chunk, sc, rows_wg);
-  const dim3 block(sc.by_piece == 2 ? FD_WAVE : MF_BLOCK);         // (a wave finds its piece by itself, a share of the line takes the work-group; 4.4 -> 3.9 us)
+  // a wave finds its piece by itself, a share of the line takes the work-group (kernel, four waves -> one, median of 120 launches: 4 of 32768 keys 7.2 -> 5.8 us,
+  // 2 of 272 rows 5.4 -> 4.9, 16 of 512..4096 5.1 -> 4.8, 1 of 2048 3.9 -> 3.5)
+  const dim3 block(sc.by_piece == 2 ? FD_WAVE : MF_BLOCK);
   if (rows_wg == 64) hipLaunchKernelGGL(attn_mfma_plan_kernel<2>, dim3(launch_wgs(sc)), block, 0, st, p, sc);
   else hipLaunchKernelGGL(attn_mfma_plan_kernel<4>, dim3(launch_wgs(sc)), block, 0, st, p, sc);
   return hipGetLastError();

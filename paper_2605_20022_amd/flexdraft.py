@@ -109,8 +109,8 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
-# The handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object for it, 2.7 us of
-# a call's 6 to 10; the handle alone is 0.3 us (thirteen calls of a decoding step: 115 -> 77 us on the host).
+# The handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object for it, 2.2 us of
+# a call's 8; thirteen calls of a decoding step take the host 107 us with it, 79 with the handle alone (76 with plain addresses too).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
