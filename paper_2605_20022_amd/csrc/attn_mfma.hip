@@ -1669,7 +1669,10 @@ template <int MAXRB, int PG>
 static void launch_combine(const AttnParams& p, const MfmaSched& sc, hipStream_t st) {
   // No block for rows that no sequence has: with few rows most of a sequence's blocks only returned, and the next sequence's came after them
   // (us a call: 5 of 2251..4503 keys and 20 rows of 64 21.9 -> 21.5, 7 of 14853 at head dim 64 and 50 rows 43.1 -> 42.7; 64 rows equal).
-  const int row_blocks = 32 * MAXRB * PG / 16, of_rows = (int)(((long long)p.max_new_rows * p.G * PG + 15) / 16);
+  // Rounded up to a whole number of rounds over the XCDs, so that a head's blocks run on the same one whatever the sequence (2 of 81 keys, ten heads
+  // of 288 rows 12.3 / 11.9).
+  const int row_blocks = 32 * MAXRB * PG / 16, round = sc.xcds / min(sc.xcds, p.Hkv & -p.Hkv);
+  const int of_rows = (int)(((long long)p.max_new_rows * p.G * PG + 15) / 16 + round - 1) / round * round;
   const dim3 grid = sc.by_item ? dim3(p.Hkv, min(of_rows, sc.rt_max * row_blocks), p.B) : dim3(sc.num_wgs, min(of_rows, row_blocks));
   if (p.D == 64) hipLaunchKernelGGL((attn_mfma_combine_kernel<MAXRB, 64, PG>), grid, dim3(256), 0, st, p, sc);
   else hipLaunchKernelGGL((attn_mfma_combine_kernel<MAXRB, 128, PG>), grid, dim3(256), 0, st, p, sc);
