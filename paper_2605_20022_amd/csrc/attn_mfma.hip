@@ -138,6 +138,7 @@ struct MfmaSched {
   float* part_ml;             // [2 * num_wgs][ROWS_WG][4]: running maximum (base 2), row sum, that largest magnitude, unused
   int rt_max;         // row blocks of the largest sequence
   int alone;          // 1: whatever the lengths, pieces of at most MF_ALONE tiles on num_wgs / 2 work-groups hold every item
+  int rows_last;      // != 0: the combine kernel's grid runs over the sequences before the row blocks
   int by_item;        // != 0: the combine entries are indexed by item, else by share
   // Combine entries [num_wgs + 1].
   //   by share  entry w: the split item that ends in the work-group of share w: (first packed row, head | row block << 16,
@@ -1417,13 +1418,15 @@ __global__ __launch_bounds__(256) void attn_mfma_combine_kernel(AttnParams p, Mf
   const int l16 = lane & 15;
   const int pg = PG == 1 ? 0 : lane >> 4;                      // piece group
   constexpr int ROW_BLOCKS = ROWS_WG * PG / 16;
-  const int seq = blockIdx.z, row_block = blockIdx.y % ROW_BLOCKS;            // (by item)
-  const int entry = sc_.by_item ? (seq * p.Hkv + blockIdx.x) * sc_.rt_max + blockIdx.y / ROW_BLOCKS : blockIdx.x;
+  const bool rows_last = PG > 1 && sc_.rows_last;
+  const int rows_id = rows_last ? blockIdx.z : blockIdx.y;
+  const int seq = rows_last ? blockIdx.y : blockIdx.z, row_block = rows_id % ROW_BLOCKS;            // (by item)
+  const int entry = sc_.by_item ? (seq * p.Hkv + blockIdx.x) * sc_.rt_max + rows_id / ROW_BLOCKS : blockIdx.x;
   const int4* ep4 = sc_.entries + entry;
   const int* ep = reinterpret_cast<const int*>(ep4);
   int row0, head, rt, rows_here, first_slot, wl;
   if (sc_.by_item) {
-    head = blockIdx.x; rt = blockIdx.y / ROW_BLOCKS;
+    head = blockIdx.x; rt = rows_id / ROW_BLOCKS;
     first_slot = sload(ep, 0); wl = sload(ep, 1);
     const int r0 = sload(p.row_indptr, seq), r1 = sload(p.row_indptr, seq + 1);          // (clamped as load_seq does)
     row0 = clampi(r0, 0, p.total_rows);
@@ -1585,6 +1588,9 @@ static void fill_sched(const AttnParams& p, void* workspace, int kv_chunk, MfmaS
   sc.by_item = (long long)p.B * p.Hkv * sc.rt_max <= sc.num_wgs ? 1 : 0;
   sc.by_piece = sc.by_item && p.B <= 64 && sc.fixed_share == 0 && sc.num_wgs < 1024 ? 1 : 0;      // (find_piece counts pieces in ten bits)
   const long long items_max = (long long)p.B * p.Hkv * sc.rt_max;
+  // As many items as XCDs: cut into runs each has an XCD to itself, and its blocks in the combine kernel run there (us a call, row blocks / sequences
+  // first: one KV head, 8 of 3167 keys 14.9 / 13.6, two heads, 4 of 1000..3000 12.3 / 11.8; five sequences and two heads 17.9 / 18.6).
+  sc.rows_last = items_max == sc.xcds ? 1 : 0;
   if (sc.by_piece && items_max <= sc.num_wgs / 2) sc.by_piece = 2;
   // With close to num_wgs / 2 items and one piece per work-group, an item has hardly more than one piece or two: where lengths differ, the
   // longest piece is far above the average, which long prefixes show.  The device decides there.  us a call, always pieces / the
@@ -1673,7 +1679,8 @@ static void launch_combine(const AttnParams& p, const MfmaSched& sc, hipStream_t
   // of 288 rows 12.3 / 11.9).
   const int row_blocks = 32 * MAXRB * PG / 16, round = sc.xcds / min(sc.xcds, p.Hkv & -p.Hkv);
   const int of_rows = (int)(((long long)p.max_new_rows * p.G * PG + 15) / 16 + round - 1) / round * round;
-  const dim3 grid = sc.by_item ? dim3(p.Hkv, min(of_rows, sc.rt_max * row_blocks), p.B) : dim3(sc.num_wgs, min(of_rows, row_blocks));
+  const int rows = min(of_rows, sc.rt_max * row_blocks);
+  const dim3 grid = !sc.by_item ? dim3(sc.num_wgs, min(of_rows, row_blocks)) : PG > 1 && sc.rows_last ? dim3(p.Hkv, p.B, rows) : dim3(p.Hkv, rows, p.B);
   if (p.D == 64) hipLaunchKernelGGL((attn_mfma_combine_kernel<MAXRB, 64, PG>), grid, dim3(256), 0, st, p, sc);
   else hipLaunchKernelGGL((attn_mfma_combine_kernel<MAXRB, 128, PG>), grid, dim3(256), 0, st, p, sc);
 }

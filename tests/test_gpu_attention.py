@@ -502,6 +502,21 @@ def test_row_blocks_of_the_same_tiles_share_an_xcd(fd, lens, Hkv, G, n, D):
     assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
 
 
+@pytest.mark.parametrize("lens,Hkv,G,n,D", [
+    ([900, 0, 1500, 700, 64, 2000, 130, 1], 1, 3, 34, 64),         # a sequence per XCD, 102 rows of 128
+    ([1000, 3000, 400, 65], 2, 4, 16, 128),
+    ([1000, 900], 4, 4, 1, 128),                                   # four rows: one row block
+    ([3000, 500], 1, 8, 60, 128),                                  # four row blocks, the last one of 96 rows
+    ([3000], 8, 4, 20, 128),
+])
+def test_as_many_items_as_xcds(fd, lens, Hkv, G, n, D):
+    """Eight items: the combine kernel's grid runs over the sequences before the row blocks."""
+    w = _wl("eight", "bf16", len(lens), G * Hkv, Hkv, D, 16, (max(lens), max(lens)), (n, n), 0, seed=370 + n)
+    inp = W.make_attention_inputs(w)
+    inp["kv_len"] = np.array(lens, dtype=np.int32)                 # (the page lists are long enough for all of them)
+    _check(fd, inp, "bf16", f"eight items {lens} Hkv={Hkv} n={n} D={D}", lse_tol=2e-2)
+
+
 @pytest.mark.parametrize("D,lens,Hkv,n,what", [
     (64, [2000, 2000, 2000, 4200], 64, 4, "256 items, the line"),
     (64, [2000, 4200, 2000, 2000], 64, 65, "128-row items, the line"),
